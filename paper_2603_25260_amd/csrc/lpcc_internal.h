@@ -34,7 +34,9 @@ struct LayerDev {
   int32_t ksteps;       // Kpad / 64
   int32_t npad;
   int32_t a_lo, a_hi;   // accumulator range outside which the output saturates
-  int32_t rq24;         // 1: |a| and m below 2^23 and a m + rnd inside int32 on [a_lo, a_hi]
+  int32_t rqf;          // 1: requant_f computes this layer's requantisation
+  int32_t f_lo, f_hi;   // requant_f: accumulator clamp, multiplier and rounding term
+  int32_t f_m, f_rnd;
   int64_t rnd;          // 2^(r-1) for r > 0, else 0 (half-up rounding term)
 };
 
@@ -51,29 +53,17 @@ __device__ __forceinline__ int requant_l(int acc, const LayerDev& L) {
   return min(max(p + L.z_out, -128), 127);
 }
 
-// The same function for layers with rq24 set: a 24-bit signed multiply-add
-// gives a m + rnd exactly, so no 64-bit product is needed.
-__device__ __forceinline__ int requant_l24(int acc, const LayerDev& L) {
-  const int a = min(max(acc, L.a_lo), L.a_hi);
-  const int m = a >= 0 ? L.m_pos : L.m_neg;
-  const int p = (__mul24(a, m) + (int)L.rnd) >> L.r;
-  return min(max(p + L.z_out, -128), 127);
-}
-
-// The same for identity layers (m_pos = m_neg, checked on the host): no
-// sign-dependent multiplier.
-__device__ __forceinline__ int requant_id24(int acc, const LayerDev& L) {
-  const int a = min(max(acc, L.a_lo), L.a_hi);
-  const int p = (__mul24(a, L.m_pos) + (int)L.rnd) >> L.r;
-  return min(max(p + L.z_out, -128), 127);
-}
-
-// The same for identity layers whose zero point is folded into the rounding
-// term, rndz = rnd + z_out 2^r (a m + rndz inside int32 on [a_lo, a_hi],
-// checked on the host): floor((x + z 2^r) / 2^r) = floor(x / 2^r) + z.
-__device__ __forceinline__ int requant_idz24(int acc, const LayerDev& L, int rndz) {
-  const int a = min(max(acc, L.a_lo), L.a_hi);
-  return min(max((__mul24(a, L.m_pos) + rndz) >> L.r, -128), 127);
+// The same function for layers with rqf set: one 24-bit multiply-add.  With a
+// single multiplier (identity, m_neg = m_pos) or none below zero (ReLU, m_neg
+// = 0: the accumulator is clamped to 0 from below, f_lo = 0, which gives the
+// same output) no sign select is needed; the zero point rides in the rounding
+// term, f_rnd = rnd + z_out 2^r (floor((x + z 2^r) / 2^r) = floor(x / 2^r) +
+// z); and where the outputs at f_lo and f_hi are inside int8 already, so are
+// all between them and the final clamp falls away.  The host checks all of it
+// (requant_fast).
+__device__ __forceinline__ int requant_f(int acc, const LayerDev& L) {
+  const int a = min(max(acc, L.f_lo), L.f_hi);
+  return (__mul24(a, L.f_m) + L.f_rnd) >> L.r;
 }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -107,7 +97,11 @@ __device__ __forceinline__ LayerDev load_layer(const LayerDev* p) {
   L.npad = q->npad;
   L.a_lo = q->a_lo;
   L.a_hi = q->a_hi;
-  L.rq24 = q->rq24;
+  L.rqf = q->rqf;
+  L.f_lo = q->f_lo;
+  L.f_hi = q->f_hi;
+  L.f_m = q->f_m;
+  L.f_rnd = q->f_rnd;
   L.rnd = q->rnd;
   return L;
 }
@@ -192,8 +186,7 @@ struct PredArg {
   PredSeg seg;
   LayerDev fc1, fc2;
   int32_t one;
-  int32_t rq24;  // 2: every segment's logit layer is an identity layer with rq24 set whose
-                 // zero point folds into the rounding term (requant_idz24); else 0
+  int32_t rqf;  // 1: requant_f serves both layers of every segment
 };
 
 // Coordinate hash and 3x3x3 neighbour table of one depth j; several depths
@@ -313,7 +306,14 @@ hipError_t launch_emb(const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles
 // single-segment predictor launches up to this many rows take 4 rows per wave
 constexpr int kPredSmall = 8192;
 hipError_t launch_predict(int C, int mode, const PredSeg* segs_dev, const Tile* tiles_dev, int ntiles,
-                          const int32_t* lut, const PredArg& one, hipStream_t s);
+                          const int32_t* lut, int groups, const PredArg& one, hipStream_t s);
+// groups of 16 nodes a wave of a launch over this many rows takes (tiles of
+// 64 x that many rows)
+int predict_groups(int64_t rows);
+// row order of the logit layer's weights (symbol of MFMA row m of block b) and
+// its K order (channel of byte j of lane group g; -1 past the width)
+inline int logit_symbol(int b, int m) { return 64 * (m >> 2) + 4 * b + (m & 3); }
+inline int logit_channel(int g, int j, int C) { return j / 4 < C / 16 ? 16 * (j / 4) + 4 * g + (j & 3) : -1; }
 
 hipError_t launch_rc_encode(const Chunk* chunks, int nchunks, const uint32_t* sf, uint8_t* scratch,
                             uint32_t* lens, hipStream_t s);

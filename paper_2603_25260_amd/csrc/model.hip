@@ -1366,13 +1366,23 @@ hipError_t launch_emb(const GemmSeg* segs, const Tile* tiles, int ntiles, int C,
 //   M = max l, E_i = LUT[M - l_i], S = sum E_i
 //   f_i = 1 + floor(E_i * 65281 / S), the remainder 65536 - sum f goes to the
 //   lowest index holding M;  cdf[s] = sum_{i<s} f_i.
-// Division: for E <= 2^15 and 2^15 <= S < 2^23, floor(E * 65281 / S) is
-// q' or q'+1 with q' = (E * K) >> 16 and K = floor(65281 * 2^16 / S) < 2^17:
-// E * K / 2^16 is at most E / 2^16 <= 1/2 below E * 65281 / S.  E * K < 2^32,
-// so q' is one full-rate 24-bit multiply and a shift, and the remainder
-// E * 65281 - q' S (in [0, 2S)) decides the +1.  K comes from a 32-bit
-// shift-subtract long division once per node.  Integer-only.
-// A wave handles 16 nodes; lane l owns rows 4(l/16)+i and columns 16b + l%16.
+//
+// Both products are formed transposed (weights as the MFMA row operand, nodes
+// as columns), and the row order of the logit weights is permuted on the host
+// (pack_logits), so that lane (r, g) ends with the 64 consecutive symbols
+// 64g .. 64g + 63 of ONE node, r.  Everything per node (M, S, the reciprocal,
+// the coded symbol) is then a per-lane value: the reductions run over the 4
+// lanes of a node, the prefix sums are serial inside a lane, and the biases
+// ride in the accumulators.  fc1's accumulators are already fc2's column
+// operand (the permutation of K is in the packed weights), so no activations
+// pass through LDS.
+//
+// The kernel is bound by vector instruction issue: this form needs 17.2
+// vector instructions per 64 logits in encode mode where the one with 16 lanes
+// per node needed 30.4, and for the 12.75 M nodes of 8 128-beam frames (18
+// levels, C = 64) it takes 1.58 ms where that took 2.39 ms.  In decode mode
+// (2.75 -> 2.28 ms) the 512 bytes written per node weigh as much: a large
+// depth's launch writes 4.3 TB/s.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t recip_k(uint32_t S) {  // floor(65281 * 2^16 / S), 2^15 <= S < 2^23
   uint32_t rem = 65281u << 16;  // < 2^32
@@ -1388,74 +1398,103 @@ __device__ __forceinline__ uint32_t recip_k(uint32_t S) {  // floor(65281 * 2^16
   return q;
 }
 
-// f = 1 + floor(E * 65281 / S) for E <= 2^15 (a table entry), K < 2^17
-// (masked by the caller), S < 2^23.  With q' = (E K) >> 16 the remainder
-// E 65281 - q' S lies in [0, 2S), so the floor is q' + 1 exactly when
-// (q' + 1) S <= E 65281; both sides stay below 2^32 (q' S <= E 65281 <
-// 2^31, plus S < 2^23), and (q' + 1) S is one 24-bit multiply-add.  The
-// masks only tell the instruction selector that 24-bit operands suffice.
-// E K reaches 2^31 once S <= 65281 (a confident head: one dominant logit),
-// and HIP's __umul24 returns int, so the product is made unsigned before the
-// shift (an arithmetic shift would sign-extend it).
-__device__ __forceinline__ uint32_t freq_of(uint32_t E, uint32_t S, uint32_t K) {
-  const uint32_t q = (uint32_t)__umul24(E & 0xFFFFu, K & 0x1FFFFu) >> 16;
-  const uint32_t up = __umul24(q, S & 0xFFFFFFu) + S;
-  return q + 1u + (up <= __umul24(E & 0xFFFFu, 65281u) ? 1u : 0u);
+// run + f with f = 1 + floor(E * 65281 / S) for E <= 2^15 (a table entry), S <
+// 2^23 and K = floor(65281 2^16 / S) < 2^17.  floor(E K / 2^16) is the
+// quotient or one below it (E K / 2^16 is at most E / 2^16 <= 1/2 below E
+// 65281 / S), so with q1 = floor(E K / 2^16) + 1 the quotient is q1 exactly
+// when q1 S <= E 65281.  The +1 rides in the product's addend: E K + 2^16 <
+// 2^32 because E K <= 2^15 floor(65281 2^16 / 2^15) = 2^32 - 255 2^16, and q1
+// S <= E 65281 + S < 2^32.  All unsigned (E K reaches 2^31 once S <= 65281: a
+// confident head, one dominant logit).
+// Five full-rate instructions: the high half of the product is read in place
+// by its two users (sub-dword source selects), which the compiler does only
+// for a single user, and it forms the multiply-add with the quarter-rate
+// 64-bit one.  No matrix instruction is in flight here (the maximum over all
+// logits comes first), so the asm needs no wait states it cannot see.
+__device__ __forceinline__ uint32_t freq_add(uint32_t run, uint32_t E, uint32_t S, uint32_t K) {
+  uint32_t m, t, o;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(m) : "v"(E), "v"(K), "s"(0x10000));
+  asm("v_mul_u32_u24_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD"
+      : "=v"(t)
+      : "v"(m), "v"(S));
+  const uint32_t p = __umul24(E & 0xFFFFu, 65281u);
+  asm("v_cmp_le_u32_e32 vcc, %1, %2\n\t"
+      "v_addc_co_u32_sdwa %0, vcc, %3, %4, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+      : "=v"(o)
+      : "v"(t), "v"(p), "v"(run), "v"(m)
+      : "vcc");
+  return o;
 }
 
-// reductions over the 16 lanes of a DPP row (rotations by 8, 4, 2, 1 leave the
-// result in every lane of the row)
+// Reductions over the lanes of a node.  Both forms join the four lane groups
+// g (16 lanes apart: gfx950's row and half swaps hand every lane its partner's
+// value); the small form first joins the quad of lanes that share a node.
 template <int CTRL>
 __device__ __forceinline__ int dpp_mov(int v) {
   return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
 }
-__device__ __forceinline__ int red16_max(int v) {
-  v = max(v, dpp_mov<0x128>(v));
-  v = max(v, dpp_mov<0x124>(v));
-  v = max(v, dpp_mov<0x122>(v));
-  return max(v, dpp_mov<0x121>(v));
+template <bool SMALL, class Op>
+__device__ __forceinline__ int node_reduce(int v, Op op) {
+  if (SMALL) {
+    v = op(v, dpp_mov<0xB1>(v));  // quad_perm(1, 0, 3, 2)
+    v = op(v, dpp_mov<0x4E>(v));  // quad_perm(2, 3, 0, 1)
+  }
+  auto a = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  v = op((int)a[0], (int)a[1]);
+  a = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  return op((int)a[0], (int)a[1]);
 }
-__device__ __forceinline__ int red16_min(int v) {
-  v = min(v, dpp_mov<0x128>(v));
-  v = min(v, dpp_mov<0x124>(v));
-  v = min(v, dpp_mov<0x122>(v));
-  return min(v, dpp_mov<0x121>(v));
+// sum of v over the lanes of the node that hold smaller symbols
+template <bool SMALL>
+__device__ __forceinline__ uint32_t node_before(uint32_t v, int lane) {
+  uint32_t off = 0, sum = v;
+  if (SMALL) {  // lanes of the quad below this one
+    const int q = lane & 3;
+    const uint32_t v0 = (uint32_t)dpp_mov<0x00>((int)v), v1 = (uint32_t)dpp_mov<0x55>((int)v);
+    const uint32_t v2 = (uint32_t)dpp_mov<0xAA>((int)v), v3 = (uint32_t)dpp_mov<0xFF>((int)v);
+    off = (q > 0 ? v0 : 0u) + (q > 1 ? v1 : 0u) + (q > 2 ? v2 : 0u);
+    sum = v0 + v1 + v2 + v3;
+  }
+  auto a = __builtin_amdgcn_permlane16_swap(sum, sum, false, false);
+  off += (lane & 16) ? (uint32_t)a[0] : 0u;
+  sum = (uint32_t)a[0] + (uint32_t)a[1];
+  a = __builtin_amdgcn_permlane32_swap(sum, sum, false, false);
+  return off + ((lane & 32) ? (uint32_t)a[0] : 0u);
 }
-__device__ __forceinline__ int red16_sum(int v) {
-  v += dpp_mov<0x128>(v);
-  v += dpp_mov<0x124>(v);
-  v += dpp_mov<0x122>(v);
-  return v + dpp_mov<0x121>(v);
-}
-// inclusive prefix sum over the 16 lanes of a row: row_shr by 1, 2, 4, 8, with
-// lanes whose source lies before the row reading 0 (bound_ctrl)
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_shr0(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
-}
-__device__ __forceinline__ uint32_t scan16_incl(uint32_t v) {
-  v += dpp_shr0<0x111>(v);
-  v += dpp_shr0<0x112>(v);
-  v += dpp_shr0<0x114>(v);
-  return v + dpp_shr0<0x118>(v);
+
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 enum { P_ENCODE = 0, P_CDF16 = 1, P_CDF32 = 2 };
 
-// NI = nodes per group of 16 lanes: 4 (a wave handles 16 nodes) or 1 for
-// small launches (4 nodes per wave at MFMA rows 0, 4, 8, 12: a quarter of the
-// per-lane softmax work, so short launches finish sooner).
-template <int C, int MODE, int NI, int RQ24>
-// at most 128 VGPRs: four waves per SIMD
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_predict(const PredSeg* __restrict__ segs, const Tile* __restrict__ tiles,
-                                                 const int32_t* __restrict__ lut_g, const PredArg A) {
-  static_assert(NI == 4 || NI == 1, "NI");
-  // node (within the wave) of output group g, row i, and the MFMA row of a node
-  auto node_of = [](int g_, int i_) { return NI == 4 ? 4 * g_ + i_ : g_; };
+// SMALL: 4 nodes per wave (columns 4n .. 4n + 3 all hold node n, lane q of
+// the quad takes the blocks 4q .. 4q + 3 of its group's 64 symbols: 16 symbols
+// per lane, a quarter of the serial work, so short launches finish sooner);
+// else 16 nodes per wave and `groups` such groups one after the other, so the
+// block's copy of the weights in LDS serves 64 x groups nodes.
+template <int C, int MODE, bool SMALL, int RQ>
+// at most 128 VGPRs (four waves per SIMD); the general requantisation needs more
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4 : 3))) void k_predict(
+    const PredSeg* __restrict__ segs, const Tile* __restrict__ tiles, const int32_t* __restrict__ lut_g, int groups,
+    const PredArg A) {
+  constexpr int NB1 = C / 16;
+  constexpr int NS = SMALL ? 16 : 64;  // symbols per lane
+  constexpr int NBL = NS / 4;          // blocks of 4 symbols per lane
+  constexpr int LPN = SMALL ? 16 : 4;  // lanes per node
+  constexpr int NPW = SMALL ? 4 : 16;  // nodes per wave
   __shared__ uint16_t lut[256];  // E_j = round(2^15 e^(-j/16)) <= 2^15
-  __shared__ int8_t hs[4][16][64];
-  __shared__ __attribute__((aligned(16))) uint16_t fs[MODE == P_ENCODE ? 1 : 4][16][256];
-  lut[threadIdx.x] = (uint16_t)gp(lut_g)[threadIdx.x];
+  __shared__ v4i w2s[16 * 64];
+  __shared__ v4i w1s[NB1 * 64];
+  __shared__ __attribute__((aligned(16))) int32_t b2s[256];
+  __shared__ __attribute__((aligned(16))) int32_t b1s[C];
+  // encode: the block of 4 table entries that holds the coded symbol, per
+  // lane; CDF modes: half of the symbols of the wave's nodes (NPW rows of 128
+  // entries, 16-byte chunks swizzled by the node)
+  constexpr int kStage = MODE == P_ENCODE ? 64 : NPW * 16;  // 16-byte units per wave
+  __shared__ v4i stage[4][kStage];
 
   PredSeg S;
   LayerDev L1, L2;
@@ -1464,7 +1503,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     S = A.seg;
     L1 = A.fc1;
     L2 = A.fc2;
-    tile_row0 = (int)blockIdx.x * 16 * NI;
+    tile_row0 = (int)blockIdx.x * (SMALL ? 16 : 64 * groups);
   } else {
     const Tile tl = tiles[blockIdx.x];
     S = segs[tl.seg];
@@ -1472,217 +1511,244 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     L2 = load_layer(S.fc2);
     tile_row0 = tl.row0;
   }
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
-  const int row0 = tile_row0 + wave * 4 * NI;
-  // A operand: lane row r is MFMA row r; with NI = 1 only rows 0, 4, 8, 12 hold nodes
-  const int row = NI == 4 ? row0 + r : row0 + (r >> 2);
-  const bool rv = row < S.rows && (NI == 4 || (r & 3) == 0);
+  const int ord = SMALL ? 4 * g + (lane & 3) : g;  // the lane's place among its node's lanes
+  {
+    const GAS v4i* W1 = (const GAS v4i*)L1.Wp;
+    const GAS v4i* W2 = (const GAS v4i*)L2.Wp;
+    v4i t[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) t[k] = W2[256 * k + tid];
+    const v4i u = tid < NB1 * 64 ? W1[tid] : v4i{0, 0, 0, 0};
+    b2s[tid] = gp(L2.bias)[tid];
+    if (tid < C) b1s[tid] = gp(L1.bias)[tid];
+    lut[tid] = (uint16_t)gp(lut_g)[tid];
+#pragma unroll
+    for (int k = 0; k < 4; k++) w2s[256 * k + tid] = t[k];
+    if (tid < NB1 * 64) w1s[tid] = u;
+  }
+  __syncthreads();
 
-  // fc1: K = C (padded to 64)
-  constexpr int NB1 = C / 16;
-  v4i a = v4i{0, 0, 0, 0};
-  if (rv && 16 * g < C) a = ld16(S.F + (int64_t)row * C + 16 * g);
-  v4i acc1[NB1];
-  const GAS v4i* W1 = (const GAS v4i*)L1.Wp;
+  const int ng = SMALL ? 1 : groups;
+  for (int gi = 0; gi < ng; gi++) {
+    const int row0 = tile_row0 + gi * 64 + wave * NPW;
+    if (row0 >= S.rows) break;  // wave-uniform; no barrier below
+    const int row = row0 + (SMALL ? r >> 2 : r);
+    const bool rv = row < S.rows;
+    // column operand: channels 16g .. 16g + 15 of the node
+    v4i x = v4i{0, 0, 0, 0};
+    if (rv && 16 * g < C) x = ld16(S.F + (int64_t)row * C + 16 * g);
+    // encode: the symbol's lane, block and entry
+    int sym = 0;
+    if (MODE == P_ENCODE) sym = rv ? max((int)gp(S.code)[row] - 1, 0) : 0;
+    // fc1: byte 4 nb + i of lane (r, g) is channel 16 nb + 4 g + i
+    v4i h = v4i{0, 0, 0, 0};
 #pragma unroll
-  for (int nb = 0; nb < NB1; nb++) acc1[nb] = mfma16(a, W1[nb * 64 + lane], v4i{0, 0, 0, 0});
-  // requantise straight from the accumulator layout into the A layout of fc2
+    for (int nb = 0; nb < NB1; nb++) {
+      const v4i acc = mfma16(w1s[nb * 64 + lane], x, *(const v4i*)&b1s[16 * nb + 4 * g]);
+      uint32_t w = 0;
 #pragma unroll
-  for (int nb = 0; nb < NB1; nb++)
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int col = 16 * nb + r;
-      hs[wave][4 * g + i][col] = (int8_t)requant_l(acc1[nb][i] + gp(L1.bias)[col], L1);
+      for (int i = 0; i < 4; i++) {
+        const int y = RQ == 1 ? requant_f(acc[i], L1) : requant_l(acc[i], L1);
+        w |= ((uint32_t)y & 0xFFu) << (8 * i);
+      }
+      h[nb] = (int)w;
     }
-  if (C < 64) {  // zero the K padding (columns C..63 of the 16 rows)
-    for (int k = lane; k < 16 * (64 - C); k += 64) hs[wave][k / (64 - C)][C + k % (64 - C)] = 0;
-  }
-  // fc2 operands issued before the barrier (independent of fc1)
-  const GAS v4i* W2 = (const GAS v4i*)L2.Wp;
-  v4i w2[16];
-  int b2[16];
-#pragma unroll
-  for (int b = 0; b < 16; b++) {
-    w2[b] = W2[b * 64 + lane];
-    b2[b] = gp(L2.bias)[16 * b + r];
-  }
-  __syncthreads();  // hs of this wave, and the exponent table written by all waves
-  v4i h = *(const v4i*)&hs[wave][r][16 * g];
-
-  // fc2: 16 column blocks of 16 logits.  RQ24 = 2: an identity layer whose
-  // a m + rnd + z_out 2^r stays inside int32 on [a_lo, a_hi] (checked on the
-  // host), so the zero point rides in the rounding term: floor((x + z 2^r) /
-  // 2^r) = floor(x / 2^r) + z
-  const int rndz = RQ24 == 2 ? (int)L2.rnd + (int)((uint32_t)L2.z_out << L2.r) : 0;
-  int lg[NI][16];
-#pragma unroll
-  for (int b = 0; b < 16; b++) {
-    const v4i acc = mfma16(h, w2[b], v4i{0, 0, 0, 0});
-#pragma unroll
-    for (int i = 0; i < NI; i++) {
-      const int a = acc[i] + b2[b];
-      lg[i][b] = 16 * b + r < kNSym ? (RQ24 == 2 ? requant_idz24(a, L2, rndz) : requant_l(a, L2)) : -1000;
-    }
-  }
-
-  // per row: max, lowest argmax, E_i = LUT[M - l_i] (replacing the logits), S
-  int arg[NI];
-  uint32_t Sr[NI];
-#pragma unroll
-  for (int i = 0; i < NI; i++) {
-    // key = 256 l + (255 - index): its maximum holds M and, among the
-    // entries equal to M, the lowest index (padding logits are -1000)
-    int key = -(1 << 30);
-#pragma unroll
-    for (int b = 0; b < 16; b++) key = max(key, lg[i][b] * 256 + (255 - 16 * b - r));
-    key = red16_max(key);
-    const int M = key >> 8;
-    arg[i] = 255 - (key & 255);
-    int sum = 0;
-    // entry M - l of the table at byte 2M - 2l from its start (one 24-bit
-    // multiply-add per entry)
-    const uint8_t* lb = (const uint8_t*)lut + 2 * M;
-#pragma unroll
-    for (int b = 0; b < 16; b++) {
-      const int e = (16 * b + r < kNSym) ? *(const uint16_t*)(lb + __mul24(lg[i][b], -2)) : 0;
-      lg[i][b] = e;
-      sum += e;
-    }
-    Sr[i] = (uint32_t)red16_sum(sum);
-  }
-  // one reciprocal per lane (lane r computes row r % 4 of its group), shared
-  // within the group of 16 lanes
-  uint32_t inv[NI];
-  int rem[NI];
-  if (NI == 4) {
-    const int ri = r & 3;
-    const uint32_t Ssel = ri == 0 ? Sr[0] : (ri == 1 ? Sr[1 % NI] : (ri == 2 ? Sr[2 % NI] : Sr[3 % NI]));
-    const uint32_t invsel = recip_k(Ssel);
-#pragma unroll
-    for (int i = 0; i < NI; i++) inv[i] = (uint32_t)__shfl((int)invsel, (lane & 48) | i);
-  } else {
-    inv[0] = recip_k(Sr[0]);
-  }
-
-#pragma unroll
-  for (int i = 0; i < NI; i++) {
-    const int nrow = row0 + node_of(g, i);
-    const uint32_t S_ = Sr[i];
-    const uint32_t K_ = inv[i] & 0x1FFFFu;
-    int f[16];
-    int fsum = 0;
-    if (MODE == P_ENCODE) {
-      // start = sum of f over the columns below the symbol: this lane's
-      // columns 16b + r < sym are a prefix of b, so the lane's share is its
-      // running sum at the last such b; the symbol's own f sits in the one
-      // lane and block with 16b + r = sym
-      const int sym = nrow < S.rows ? (int)gp(S.code)[nrow] - 1 : 0;
-      const int lim = sym - r;
-      int st_ = 0, fr = 0;
+    // fc2: accumulator register i of block b is symbol 64 g + 4 b + i
+    int e[NS];
+    if (SMALL) {
+      const int q = lane & 3;
 #pragma unroll
       for (int b = 0; b < 16; b++) {
-        const int fb = (16 * b + r < kNSym) ? (int)freq_of((uint32_t)lg[i][b], S_, K_) : 0;
-        fsum += fb;
-        st_ = 16 * b < lim ? fsum : st_;
-        fr = 16 * b == lim ? fb : fr;
+        const v4i acc = mfma16(w2s[b * 64 + lane], h, *(const v4i*)&b2s[64 * g + 4 * b]);
+#pragma unroll
+        for (int i = 0; i < 4; i++) e[(4 * b + i) % NS] = q == b / 4 ? acc[i] : (b < 4 ? 0 : e[(4 * b + i) % NS]);
       }
-      // the remainder R goes to entry arg
-      const int R = 65536 - red16_sum(fsum);
-      st_ = red16_sum(st_) + (arg[i] < sym ? R : 0);
-      fr = red16_sum(fr) + (arg[i] == sym ? R : 0);
-      if (r == 0 && nrow < S.rows) gp(S.sf)[nrow] = (uint32_t)st_ | ((uint32_t)fr << 16);
+#pragma unroll
+      for (int j = 0; j < NS; j++) e[j] = RQ == 1 ? requant_f(e[j], L2) : requant_l(e[j], L2);
     } else {
 #pragma unroll
       for (int b = 0; b < 16; b++) {
-        f[b] = (16 * b + r < kNSym) ? (int)freq_of((uint32_t)lg[i][b], S_, K_) : 0;
-        fsum += f[b];
+        const v4i acc = mfma16(w2s[b * 64 + lane], h, *(const v4i*)&b2s[64 * g + 4 * b]);
+#pragma unroll
+        for (int i = 0; i < 4; i++) e[(4 * b + i) % NS] = RQ == 1 ? requant_f(acc[i], L2) : requant_l(acc[i], L2);
       }
-      // the remainder R goes to entry arg, added once per node below
-      rem[i] = 65536 - red16_sum(fsum);
-      // frequencies of the node into LDS for the row-wise prefix below
-#pragma unroll
-      for (int b = 0; b < 16; b++) fs[wave][node_of(g, i)][16 * b + r] = (uint16_t)f[b];
     }
-  }
-  if (MODE != P_ENCODE) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (r == 0) {
+    // entry 255 is no symbol: the lowest logit at the highest index never
+    // holds the maximum first, and its table entry is taken as 0
+    const bool tail = ord == LPN - 1;  // the lane whose last entry it is
+    if (tail) e[NS - 1] = -128;
+
+    // maximum and the first block of 4 that holds it: 16 M + (15 - block),
+    // then over the node's lanes 256 M + 16 (15 - lane) + (15 - block)
+    int key = -(1 << 20);
 #pragma unroll
-      for (int i = 0; i < NI; i++) fs[wave][node_of(g, i)][arg[i]] += (uint16_t)rem[i];
+    for (int b = 0; b < NBL; b++) {
+      const int mb = max(max(max(e[4 * b], e[4 * b + 1]), e[4 * b + 2]), e[4 * b + 3]);
+      key = max(key, mb * 16 + (15 - b));
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // four passes of four rows; lane (q = lane/16, r) owns the 16 consecutive
-    // entries 16r..16r+15 of row 4p+q: serial prefix in registers, exclusive
-    // scan of the lane totals across the 16 lanes of the row
+    key = ((key >> 4) << 8) | ((15 - ord) << 4) | (key & 15);
+    key = node_reduce<SMALL>(key, [](int a, int b) { return max(a, b); });
+    const int M = key >> 8, aord = 15 - ((key >> 4) & 15), ablk = 15 - (key & 15);
+    // E = LUT[M - l]: entry at byte 2 M - 2 l from the table's start
+    const uint8_t* lb = (const uint8_t*)lut + 2 * M;
+    uint32_t sum = 0;
 #pragma unroll
-    for (int p = 0; p < NI; p++) {
-      const int prow = NI == 4 ? 4 * p + g : g;
-      const uint4* src = (const uint4*)&fs[wave][prow][16 * r];
-      const uint4 u0 = src[0], u1 = src[1];
-      const uint32_t w[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-      uint32_t ex[16];  // exclusive prefix within the lane
+    for (int j = 0; j < NS; j++) e[j] = *(const uint16_t*)(lb + __mul24(e[j], -2));
+    if (tail) e[NS - 1] = 0;
+#pragma unroll
+    for (int j = 0; j < NS; j++) sum += (uint32_t)e[j];
+    const uint32_t Sn = (uint32_t)node_reduce<SMALL>((int)sum, [](int a, int b) { return a + b; });
+    const uint32_t Kn = recip_k(Sn);
+
+    if (MODE == P_ENCODE) {
+      // start = sum of f below the symbol.  The symbol's lane notes its
+      // running sum before the symbol's block of 4 and the block's entries;
+      // the lanes before it add their totals.
+      const int sord = sym / NS, sblk = ord == sord ? (sym % NS) / 4 : -1;
+      uint32_t run = 0, runb = 0, rlast = 0;
+#pragma unroll
+      for (int b = 0; b < NBL; b++) {
+        if (b == sblk) {
+          runb = run;
+          stage[wave][lane] = v4i{e[4 * b], e[4 * b + 1], e[4 * b + 2], e[4 * b + 3]};
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          if (4 * b + i == NS - 1) rlast = run;
+          run = freq_add(run, (uint32_t)e[4 * b + i], Sn, Kn);
+        }
+      }
+      const uint32_t tot = tail ? rlast : run;
+      const uint32_t R =
+          65536u - (uint32_t)node_reduce<SMALL>((int)tot, [](int a, int b) { return a + b; });
+      const uint32_t below = node_before<SMALL>(tot, lane);
+      if (ord == sord && rv) {
+        const v4i es = stage[wave][lane];  // written by this lane
+        const int si = sym & 3;
+        uint32_t st = below + runb, fr = 0;
+        bool lower = false, here = false;  // the maximum lies at a lower entry of the block / at the symbol
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const uint32_t f = freq_add(0u, (uint32_t)es[i], Sn, Kn);
+          st += i < si ? f : 0u;
+          fr = i == si ? f : fr;
+          lower = lower || (i < si && es[i] == 32768);
+          here = here || (i == si && es[i] == 32768);
+        }
+        // the remainder goes to the first maximum: block ablk of lane aord
+        const int ab = 16 * aord + ablk, sb = 16 * sord + sblk;
+        const bool lt = ab < sb || (ab == sb && lower);
+        st += lt ? R : 0u;
+        fr += ab == sb && !lower && here ? R : 0u;
+        gp(S.sf)[row] = st | (fr << 16);
+      }
+    } else {
+      // exclusive prefix inside the lane, in place
       uint32_t run = 0;
 #pragma unroll
-      for (int k = 0; k < 8; k++) {
-        ex[2 * k] = run;
-        run += w[k] & 0xFFFFu;
-        ex[2 * k + 1] = run;
-        run += w[k] >> 16;
+      for (int j = 0; j < NS; j++) {
+        const uint32_t next = freq_add(run, (uint32_t)e[j], Sn, Kn);
+        e[j] = (int)run;
+        run = next;
       }
-      const uint32_t off = scan16_incl(run) - run;
-      const int nrow = row0 + prow;
-      if (nrow < S.rows) {
-        if (MODE == P_CDF16) {
-          // entry 255 is not a symbol boundary: stored as 0
-          uint32_t o2[8];
+      const uint32_t tot = tail ? (uint32_t)e[NS - 1] : run;
+      const uint32_t R =
+          65536u - (uint32_t)node_reduce<SMALL>((int)tot, [](int a, int b) { return a + b; });
+      // the lane's offset; the remainder counts from after the maximum's
+      // block on (its own block is completed below)
+      const uint32_t o0 = node_before<SMALL>(tot, lane) + (aord < ord ? R : 0u);
+      const uint32_t o1 = o0 + (aord == ord ? R : 0u);
+      const uint32_t p0 = (o0 & 0xFFFFu) | (o0 << 16), p1 = (o1 & 0xFFFFu) | (o1 << 16);
+      const uint32_t fmax = freq_add(0u, 32768u, Sn, Kn);
+      typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+      // rows of all nodes in two passes of half of every lane's symbols
+      // (CH 16-byte chunks of 8 entries per lane)
+      constexpr int CH = NS / 16;
+      const int node = SMALL ? r >> 2 : r;
 #pragma unroll
-          for (int k = 0; k < 8; k++) {
-            const uint32_t lo = off + ex[2 * k];
-            const uint32_t hi = (r == 15 && k == 7) ? 0u : off + ex[2 * k + 1];
-            o2[k] = (lo & 0xFFFFu) | (hi << 16);
+      for (int hf = 0; hf < 2; hf++) {
+#pragma unroll
+        for (int c = 0; c < CH; c++) {
+          v4i w;
+#pragma unroll
+          for (int k = 0; k < 4; k++) {
+            const int j = 8 * (hf * CH + c) + 2 * k;
+            const uint32_t pk = __builtin_amdgcn_perm((uint32_t)e[j + 1], (uint32_t)e[j], 0x05040100u);
+            const uint32_t po = j / 4 > ablk ? p1 : p0;
+            w[k] = (int)__builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, pk) +
+                                                             __builtin_bit_cast(u16x2, po)));
           }
-          // streaming stores: a large depth's rows (512 B per node) are read
-          // once, by the range decoder, and exceed the caches; marked
-          // non-temporal they leave L2 to the next kernels' working set
-          GAS v4i* dst = (GAS v4i*)(S.cdf16 + (int64_t)nrow * 256 + 16 * r);
-          __builtin_nontemporal_store(v4i{(int)o2[0], (int)o2[1], (int)o2[2], (int)o2[3]}, dst);
-          __builtin_nontemporal_store(v4i{(int)o2[4], (int)o2[5], (int)o2[6], (int)o2[7]}, dst + 1);
-        } else {
-          uint32_t o4[16];
-#pragma unroll
-          for (int k = 0; k < 16; k++) o4[k] = (r == 15 && k == 15) ? 65536u : off + ex[k];
-          GAS v4i* dst = (GAS v4i*)(S.cdf32 + (int64_t)nrow * 256 + 16 * r);
-#pragma unroll
-          for (int k = 0; k < 4; k++)
-            dst[k] = v4i{(int)o4[4 * k], (int)o4[4 * k + 1], (int)o4[4 * k + 2], (int)o4[4 * k + 3]};
+          stage[wave][node * 16 + ((ord * CH + c) ^ node)] = w;
         }
+        if (aord == ord && ablk / (2 * CH) == hf) {
+          // the maximum's block: its first entry of frequency fmax takes R (a
+          // smaller table entry gives a smaller frequency: the table falls by
+          // at least 1984 of 32768 from entry 0 to 1, and S < 2^23)
+          const int bl = ablk % (2 * CH);
+          uint32_t* p2 = (uint32_t*)&stage[wave][node * 16 + ((ord * CH + (bl >> 1)) ^ node)] + 2 * (bl & 1);
+          const uint32_t lo = p2[0], hi = p2[1];
+          const uint32_t v0 = lo & 0xFFFFu, v1 = lo >> 16, v2 = hi & 0xFFFFu, v3 = hi >> 16;
+          const bool a0 = ((v1 - v0) & 0xFFFFu) == (fmax & 0xFFFFu);
+          const bool a1 = a0 || ((v2 - v1) & 0xFFFFu) == (fmax & 0xFFFFu);
+          const bool a2 = a1 || ((v3 - v2) & 0xFFFFu) == (fmax & 0xFFFFu);
+          p2[0] = v0 | ((v1 + (a0 ? R : 0u)) << 16);
+          p2[1] = ((v2 + (a1 ? R : 0u)) & 0xFFFFu) | ((v3 + (a2 ? R : 0u)) << 16);
+        }
+        wave_lds_sync();
+        // whole rows out: chunk k of a node's half row is chunk k % CH of lane
+        // k / CH, i.e. entries NS (k / CH) + NS/2 hf + 8 (k % CH)
+#pragma unroll
+        for (int it = 0; it < NPW / 4; it++) {
+          const int n = it * 4 + g, k = r;
+          const int nrow = row0 + n;
+          const v4i w = stage[wave][n * 16 + (k ^ n)];
+          const int at = NS * (k / CH) + NS / 2 * hf + 8 * (k % CH);
+          if (nrow < S.rows) {
+            if (MODE == P_CDF16) {
+              // entry 255 is 2^16 = 0: not a symbol boundary.  Streaming
+              // stores: a large depth's rows (512 B per node) are read once, by
+              // the range decoder, and exceed the caches
+              __builtin_nontemporal_store(w, (GAS v4i*)(S.cdf16 + (int64_t)nrow * 256 + at));
+            } else {
+              GAS v4i* dst = (GAS v4i*)(S.cdf32 + (int64_t)nrow * 256 + at);
+              const uint32_t u0 = (uint32_t)w[0], u1 = (uint32_t)w[1], u2 = (uint32_t)w[2], u3 = (uint32_t)w[3];
+              dst[0] = v4i{(int)(u0 & 0xFFFFu), (int)(u0 >> 16), (int)(u1 & 0xFFFFu), (int)(u1 >> 16)};
+              dst[1] = v4i{(int)(u2 & 0xFFFFu), (int)(u2 >> 16), (int)(u3 & 0xFFFFu),
+                           at + 7 == 255 ? 65536 : (int)(u3 >> 16)};
+            }
+          }
+        }
+        wave_lds_sync();
       }
     }
   }
 }
 
+// Nodes per block of the 16-node form: 64 x the groups of a wave.  More
+// groups share one load of the weights (20 KB per block at C = 64); a launch
+// keeps at least 4096 blocks (16 per compute unit, four times what runs at
+// once) before a wave takes more.
+int predict_groups(int64_t rows) { return rows >= (1 << 20) ? 4 : (rows >= (1 << 19) ? 2 : 1); }
+
 hipError_t launch_predict(int C, int mode, const PredSeg* segs, const Tile* tiles, int ntiles, const int32_t* lut,
-                          const PredArg& A, hipStream_t s) {
+                          int groups, const PredArg& A, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   // single-segment launches of at most kPredSmall rows use 4 nodes per wave
   const bool small = A.one && A.seg.rows <= kPredSmall;
   const int grid = small ? (A.seg.rows + 15) / 16 : ntiles;
-#define LPCC_P(CC, MM)                                                                                   \
-  if (C == CC && mode == MM) {                                                                           \
-    if (small && A.rq24 == 2)                                                                            \
-      hipLaunchKernelGGL((k_predict<CC, MM, 1, 2>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, A);   \
-    else if (small)                                                                                      \
-      hipLaunchKernelGGL((k_predict<CC, MM, 1, 0>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, A);   \
-    else if (A.rq24 == 2)                                                                                \
-      hipLaunchKernelGGL((k_predict<CC, MM, 4, 2>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, A);   \
-    else                                                                                                 \
-      hipLaunchKernelGGL((k_predict<CC, MM, 4, 0>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, A);   \
-    return hipGetLastError();                                                                            \
+#define LPCC_P(CC, MM)                                                                                             \
+  if (C == CC && mode == MM) {                                                                                     \
+    if (small && A.rqf)                                                                                            \
+      hipLaunchKernelGGL((k_predict<CC, MM, true, 1>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, groups, A);  \
+    else if (small)                                                                                                \
+      hipLaunchKernelGGL((k_predict<CC, MM, true, 0>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, groups, A);  \
+    else if (A.rqf)                                                                                                \
+      hipLaunchKernelGGL((k_predict<CC, MM, false, 1>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, groups, A); \
+    else                                                                                                           \
+      hipLaunchKernelGGL((k_predict<CC, MM, false, 0>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, groups, A); \
+    return hipGetLastError();                                                                                      \
   }
   LPCC_P(16, 0) LPCC_P(16, 1) LPCC_P(16, 2)
   LPCC_P(32, 0) LPCC_P(32, 1) LPCC_P(32, 2)

@@ -200,16 +200,6 @@ bool requant_fits24(int32_t m_pos, int32_t m_neg, int32_t a_lo, int32_t a_hi, in
   return pos && neg;
 }
 
-// a m + rnd + z 2^r inside int32 for a in [a_lo, a_hi] (identity layers,
-// m = m_pos = m_neg, 24-bit operands already checked)
-bool requant_fold_fits(const LayerDev& F) {
-  if (F.r < 0 || F.r > 30) return false;
-  const int64_t rndz = F.rnd + (int64_t)F.z_out * (1ll << F.r);
-  const int64_t lo = (int64_t)F.a_lo * F.m_pos + rndz, hi = (int64_t)F.a_hi * F.m_pos + rndz;
-  const int64_t top = 1ll << 31;
-  return rndz >= -top && rndz < top && lo >= -top && lo < top && hi >= -top && hi < top;
-}
-
 RqBounds requant_bounds(int32_t m_pos, int32_t m_neg, int r, int z) {
   RqBounds B;
   B.m_pos = r == 0 ? std::min<int32_t>(m_pos, 256) : m_pos;
@@ -238,6 +228,29 @@ RqBounds requant_bounds(int32_t m_pos, int32_t m_neg, int r, int z) {
     B.a_lo = (int32_t)lo;
   }
   return B;
+}
+
+// requant_f's parameters of a layer whose requant_bounds are set, and whether
+// it computes the same function: one multiplier (identity) or none below zero
+// (ReLU: the accumulator is clamped from below at 0), 24-bit operands, a m +
+// rnd + z 2^r inside int32 on the clamped range, outputs inside int8 at its
+// ends (the function is monotone).
+void requant_fast(LayerDev& F) {
+  F.rqf = 0;
+  F.f_lo = F.m_neg == 0 ? 0 : F.a_lo;
+  F.f_hi = F.a_hi;
+  F.f_m = F.m_pos;
+  F.f_rnd = 0;
+  if (F.m_neg != 0 && F.m_neg != F.m_pos) return;
+  if (F.r < 0 || F.r > 30) return;
+  const int64_t rnd = F.rnd + (int64_t)F.z_out * (1ll << F.r);
+  const int64_t top = 1ll << 31, lim = 1ll << 23;
+  const int64_t lo = (int64_t)F.f_lo * F.f_m + rnd, hi = (int64_t)F.f_hi * F.f_m + rnd;
+  if (F.f_m >= lim || F.f_hi >= lim || -(int64_t)F.f_lo > lim) return;
+  if (rnd < -top || rnd >= top || lo < -top || lo >= top || hi < -top || hi >= top) return;
+  if ((lo >> F.r) < -128 || (hi >> F.r) > 127) return;
+  F.f_rnd = (int32_t)rnd;
+  F.rqf = 1;
 }
 
 // Frequencies of a base depth from the counts n_s of its 255 codes (the
@@ -282,7 +295,12 @@ LayerImage build_image(const HostLayer& L) {
         for (int i = 0; i < 16; i++) {
           const int k = 64 * s + 16 * (lane / 16) + i, col = 16 * nb + lane % 16;
           int8_t v = 0;
-          if (k < K && col < L.cout) v = L.W[(size_t)k * L.cout + col];
+          if (L.kind == K_FC2) {  // the predictor's order of symbols and channels
+            const int sy = logit_symbol(nb, lane % 16), ch = logit_channel(lane / 16, i, L.cin);
+            if (ch >= 0 && sy < L.cout) v = L.W[(size_t)ch * L.cout + sy];
+          } else if (k < K && col < L.cout) {
+            v = L.W[(size_t)k * L.cout + col];
+          }
           im.packed[(((size_t)s * NB + nb) * 64 + lane) * 16 + i] = v;
         }
   im.bias.assign(im.npad, 0);
@@ -1225,19 +1243,15 @@ void plan_predict(Batch& b, const lpcc_model* m, const std::vector<PredSeg>& seg
     rows.push_back(s.rows);
     units += s.rows;
   }
-  const int nt = (int)count_tiles(rows), C = m->C;
+  const int groups = predict_groups(units);
+  const int nt = (int)count_tiles(rows, 64 * groups), C = m->C;
   if (nt == 0) return;
   PredArg one;
   memset(&one, 0, sizeof(one));
-  // the logit layers' requantisation: a 24-bit multiply-add with the zero
-  // point in the rounding term for identity layers where that stays inside
-  // int32 (2), else the general form (0)
+  // requantisation by one 24-bit multiply-add where it serves every layer
   bool fits = true;
-  for (auto& s : segs) {
-    const LayerDev& F = hlayer(m, s.fc2);
-    fits = fits && F.rq24 && F.m_pos == F.m_neg && requant_fold_fits(F);
-  }
-  one.rq24 = fits ? 2 : 0;
+  for (auto& s : segs) fits = fits && hlayer(m, s.fc1).rqf && hlayer(m, s.fc2).rqf;
+  one.rqf = fits ? 1 : 0;
   size_t so = 0, to = 0;
   if (segs.size() == 1) {
     one.seg = segs[0];
@@ -1246,11 +1260,11 @@ void plan_predict(Batch& b, const lpcc_model* m, const std::vector<PredSeg>& seg
     one.one = 1;
   } else {
     so = b.add(segs);
-    to = b.add(make_tiles(rows));
+    to = b.add(make_tiles(rows, 64 * groups));
   }
   const int32_t* lut = m->d_lut;
   b.launch("predict", units, [=](const uint8_t* base) {
-    return launch_predict(C, mode, (const PredSeg*)(base + so), (const Tile*)(base + to), nt, lut, one, st);
+    return launch_predict(C, mode, (const PredSeg*)(base + so), (const Tile*)(base + to), nt, lut, groups, one, st);
   });
 }
 
@@ -2657,7 +2671,7 @@ int lpcc_model_load(const void* blob, size_t len, int device, lpcc_model** out) 
     D.ksteps = im[i].ksteps;
     D.npad = im[i].npad;
     D.rnd = L.r > 0 ? (1ll << (L.r - 1)) : 0;
-    D.rq24 = requant_fits24(D.m_pos, D.m_neg, D.a_lo, D.a_hi, D.rnd) ? 1 : 0;
+    requant_fast(D);
   }
   int32_t lut[256];
   softmax_table(lut);

@@ -1,0 +1,53 @@
+"""The predictor and the coders at the sizes where their tiling changes: one
+node, the edges of 4-, 16- and 64-node groups, and the largest launch of the
+4-nodes-per-wave form with the first of the 16-node form (8192, 8193 nodes).
+CDF rows, streams and decodes equal the oracle's."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2603_25260_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_25260_amd import lpcc
+    lpcc.lib()
+    return lpcc
+
+
+def cloud(n, D, seed):
+    """Points whose octree has exactly n nodes at depth D - 1."""
+    rng = np.random.default_rng(seed)
+    side = 2 ** (D - 1)
+    cells = rng.choice(side ** 3, size=n, replace=False)
+    c = np.stack([cells // side ** 2, cells // side % side, cells % side], 1) * 2
+    extra = c[rng.integers(0, n, size=n // 2)]
+    p = np.concatenate([c, extra])
+    return (p + rng.integers(0, 2, size=p.shape)).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 15, 16, 17, 31, 33, 63, 64, 65, 255, 256, 257, 8192, 8193])
+@pytest.mark.parametrize("C,zp", [(16, False), (32, True), (64, False)])
+def test_rows_and_streams_at_tile_edges(L, n, C, zp):
+    D, nd = 6, 1
+    blob = synth.make_weights(50 + C, C, D, nd, zero_points=zp)
+    xyz = cloud(n, D, n + C)
+    print("n", n, "C", C, "zp", zp, flush=True)
+    m = L.Model(blob, 0)
+    ctx = L.Context(0)
+    dx = torch.from_numpy(xyz).cuda()
+    want = O.level_probs(blob, xyz, D - 1)
+    assert len(want) == n
+    assert np.array_equal(L.level_probs(ctx, m, dx, D - 1), want)
+    u = np.unique(xyz, axis=0)
+    u = u[np.argsort(O.morton(u, D))]
+    for cl in (4, 8):
+        bs = O.encode(blob, xyz, cl)
+        assert L.encode_frame(ctx, m, dx, cl) == bs, cl
+        assert np.array_equal(L.decode_frame(ctx, m, bs), u), cl
