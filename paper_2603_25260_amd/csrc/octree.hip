@@ -724,6 +724,13 @@ __global__ __launch_bounds__(256) void k_kmap_tree(const int32_t* __restrict__ p
     tree_taps(std::make_integer_sequence<int, 27>{}, cc, cs, ox, oy, oz, out, kstride, m);
     out[27 * kstride] = (int32_t)m;
   }
+  // rows no parent has a child for (codes that claim fewer children than the
+  // stream's header, which the expansion reports): no neighbours, so that no
+  // gather follows what an earlier call left there
+  if (pe == np) {
+    for (int64_t k = max((int64_t)c1, (int64_t)0) + threadIdx.x; k < kstride; k += 256)
+      for (int t = 0; t < 28; t++) gp(kmap)[t * kstride + k] = t < 27 ? -1 : 0;
+  }
 }
 
 hipError_t launch_kmap_tree(const int32_t* pkmap, int64_t np, const uint8_t* pcode, const int32_t* pcstart,
