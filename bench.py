@@ -171,25 +171,24 @@ def frame_work(N, P, C, D, n_deep):
 
 def step_work(ws, stream_bytes):
     """Algorithmic work per family of one encode + one decode of the frames
-    whose frame_work dicts are ``ws``.  The predictor writes 4 B per node in
-    encode mode and a 510 B frequency-table row in decode mode; the range
-    decoder reads that row and the stream."""
+    whose frame_work dicts are ``ws``.  The encoder's predictor writes 4 B per
+    node; the decoder's runs in one launch with the range decoder ("decode":
+    features and stream in, one code byte per node out)."""
     fam = {}
     for f in ("conv", "down", "skip", "emb", "up"):
         fam[f] = {k: 2 * sum(w[f][k] for w in ws) for k in ("macs", "bytes", "ops", "nodes")}
     n = sum(w["predict"]["nodes"] for w in ws)
     p = {k: sum(w["predict"][k] for w in ws) for k in ("macs", "bytes", "ops")}
-    fam["predict"] = {"macs": 2 * p["macs"], "bytes": 2 * p["bytes"] + n * (4 + 510), "ops": 2 * p["ops"],
-                      "nodes": 2 * n}
+    fam["predict"] = {"macs": p["macs"], "bytes": p["bytes"] + n * 4, "ops": p["ops"], "nodes": n}
+    fam["decode"] = {"macs": p["macs"], "bytes": p["bytes"] + n + stream_bytes, "ops": p["ops"], "nodes": n}
     fam["rc_encode"] = {"macs": 0, "bytes": n * 4 + stream_bytes, "ops": 0, "nodes": n}
-    fam["rc_decode"] = {"macs": 0, "bytes": n * 510 + stream_bytes, "ops": 0, "nodes": n}
     return fam
 
 
 # bound of each family's roofline: the model stages gather rows from HBM, the
-# softmax is plain integer arithmetic, the coders move frequency rows
+# softmax is plain integer arithmetic, the range encoder moves symbol ranges
 FAMILY_BOUND = {"conv": "hbm", "down": "hbm", "skip": "hbm", "emb": "hbm", "up": "hbm", "predict": "alu",
-                "rc_encode": "hbm", "rc_decode": "hbm"}
+                "decode": "alu", "rc_encode": "hbm"}
 
 
 # HBM bytes per headline step and family, (read, write), from rocprofv3
@@ -264,7 +263,7 @@ def roofline_of(fam, work, launches, ms, traffic_ok=False):
 
 # launch families of the library (its timing names); the octree build's
 # sort and level kernels are launched outside them
-FAMILIES = ("conv", "down", "skip", "emb", "up", "predict", "rc_encode", "rc_decode", "hash", "expand", "pack",
+FAMILIES = ("conv", "down", "skip", "emb", "up", "predict", "decode", "rc_encode", "hash", "expand", "pack",
             "base")
 
 

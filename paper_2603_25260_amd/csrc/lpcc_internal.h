@@ -166,7 +166,6 @@ struct PredSeg {
   const LayerDev* fc1;
   const LayerDev* fc2;
   uint32_t* sf;            // encode: start | freq << 16 per node
-  uint16_t* cdf16;         // decode: cdf[0..254] per node (256 slots)
   int32_t* cdf32;          // level_probs: cdf[0..255] per node
   int32_t rows;
   int32_t pad_;
@@ -187,6 +186,14 @@ struct PredArg {
   LayerDev fc1, fc2;
   int32_t one;
   int32_t rqf;  // 1: requant_f serves both layers of every segment
+};
+
+// One depth of a decode: the features of its nodes and the predictor's layers
+struct DecArg {
+  const int8_t* F;  // [rows][C]
+  LayerDev fc1, fc2;
+  int32_t rqf;      // as PredArg
+  int32_t pad_;
 };
 
 // Coordinate hash and 3x3x3 neighbour table of one depth j; several depths
@@ -336,6 +343,11 @@ hipError_t launch_rc_pack_dev(const Chunk* chunks, int nchunks, const int32_t* f
 // csum (optional): per chunk, the number of children its decoded codes announce
 hipError_t launch_rc_decode_sized(const Chunk* chunks, int nchunks, const uint8_t* payload, const uint16_t* cdf16,
                                   uint8_t* codes, uint32_t* csum, uint32_t* err, size_t max_len, hipStream_t s);
+// Predictor and range decoder of one depth in one launch (the codes and, per
+// chunk, the number of children they announce)
+hipError_t launch_decode_chunks(int C, const Chunk* chunks, int nchunks, const uint8_t* payload, const int32_t* lut,
+                                const DecArg& A, uint8_t* codes, uint32_t* csum, uint32_t* err, size_t max_len,
+                                hipStream_t s);
 // Child expansion by decoded chunk (one block per chunk) from the chunks'
 // child counts: keys of V_{d+1}, first-child rows, and, when table is not
 // null, insertion of the children into the hash table of depth d+1.

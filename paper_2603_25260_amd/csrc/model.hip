@@ -1380,9 +1380,7 @@ hipError_t launch_emb(const GemmSeg* segs, const Tile* tiles, int ntiles, int C,
 // The kernel is bound by vector instruction issue: this form needs 17.2
 // vector instructions per 64 logits in encode mode where the one with 16 lanes
 // per node needed 30.4, and for the 12.75 M nodes of 8 128-beam frames (18
-// levels, C = 64) it takes 1.58 ms where that took 2.39 ms.  In decode mode
-// (2.75 -> 2.28 ms) the 512 bytes written per node weigh as much: a large
-// depth's launch writes 4.3 TB/s.
+// levels, C = 64) it takes 1.58 ms where that took 2.39 ms.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t recip_k(uint32_t S) {  // floor(65281 * 2^16 / S), 2^15 <= S < 2^23
   uint32_t rem = 65281u << 16;  // < 2^32
@@ -1468,7 +1466,161 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-enum { P_ENCODE = 0, P_CDF16 = 1, P_CDF32 = 2 };
+// Per-node results of the logits, held by each of the node's lanes.
+struct NodeSum {
+  uint32_t S, K;  // sum of the table entries, floor(65281 2^16 / S)
+  int aord, ablk;  // lane (in the node's order) and block of 4 of the first maximum
+  int ord;         // this lane's place among its node's lanes
+  bool tail;       // this lane's last entry is 255, which is no symbol
+};
+
+// Table entries e[j] of this lane's NS symbols, from the column operand x
+// (channels 16g .. 16g + 15 of the node).  w1(k), w2(k): this lane's packed
+// weights of block k (from LDS or global memory), b1, b2: biases.
+template <int C, bool SMALL, int RQ, class W1, class W2>
+__device__ __forceinline__ void predict_table(W1 w1, W2 w2, const int32_t* b1, const int32_t* b2, const uint16_t* lut,
+                                              const v4i x, int lane, const LayerDev& L1, const LayerDev& L2,
+                                              int (&e)[SMALL ? 16 : 64], NodeSum& n) {
+  constexpr int NB1 = C / 16;
+  constexpr int NS = SMALL ? 16 : 64;  // symbols per lane
+  constexpr int NBL = NS / 4;          // blocks of 4 symbols per lane
+  constexpr int LPN = SMALL ? 16 : 4;  // lanes per node
+  const int g = lane >> 4, q = lane & 3;
+  n.ord = SMALL ? 4 * g + q : g;
+  n.tail = n.ord == LPN - 1;
+  // fc1: byte 4 nb + i of lane (r, g) is channel 16 nb + 4 g + i
+  v4i h = v4i{0, 0, 0, 0};
+#pragma unroll
+  for (int nb = 0; nb < NB1; nb++) {
+    const v4i acc = mfma16(w1(nb), x, *(const v4i*)&b1[16 * nb + 4 * g]);
+    uint32_t w = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int y = RQ == 1 ? requant_f(acc[i], L1) : requant_l(acc[i], L1);
+      w |= ((uint32_t)y & 0xFFu) << (8 * i);
+    }
+    h[nb] = (int)w;
+  }
+  // fc2: accumulator register i of block b is symbol 64 g + 4 b + i
+  if (SMALL) {
+#pragma unroll
+    for (int b = 0; b < 16; b++) {
+      const v4i acc = mfma16(w2(b), h, *(const v4i*)&b2[64 * g + 4 * b]);
+#pragma unroll
+      for (int i = 0; i < 4; i++) e[(4 * b + i) % NS] = b < 4 || q == b / 4 ? acc[i] : e[(4 * b + i) % NS];
+      if (b % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < NS; j++) e[j] = RQ == 1 ? requant_f(e[j], L2) : requant_l(e[j], L2);
+  } else {
+    // the weights of the next two blocks are in flight while two are
+    // multiplied; the scheduling barriers keep all loads from moving to the
+    // front (64 registers on top of the 64 logits)
+    v4i w[2][2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) w[0][k] = w2(k);
+#pragma unroll
+    for (int p = 0; p < 8; p++) {
+      if (p < 7) {
+#pragma unroll
+        for (int k = 0; k < 2; k++) w[(p + 1) & 1][k] = w2(2 * p + 2 + k);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        const int b = 2 * p + k;
+        const v4i acc = mfma16(w[p & 1][k], h, *(const v4i*)&b2[64 * g + 4 * b]);
+#pragma unroll
+        for (int i = 0; i < 4; i++) e[(4 * b + i) % NS] = RQ == 1 ? requant_f(acc[i], L2) : requant_l(acc[i], L2);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // entry 255 is no symbol: the lowest logit at the highest index never
+  // holds the maximum first, and its table entry is taken as 0
+  if (n.tail) e[NS - 1] = -128;
+  // maximum and the first block of 4 that holds it: 16 M + (15 - block),
+  // then over the node's lanes 256 M + 16 (15 - lane) + (15 - block)
+  int key = -(1 << 20);
+#pragma unroll
+  for (int b = 0; b < NBL; b++) {
+    const int mb = max(max(max(e[4 * b], e[4 * b + 1]), e[4 * b + 2]), e[4 * b + 3]);
+    key = max(key, mb * 16 + (15 - b));
+  }
+  key = ((key >> 4) << 8) | ((15 - n.ord) << 4) | (key & 15);
+  key = node_reduce<SMALL>(key, [](int a, int b) { return max(a, b); });
+  const int M = key >> 8;
+  n.aord = 15 - ((key >> 4) & 15);
+  n.ablk = 15 - (key & 15);
+  // E = LUT[M - l]: entry at byte 2 M - 2 l from the table's start
+  const uint8_t* lb = (const uint8_t*)lut + 2 * M;
+  uint32_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < NS; j++) {
+    e[j] = *(const uint16_t*)(lb + __mul24(e[j], -2));
+    if (j % 16 == 15) __builtin_amdgcn_sched_barrier(0);
+  }
+  if (n.tail) e[NS - 1] = 0;
+#pragma unroll
+  for (int j = 0; j < NS; j++) sum += (uint32_t)e[j];
+  n.S = (uint32_t)node_reduce<SMALL>((int)sum, [](int a, int b) { return a + b; });
+  n.K = recip_k(n.S);
+}
+
+// The CDF row of the node, in place: e[j] becomes the exclusive prefix inside
+// the lane; p0 / p1 are the packed offsets of the pairs up to / after the
+// block of the first maximum (mod 2^16), R the remainder it takes.
+template <bool SMALL>
+__device__ __forceinline__ void row_prefix(int (&e)[SMALL ? 16 : 64], const NodeSum& n, int lane, uint32_t& p0,
+                                           uint32_t& p1, uint32_t& R) {
+  constexpr int NS = SMALL ? 16 : 64;
+  uint32_t run = 0;
+#pragma unroll
+  for (int j = 0; j < NS; j++) {
+    const uint32_t next = freq_add(run, (uint32_t)e[j], n.S, n.K);
+    e[j] = (int)run;
+    run = next;
+  }
+  const uint32_t tot = n.tail ? (uint32_t)e[NS - 1] : run;
+  R = 65536u - (uint32_t)node_reduce<SMALL>((int)tot, [](int a, int b) { return a + b; });
+  const uint32_t o0 = node_before<SMALL>(tot, lane) + (n.aord < n.ord ? R : 0u);
+  const uint32_t o1 = o0 + (n.aord == n.ord ? R : 0u);
+  p0 = (o0 & 0xFFFFu) | (o0 << 16);
+  p1 = (o1 & 0xFFFFu) | (o1 << 16);
+}
+
+// 8 entries of the row (chunk c of this lane's symbols) as 16-bit values;
+// entry 255 comes out as 2^16 = 0
+template <int NS>
+__device__ __forceinline__ v4i row_chunk(const int (&e)[NS], int c, int ablk, uint32_t p0, uint32_t p1) {
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  v4i w;
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    const int j = 8 * c + 2 * k;
+    const uint32_t pk = __builtin_amdgcn_perm((uint32_t)e[j + 1], (uint32_t)e[j], 0x05040100u);
+    const uint32_t po = j / 4 > ablk ? p1 : p0;
+    w[k] = (int)__builtin_bit_cast(uint32_t,
+                                   (u16x2)(__builtin_bit_cast(u16x2, pk) + __builtin_bit_cast(u16x2, po)));
+  }
+  return w;
+}
+
+// The block of the first maximum (4 entries at p, not counting R yet): the
+// entries after its first one of frequency fmax, the largest, take R (a
+// smaller table entry gives a smaller frequency: the table falls by at least
+// 1984 of 32768 from entry 0 to 1, and S < 2^23).
+__device__ __forceinline__ void row_remainder(uint32_t* p, const NodeSum& n, uint32_t R) {
+  const uint32_t fmax = freq_add(0u, 32768u, n.S, n.K) & 0xFFFFu;
+  const uint32_t lo = p[0], hi = p[1];
+  const uint32_t v0 = lo & 0xFFFFu, v1 = lo >> 16, v2 = hi & 0xFFFFu, v3 = hi >> 16;
+  const bool a0 = ((v1 - v0) & 0xFFFFu) == fmax;
+  const bool a1 = a0 || ((v2 - v1) & 0xFFFFu) == fmax;
+  const bool a2 = a1 || ((v3 - v2) & 0xFFFFu) == fmax;
+  p[0] = v0 | ((v1 + (a0 ? R : 0u)) << 16);
+  p[1] = ((v2 + (a1 ? R : 0u)) & 0xFFFFu) | ((v3 + (a2 ? R : 0u)) << 16);
+}
+
+enum { P_ENCODE = 0, P_CDF32 = 2 };
 
 // SMALL: 4 nodes per wave (columns 4n .. 4n + 3 all hold node n, lane q of
 // the quad takes the blocks 4q .. 4q + 3 of its group's 64 symbols: 16 symbols
@@ -1483,7 +1635,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
   constexpr int NB1 = C / 16;
   constexpr int NS = SMALL ? 16 : 64;  // symbols per lane
   constexpr int NBL = NS / 4;          // blocks of 4 symbols per lane
-  constexpr int LPN = SMALL ? 16 : 4;  // lanes per node
   constexpr int NPW = SMALL ? 4 : 16;  // nodes per wave
   __shared__ uint16_t lut[256];  // E_j = round(2^15 e^(-j/16)) <= 2^15
   __shared__ v4i w2s[16 * 64];
@@ -1491,7 +1642,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
   __shared__ __attribute__((aligned(16))) int32_t b2s[256];
   __shared__ __attribute__((aligned(16))) int32_t b1s[C];
   // encode: the block of 4 table entries that holds the coded symbol, per
-  // lane; CDF modes: half of the symbols of the wave's nodes (NPW rows of 128
+  // lane; CDF rows: half of the symbols of the wave's nodes (NPW rows of 128
   // entries, 16-byte chunks swizzled by the node)
   constexpr int kStage = MODE == P_ENCODE ? 64 : NPW * 16;  // 16-byte units per wave
   __shared__ v4i stage[4][kStage];
@@ -1513,7 +1664,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
   }
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int r = lane & 15, g = lane >> 4;
-  const int ord = SMALL ? 4 * g + (lane & 3) : g;  // the lane's place among its node's lanes
   {
     const GAS v4i* W1 = (const GAS v4i*)L1.Wp;
     const GAS v4i* W2 = (const GAS v4i*)L2.Wp;
@@ -1536,77 +1686,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
     if (row0 >= S.rows) break;  // wave-uniform; no barrier below
     const int row = row0 + (SMALL ? r >> 2 : r);
     const bool rv = row < S.rows;
-    // column operand: channels 16g .. 16g + 15 of the node
     v4i x = v4i{0, 0, 0, 0};
     if (rv && 16 * g < C) x = ld16(S.F + (int64_t)row * C + 16 * g);
-    // encode: the symbol's lane, block and entry
     int sym = 0;
     if (MODE == P_ENCODE) sym = rv ? max((int)gp(S.code)[row] - 1, 0) : 0;
-    // fc1: byte 4 nb + i of lane (r, g) is channel 16 nb + 4 g + i
-    v4i h = v4i{0, 0, 0, 0};
-#pragma unroll
-    for (int nb = 0; nb < NB1; nb++) {
-      const v4i acc = mfma16(w1s[nb * 64 + lane], x, *(const v4i*)&b1s[16 * nb + 4 * g]);
-      uint32_t w = 0;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int y = RQ == 1 ? requant_f(acc[i], L1) : requant_l(acc[i], L1);
-        w |= ((uint32_t)y & 0xFFu) << (8 * i);
-      }
-      h[nb] = (int)w;
-    }
-    // fc2: accumulator register i of block b is symbol 64 g + 4 b + i
     int e[NS];
-    if (SMALL) {
-      const int q = lane & 3;
-#pragma unroll
-      for (int b = 0; b < 16; b++) {
-        const v4i acc = mfma16(w2s[b * 64 + lane], h, *(const v4i*)&b2s[64 * g + 4 * b]);
-#pragma unroll
-        for (int i = 0; i < 4; i++) e[(4 * b + i) % NS] = q == b / 4 ? acc[i] : (b < 4 ? 0 : e[(4 * b + i) % NS]);
-      }
-#pragma unroll
-      for (int j = 0; j < NS; j++) e[j] = RQ == 1 ? requant_f(e[j], L2) : requant_l(e[j], L2);
-    } else {
-#pragma unroll
-      for (int b = 0; b < 16; b++) {
-        const v4i acc = mfma16(w2s[b * 64 + lane], h, *(const v4i*)&b2s[64 * g + 4 * b]);
-#pragma unroll
-        for (int i = 0; i < 4; i++) e[(4 * b + i) % NS] = RQ == 1 ? requant_f(acc[i], L2) : requant_l(acc[i], L2);
-      }
-    }
-    // entry 255 is no symbol: the lowest logit at the highest index never
-    // holds the maximum first, and its table entry is taken as 0
-    const bool tail = ord == LPN - 1;  // the lane whose last entry it is
-    if (tail) e[NS - 1] = -128;
-
-    // maximum and the first block of 4 that holds it: 16 M + (15 - block),
-    // then over the node's lanes 256 M + 16 (15 - lane) + (15 - block)
-    int key = -(1 << 20);
-#pragma unroll
-    for (int b = 0; b < NBL; b++) {
-      const int mb = max(max(max(e[4 * b], e[4 * b + 1]), e[4 * b + 2]), e[4 * b + 3]);
-      key = max(key, mb * 16 + (15 - b));
-    }
-    key = ((key >> 4) << 8) | ((15 - ord) << 4) | (key & 15);
-    key = node_reduce<SMALL>(key, [](int a, int b) { return max(a, b); });
-    const int M = key >> 8, aord = 15 - ((key >> 4) & 15), ablk = 15 - (key & 15);
-    // E = LUT[M - l]: entry at byte 2 M - 2 l from the table's start
-    const uint8_t* lb = (const uint8_t*)lut + 2 * M;
-    uint32_t sum = 0;
-#pragma unroll
-    for (int j = 0; j < NS; j++) e[j] = *(const uint16_t*)(lb + __mul24(e[j], -2));
-    if (tail) e[NS - 1] = 0;
-#pragma unroll
-    for (int j = 0; j < NS; j++) sum += (uint32_t)e[j];
-    const uint32_t Sn = (uint32_t)node_reduce<SMALL>((int)sum, [](int a, int b) { return a + b; });
-    const uint32_t Kn = recip_k(Sn);
+    NodeSum n;
+    predict_table<C, SMALL, RQ>([&](int k) { return w1s[k * 64 + lane]; }, [&](int k) { return w2s[k * 64 + lane]; },
+                                b1s, b2s, lut, x, lane, L1, L2, e, n);
 
     if (MODE == P_ENCODE) {
       // start = sum of f below the symbol.  The symbol's lane notes its
       // running sum before the symbol's block of 4 and the block's entries;
       // the lanes before it add their totals.
-      const int sord = sym / NS, sblk = ord == sord ? (sym % NS) / 4 : -1;
+      const int sord = sym / NS, sblk = n.ord == sord ? (sym % NS) / 4 : -1;
       uint32_t run = 0, runb = 0, rlast = 0;
 #pragma unroll
       for (int b = 0; b < NBL; b++) {
@@ -1617,52 +1710,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
 #pragma unroll
         for (int i = 0; i < 4; i++) {
           if (4 * b + i == NS - 1) rlast = run;
-          run = freq_add(run, (uint32_t)e[4 * b + i], Sn, Kn);
+          run = freq_add(run, (uint32_t)e[4 * b + i], n.S, n.K);
         }
       }
-      const uint32_t tot = tail ? rlast : run;
+      const uint32_t tot = n.tail ? rlast : run;
       const uint32_t R =
           65536u - (uint32_t)node_reduce<SMALL>((int)tot, [](int a, int b) { return a + b; });
       const uint32_t below = node_before<SMALL>(tot, lane);
-      if (ord == sord && rv) {
+      if (n.ord == sord && rv) {
         const v4i es = stage[wave][lane];  // written by this lane
         const int si = sym & 3;
         uint32_t st = below + runb, fr = 0;
         bool lower = false, here = false;  // the maximum lies at a lower entry of the block / at the symbol
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          const uint32_t f = freq_add(0u, (uint32_t)es[i], Sn, Kn);
+          const uint32_t f = freq_add(0u, (uint32_t)es[i], n.S, n.K);
           st += i < si ? f : 0u;
           fr = i == si ? f : fr;
           lower = lower || (i < si && es[i] == 32768);
           here = here || (i == si && es[i] == 32768);
         }
         // the remainder goes to the first maximum: block ablk of lane aord
-        const int ab = 16 * aord + ablk, sb = 16 * sord + sblk;
+        const int ab = 16 * n.aord + n.ablk, sb = 16 * sord + sblk;
         const bool lt = ab < sb || (ab == sb && lower);
         st += lt ? R : 0u;
         fr += ab == sb && !lower && here ? R : 0u;
         gp(S.sf)[row] = st | (fr << 16);
       }
     } else {
-      // exclusive prefix inside the lane, in place
-      uint32_t run = 0;
-#pragma unroll
-      for (int j = 0; j < NS; j++) {
-        const uint32_t next = freq_add(run, (uint32_t)e[j], Sn, Kn);
-        e[j] = (int)run;
-        run = next;
-      }
-      const uint32_t tot = tail ? (uint32_t)e[NS - 1] : run;
-      const uint32_t R =
-          65536u - (uint32_t)node_reduce<SMALL>((int)tot, [](int a, int b) { return a + b; });
-      // the lane's offset; the remainder counts from after the maximum's
-      // block on (its own block is completed below)
-      const uint32_t o0 = node_before<SMALL>(tot, lane) + (aord < ord ? R : 0u);
-      const uint32_t o1 = o0 + (aord == ord ? R : 0u);
-      const uint32_t p0 = (o0 & 0xFFFFu) | (o0 << 16), p1 = (o1 & 0xFFFFu) | (o1 << 16);
-      const uint32_t fmax = freq_add(0u, 32768u, Sn, Kn);
-      typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+      uint32_t p0, p1, R;
+      row_prefix<SMALL>(e, n, lane, p0, p1, R);
       // rows of all nodes in two passes of half of every lane's symbols
       // (CH 16-byte chunks of 8 entries per lane)
       constexpr int CH = NS / 16;
@@ -1670,60 +1747,303 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
 #pragma unroll
       for (int hf = 0; hf < 2; hf++) {
 #pragma unroll
-        for (int c = 0; c < CH; c++) {
-          v4i w;
-#pragma unroll
-          for (int k = 0; k < 4; k++) {
-            const int j = 8 * (hf * CH + c) + 2 * k;
-            const uint32_t pk = __builtin_amdgcn_perm((uint32_t)e[j + 1], (uint32_t)e[j], 0x05040100u);
-            const uint32_t po = j / 4 > ablk ? p1 : p0;
-            w[k] = (int)__builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, pk) +
-                                                             __builtin_bit_cast(u16x2, po)));
-          }
-          stage[wave][node * 16 + ((ord * CH + c) ^ node)] = w;
-        }
-        if (aord == ord && ablk / (2 * CH) == hf) {
-          // the maximum's block: its first entry of frequency fmax takes R (a
-          // smaller table entry gives a smaller frequency: the table falls by
-          // at least 1984 of 32768 from entry 0 to 1, and S < 2^23)
-          const int bl = ablk % (2 * CH);
-          uint32_t* p2 = (uint32_t*)&stage[wave][node * 16 + ((ord * CH + (bl >> 1)) ^ node)] + 2 * (bl & 1);
-          const uint32_t lo = p2[0], hi = p2[1];
-          const uint32_t v0 = lo & 0xFFFFu, v1 = lo >> 16, v2 = hi & 0xFFFFu, v3 = hi >> 16;
-          const bool a0 = ((v1 - v0) & 0xFFFFu) == (fmax & 0xFFFFu);
-          const bool a1 = a0 || ((v2 - v1) & 0xFFFFu) == (fmax & 0xFFFFu);
-          const bool a2 = a1 || ((v3 - v2) & 0xFFFFu) == (fmax & 0xFFFFu);
-          p2[0] = v0 | ((v1 + (a0 ? R : 0u)) << 16);
-          p2[1] = ((v2 + (a1 ? R : 0u)) & 0xFFFFu) | ((v3 + (a2 ? R : 0u)) << 16);
+        for (int c = 0; c < CH; c++)
+          stage[wave][node * 16 + ((n.ord * CH + c) ^ node)] = row_chunk<NS>(e, hf * CH + c, n.ablk, p0, p1);
+        if (n.aord == n.ord && n.ablk / (2 * CH) == hf) {
+          const int bl = n.ablk % (2 * CH);
+          row_remainder((uint32_t*)&stage[wave][node * 16 + ((n.ord * CH + (bl >> 1)) ^ node)] + 2 * (bl & 1), n, R);
         }
         wave_lds_sync();
         // whole rows out: chunk k of a node's half row is chunk k % CH of lane
         // k / CH, i.e. entries NS (k / CH) + NS/2 hf + 8 (k % CH)
 #pragma unroll
         for (int it = 0; it < NPW / 4; it++) {
-          const int n = it * 4 + g, k = r;
-          const int nrow = row0 + n;
-          const v4i w = stage[wave][n * 16 + (k ^ n)];
+          const int nn = it * 4 + g, k = r;
+          const int nrow = row0 + nn;
+          const v4i w = stage[wave][nn * 16 + (k ^ nn)];
           const int at = NS * (k / CH) + NS / 2 * hf + 8 * (k % CH);
           if (nrow < S.rows) {
-            if (MODE == P_CDF16) {
-              // entry 255 is 2^16 = 0: not a symbol boundary.  Streaming
-              // stores: a large depth's rows (512 B per node) are read once, by
-              // the range decoder, and exceed the caches
-              __builtin_nontemporal_store(w, (GAS v4i*)(S.cdf16 + (int64_t)nrow * 256 + at));
-            } else {
-              GAS v4i* dst = (GAS v4i*)(S.cdf32 + (int64_t)nrow * 256 + at);
-              const uint32_t u0 = (uint32_t)w[0], u1 = (uint32_t)w[1], u2 = (uint32_t)w[2], u3 = (uint32_t)w[3];
-              dst[0] = v4i{(int)(u0 & 0xFFFFu), (int)(u0 >> 16), (int)(u1 & 0xFFFFu), (int)(u1 >> 16)};
-              dst[1] = v4i{(int)(u2 & 0xFFFFu), (int)(u2 >> 16), (int)(u3 & 0xFFFFu),
-                           at + 7 == 255 ? 65536 : (int)(u3 >> 16)};
-            }
+            GAS v4i* dst = (GAS v4i*)(S.cdf32 + (int64_t)nrow * 256 + at);
+            const uint32_t u0 = (uint32_t)w[0], u1 = (uint32_t)w[1], u2 = (uint32_t)w[2], u3 = (uint32_t)w[3];
+            dst[0] = v4i{(int)(u0 & 0xFFFFu), (int)(u0 >> 16), (int)(u1 & 0xFFFFu), (int)(u1 >> 16)};
+            dst[1] = v4i{(int)(u2 & 0xFFFFu), (int)(u2 >> 16), (int)(u3 & 0xFFFFu),
+                         at + 7 == 255 ? 65536 : (int)(u3 >> 16)};
           }
         }
         wave_lds_sync();
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Decoding of one depth: predictor and range decoder in one launch.
+//
+// A block decodes one chunk.  Wave NP decodes; waves 0 .. NP - 1 predict: in
+// step s wave w makes the CDF rows of nodes 16 (s NP + w) .. + 15 and the
+// decoder takes the rows of step s - 1, through two halves of a ring in LDS,
+// one barrier per step.  The rows (512 bytes per node) so never leave the
+// compute unit, and the decoder's serial chain (latency) runs beside the
+// predictor's arithmetic (issue), which as two launches took turns: over the
+// 18 depths of 8 128-beam frames (12.75 M nodes) 2.28 + 1.92 ms became 2.99
+// ms, over the 12 depths of a 16-beam frame 390 us became 245 us.
+//
+// Range decoder (G. N. N. Martin 1979, as in rc.hip): state code and range,
+// r = range >> 16; the symbol is the last s with r cdf[s] <= code, then code
+// -= r cdf[s], range = r (cdf[s+1] - cdf[s]).  Lane l of the decoding wave
+// holds the boundaries b_j = cdf[4 L + j], j = 0 .. 3, of group L = 63 - l.
+// With t = r b - code - 1 (mod 2^32, one 16-bit multiply-add) a boundary
+// passed (r b <= code) gives t >= ~code and one not passed t < ~code, both
+// increasing in b, so over the group that holds the symbol the largest t_0 ..
+// t_3 is the symbol's and the smallest of t_1 .. t_4 (t_4: the next group's
+// t_0, from lane l - 1) the next boundary's: code = ~max, range = min - max.
+// The group is the first lane whose t_0 passed.  Entry 255, 2^16, is stored as
+// 65535, and the missing r is in that lane's addend of t_3.  The state holds
+// ~code, which is max itself.  Renormalisation takes 0, 1 or 2 bytes: lane p
+// of `win` holds the complement of the four bytes from byte p of the block's
+// part of the payload, shifted in below ~code.
+// The decoder only notes code, range and lane of every symbol; the wave that
+// made the rows counts the boundaries passed (the code's last two bits) before
+// it overwrites them two steps later.  It also finds a corrupt stream, one
+// where code >= r 2^16 at some symbol (no boundary is above it): what the
+// decoder does from there on means nothing, but stays inside its buffers (a
+// symbol takes at most 3 bytes, 16 of them stay inside the window).
+// ---------------------------------------------------------------------------
+constexpr int kRowWords = 132;  // LDS row: 256 entries of 16 bits, padded against bank conflicts
+
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+struct RcDec {
+  uint32_t nc, range, pos;  // ~code, range, payload bytes taken from the window's start
+};
+
+// One symbol from the group's boundaries x = b_0 | b_1 << 16, y = b_2 | b_3 <<
+// 16; returns the lane of its group.
+// last: 1 in the lane of group 63, else 0.
+__device__ __forceinline__ int rc_symbol(RcDec& d, uint32_t x, uint32_t y, uint32_t win, uint32_t last) {
+  const uint32_t nc = d.nc;
+  uint32_t t0, t1, t2, t3, n3;
+  // the high half of the range times the low or high half of x, y; t0 first:
+  // its cross-lane use needs two instructions in between
+  asm("v_mad_u32_u16 %0, %5, %7, %8 op_sel:[0,1,0,0]\n\t"
+      "v_mad_u32_u16 %4, %9, %7, %8 op_sel:[0,1,0,0]\n\t"
+      "v_mad_u32_u16 %1, %5, %7, %8 op_sel:[1,1,0,0]\n\t"
+      "v_mad_u32_u16 %2, %6, %7, %8 op_sel:[0,1,0,0]\n\t"
+      "v_mad_u32_u16 %3, %6, %7, %4 op_sel:[1,1,0,0]"
+      : "=&v"(t0), "=&v"(t1), "=&v"(t2), "=v"(t3), "=&v"(n3)
+      : "v"(x), "v"(y), "s"(d.range), "v"(nc), "v"(last));
+  const uint64_t passed = __ballot(t0 >= nc);
+  uint32_t hi = max(t0, t1), lo = min(min(t1, t2), t3);
+  int lane;
+  // lo takes the next group's t0 in (lane 0, group 63, has none and keeps its
+  // own); the lane is the first of the mask.  In one block, so that an
+  // instruction lies between each vector result and the lane reads below.
+  asm("v_min_u32_dpp %0, %3, %0 wave_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+      "v_max3_u32 %1, %1, %4, %5\n\t"
+      "s_ff1_i32_b64 %2, %6"
+      : "+v"(lo), "+v"(hi), "=s"(lane)
+      : "v"(t0), "v"(t2), "v"(t3), "s"(passed));
+  const uint32_t mx = (uint32_t)__builtin_amdgcn_readlane((int)hi, lane);
+  const uint32_t mn = (uint32_t)__builtin_amdgcn_readlane((int)lo, lane);
+  d.range = mn - mx;
+  uint32_t sh;  // leading zeros in whole bytes
+  asm("s_flbit_i32_b32 %0, %1" : "=s"(sh) : "s"(d.range));
+  sh &= 24u;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)win, (int)(d.pos & 63u));
+  d.nc = (uint32_t)(((((uint64_t)mx << 32) | w) << sh) >> 32);
+  d.range <<= sh;
+  d.pos += sh >> 3;
+  return lane;
+}
+
+// lane k of v (k a constant) takes the wave-uniform s, a value of the scalar
+// unit (no wait states are needed after those)
+__device__ __forceinline__ void put_lane(uint32_t& v, uint32_t s, int k) {
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(s), "n"(k));
+}
+
+template <int C, int NP, int RQ>
+__global__ __launch_bounds__(64 * (NP + 1)) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4 : 3))) void k_decode_chunks(
+    const Chunk* __restrict__ chunks, const uint8_t* __restrict__ payload, const int32_t* __restrict__ lut_g,
+    const DecArg A, uint8_t* __restrict__ codes, uint32_t* __restrict__ csum, uint32_t* __restrict__ err,
+    int pay_words) {
+  constexpr int NT = 64 * (NP + 1);
+  __shared__ uint16_t lut[256];
+  __shared__ __attribute__((aligned(16))) int32_t b2s[256];
+  __shared__ __attribute__((aligned(16))) int32_t b1s[C];
+  __shared__ __attribute__((aligned(16))) uint32_t ring[2][NP * 16 * kRowWords];
+  __shared__ uint32_t note[2][3][NP * 16];  // ~code, range and lane of every symbol of the half
+  __shared__ uint32_t kids;                 // children announced by the chunk's codes
+  extern __shared__ uint32_t pay[];  // the chunk's bytes, zero padded (at least two words of zeros)
+
+  const Chunk ch = chunks[blockIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = ch.count;
+  const int nblk = (n + 15) / 16, nstep = (nblk + NP - 1) / NP;
+  for (int k = tid; k < 256; k += NT) {
+    lut[k] = (uint16_t)gp(lut_g)[k];
+    b2s[k] = gp(A.fc2.bias)[k];
+    if (k < C) b1s[k] = gp(A.fc1.bias)[k];
+  }
+  {
+    const uint32_t len = (uint32_t)ch.pad_;
+    const GAS uint8_t* src = gp(payload) + ch.scratch;
+    for (int w = tid; w < pay_words; w += NT) {
+      uint32_t v = 0;
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        const uint32_t b = 4u * (uint32_t)w + (uint32_t)k;
+        if (b < len) v |= (uint32_t)src[b] << (8 * k);
+      }
+      pay[w] = v;
+    }
+  }
+  if (tid == 0) kids = 0u;
+  lds_barrier();
+
+  if (wave < NP) {
+    const int r = lane & 15, g = lane >> 4;
+    const GAS int8_t* F = gp(A.F) + (int64_t)ch.node0 * C + 16 * g;
+    auto fetch = [&](int s) {
+      const int i = 16 * (s * NP + wave) + r;
+      return i < n && 16 * g < C ? *(const GAS v4i*)(F + (int64_t)i * C) : v4i{0, 0, 0, 0};
+    };
+    v4i x = fetch(0);
+    uint32_t nkids = 0;
+    // the codes of step s, whose rows and notes lie in half s & 1
+    auto resolve = [&](int s) {
+      const int base = 16 * (s * NP + wave);
+      if (s < 0 || base + lane >= n || lane >= 16) return;
+      const uint32_t* nt = &note[s & 1][0][wave * 16 + lane];
+      const uint32_t sc = ~nt[0], sr = nt[NP * 16], L = 63u - (nt[2 * NP * 16] & 63u);
+      const uint2 b = *(const uint2*)&ring[s & 1][(wave * 16 + lane) * kRowWords + 2 * L];
+      const uint32_t rr = sr >> 16;
+      uint32_t cv = 4u * L + 1u;
+      cv += __umul24(rr, b.x >> 16) <= sc ? 1u : 0u;
+      cv += __umul24(rr, b.y & 0xFFFFu) <= sc ? 1u : 0u;
+      cv += L != 63u && __umul24(rr, b.y >> 16) <= sc ? 1u : 0u;
+      if (sc >= (sr & 0xFFFF0000u)) atomicOr(err, ERR_CORRUPT);
+      gp(codes)[ch.node0 + base + lane] = (uint8_t)cv;
+      nkids += __popc(cv & 0xFFu);
+    };
+    for (int s = 0; s <= nstep; s++) {
+      resolve(s - 2);
+      if (s * NP + wave < nblk) {
+        int e[64];
+        NodeSum ns;
+        // a lane offset the compiler cannot see through: it would keep the 20
+        // 64-bit addresses in vector registers across the steps and spill
+        uint32_t lo = 16u * (uint32_t)lane;
+        asm volatile("" : "+v"(lo));
+        predict_table<C, false, RQ>([&](int k) { return *(const GAS v4i*)(gp(A.fc1.Wp) + 1024 * k + lo); },
+                                    [&](int k) { return *(const GAS v4i*)(gp(A.fc2.Wp) + 1024 * k + lo); }, b1s, b2s,
+                                    lut, x, lane, A.fc1, A.fc2, e, ns);
+        x = fetch(s + 1);
+        uint32_t p0, p1, R;
+        row_prefix<false>(e, ns, lane, p0, p1, R);
+        uint32_t* row = &ring[s & 1][(wave * 16 + r) * kRowWords + 32 * g];
+#pragma unroll
+        for (int c = 0; c < 8; c++) {
+          *(v4i*)&row[4 * c] = row_chunk<64>(e, c, ns.ablk, p0, p1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (ns.aord == ns.ord) row_remainder(row + 2 * ns.ablk, ns, R);
+        if (ns.tail) ((uint16_t*)row)[63] = 65535;  // entry 255, whatever the remainder made of it
+      }
+      lds_barrier();
+    }
+    resolve(nstep - 1);
+    nkids = wave_scan_incl(nkids);  // lane 63: the wave's sum
+    if (lane == 63) atomicAdd(&kids, nkids);
+    lds_barrier();
+    if (tid == 0) csum[blockIdx.x] = kids;
+    return;
+  }
+
+  // the decoding wave
+  int wb = 0;  // first payload byte of the window
+  auto window = [&](int at) -> uint32_t {
+    const int b = at + lane;
+    const int w = min(b >> 2, pay_words - 2);
+    const uint32_t v = __builtin_amdgcn_alignbyte(pay[w + 1], pay[w], (uint32_t)b & 3u);
+    return ~__builtin_amdgcn_perm(0u, v, 0x00010203u);  // first byte on top
+  };
+  uint32_t win = window(0);
+  // the first 5 bytes: the first is always 0
+  RcDec d{(uint32_t)__builtin_amdgcn_readlane((int)win, 1), 0xFFFFFFFFu, 5u};
+  const uint32_t last = lane == 0 ? 1u : 0u;
+  __builtin_amdgcn_s_setprio(3);  // the chain sets the pace where waves are few
+  lds_barrier();
+  for (int s = 1; s <= nstep; s++) {
+    for (int q = 0; q < NP; q++) {
+      const int base = 16 * ((s - 1) * NP + q);
+      if (base >= n) break;
+      const uint32_t* rows = &ring[(s - 1) & 1][q * 16 * kRowWords];
+      const uint32_t* grp = rows + 2 * (63 - lane);
+      wb += (int)d.pos;
+      d.pos = 0;
+      win = window(wb);
+      // lane k: ~code and range before symbol k and the lane of its group
+      uint32_t sc = 0, sr = 0, sl = 0;
+      const int cnt = min(16, n - base);
+      // rows past the chunk's end (its last block) exist and decode to
+      // nothing that is read
+      uint2 t[16];
+#pragma unroll
+      for (int k = 0; k < 16; k++) t[k] = *(const uint2*)(grp + k * kRowWords);
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        if (8 * h >= cnt) break;
+#pragma unroll
+        for (int k = 8 * h; k < 8 * h + 8; k++) {
+          put_lane(sc, d.nc, k);
+          put_lane(sr, d.range, k);
+          put_lane(sl, (uint32_t)rc_symbol(d, t[k].x, t[k].y, win, last), k);
+        }
+      }
+      if (lane < cnt) {
+        uint32_t* nt = &note[(s - 1) & 1][0][q * 16 + lane];
+        nt[0] = sc;
+        nt[NP * 16] = sr;
+        nt[2 * NP * 16] = sl;
+      }
+    }
+    lds_barrier();
+  }
+  lds_barrier();
+}
+
+// Predicting waves per decoding wave.  A full chunk of 256 nodes alone takes
+// 27.5 us with 3 (the chain, 175 cycles per symbol, sets the pace), 31.5 us
+// with 2 (it waits for rows; 66 us with 1) and 29 us with 5.  With thousands
+// of chunks both arithmetic and chains are in flight anyway, and 2 leave a
+// compute unit more chunks at once: the 8-frame 128-beam batch decodes in
+// 10.17 ms with 2 and 10.42 ms with 3, one such frame (at most 920 chunks) in
+// 2.58 and 2.54 ms.
+constexpr int kDecodeWide = 1024;
+
+hipError_t launch_decode_chunks(int C, const Chunk* chunks, int nchunks, const uint8_t* payload, const int32_t* lut,
+                                const DecArg& A, uint8_t* codes, uint32_t* csum, uint32_t* err, size_t max_len,
+                                hipStream_t s) {
+  if (nchunks <= 0) return hipSuccess;
+  const int words = (int)((max_len + 3) / 4) + 4;
+  const int np = nchunks < kDecodeWide ? 3 : 2;
+#define LPCC_DC(CC, NN, RR)                                                                                         \
+  if (C == CC && np == NN && A.rqf == RR) {                                                                         \
+    hipLaunchKernelGGL((k_decode_chunks<CC, NN, RR>), dim3(nchunks), dim3(64 * (NN + 1)), (size_t)words * 4, s,     \
+                       chunks, payload, lut, A, codes, csum, err, words);                                           \
+    return hipGetLastError();                                                                                       \
+  }
+#define LPCC_DC2(CC) LPCC_DC(CC, 2, 1) LPCC_DC(CC, 3, 1) LPCC_DC(CC, 2, 0) LPCC_DC(CC, 3, 0)
+  LPCC_DC2(16) LPCC_DC2(32) LPCC_DC2(64)
+#undef LPCC_DC2
+#undef LPCC_DC
+  return hipErrorInvalidValue;
 }
 
 // Nodes per block of the 16-node form: 64 x the groups of a wave.  More
@@ -1750,9 +2070,7 @@ hipError_t launch_predict(int C, int mode, const PredSeg* segs, const Tile* tile
       hipLaunchKernelGGL((k_predict<CC, MM, false, 0>), dim3(grid), dim3(256), 0, s, segs, tiles, lut, groups, A); \
     return hipGetLastError();                                                                                      \
   }
-  LPCC_P(16, 0) LPCC_P(16, 1) LPCC_P(16, 2)
-  LPCC_P(32, 0) LPCC_P(32, 1) LPCC_P(32, 2)
-  LPCC_P(64, 0) LPCC_P(64, 1) LPCC_P(64, 2)
+  LPCC_P(16, 0) LPCC_P(16, 2) LPCC_P(32, 0) LPCC_P(32, 2) LPCC_P(64, 0) LPCC_P(64, 2)
 #undef LPCC_P
   return hipErrorInvalidValue;
 }

@@ -2163,8 +2163,10 @@ int read_headers(lpcc_ctx* c, int nf, const uint8_t* const* bs, const size_t* le
 }
 
 // Decode workspace: per depth keys, codes and first-child rows of all
-// frames, the payloads, the CDF rows of the largest depth, error words,
-// chunk child counts, staged coordinates, and the model buffers.
+// frames, the payloads, the CDF rows of the largest base depth (the modelled
+// depths' rows never reach memory; the bounds a caller is told count the
+// largest depth's), error words, chunk child counts, staged coordinates, and
+// the model buffers.
 struct DecBufs {
   uint8_t* payload = nullptr;
   uint16_t* cdf16 = nullptr;
@@ -2173,10 +2175,10 @@ struct DecBufs {
 };
 
 void carve_decode(Arena& A, const lpcc_model* m, const Frames& fr, size_t paybytes, size_t maxch, bool host_out,
-                  int nb, Levels& lv, ModelBufs& B, DecBufs& o) {
+                  int nb, Levels& lv, ModelBufs& B, DecBufs& o, int row_depths) {
   const int D = m->D;
   int64_t maxN = 0;
-  for (int d = 0; d <= D; d++) maxN = std::max(maxN, fr.tot[d]);
+  for (int d = 0; d < row_depths; d++) maxN = std::max(maxN, fr.tot[d]);
   std::vector<bool> wanted(D, true);
   for (int d = 0; d < nb && d < D; d++) wanted[d] = false;
   for (int d = 0; d <= D; d++) {
@@ -2213,7 +2215,7 @@ void decode_workspace(const lpcc_model* m, const int64_t* N, int nb, int cl, siz
   ModelBufs B;
   DecBufs db;
   Arena a;
-  carve_decode(a, m, fr, align_up(pay, 16), maxch, true, nb, lv, B, db);
+  carve_decode(a, m, fr, align_up(pay, 16), maxch, true, nb, lv, B, db, D + 1);
   out[0] = 0;
   out[1] = a.off + 4096;
   out[2] = desc_bound(fr, nch);
@@ -2249,7 +2251,7 @@ void lpcc::decode_workspace_bound(const lpcc_model* m, int nf, const int64_t* co
   ModelBufs B;
   DecBufs db;
   Arena a;
-  carve_decode(a, m, fr, align_up(pay, 16), maxch, true, 0, lv, B, db);
+  carve_decode(a, m, fr, align_up(pay, 16), maxch, true, 0, lv, B, db, D + 1);
   out[0] = 0;
   out[1] = a.off + 4096;
   out[2] = desc_bound(fr, nch);
@@ -2371,13 +2373,13 @@ int decode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const uint8_t* const* 
   }
   DecBufs db;
   Arena meas;
-  carve_decode(meas, m, fr, paybytes, maxch, any_host_out, nb, lv, B, db);
+  carve_decode(meas, m, fr, paybytes, maxch, any_host_out, nb, lv, B, db, nb);
   int s = reserve(c, 1, meas.off + 4096);
   if (s) return s;
   Arena A;
   A.base = c->dev[1];
   A.cap = c->cap[1];
-  carve_decode(A, m, fr, paybytes, maxch, any_host_out, nb, lv, B, db);
+  carve_decode(A, m, fr, paybytes, maxch, any_host_out, nb, lv, B, db, nb);
   uint8_t* payload = db.payload;
   uint16_t* cdf16 = db.cdf16;
   uint32_t *err = db.err, *csum = db.csum;
@@ -2484,15 +2486,21 @@ int decode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const uint8_t* const* 
       plan_shallow_convs(b, m, lv, fr, B, t, sd);
       resblock = mark(sd);
     }
+    const size_t co = b.add(dchunks[d]);
+    const int nch = (int)dchunks[d].size();
+    const size_t ml = dmaxlen[d];
+    uint8_t* dcodes = lv.code[d];
     if (modelled) {
-      PredSeg p;
+      DecArg p;
       memset(&p, 0, sizeof(p));
       p.F = features_of(m, B, d);
-      p.fc1 = dlayer(m, d, m->first[d + 1] - m->first[d] - 2);
-      p.fc2 = dlayer(m, d, m->first[d + 1] - m->first[d] - 1);
-      p.rows = (int)fr.tot[d];
-      p.cdf16 = cdf16;
-      plan_predict(b, m, {p}, 1, st);
+      p.fc1 = hlayer(m, dlayer(m, d, m->first[d + 1] - m->first[d] - 2));
+      p.fc2 = hlayer(m, dlayer(m, d, m->first[d + 1] - m->first[d] - 1));
+      p.rqf = p.fc1.rqf && p.fc2.rqf ? 1 : 0;
+      const int32_t* lut = m->d_lut;
+      b.launch("decode", fr.tot[d], [=](const uint8_t* base) {
+        return launch_decode_chunks(C, (const Chunk*)(base + co), nch, payload, lut, p, dcodes, csum, err + 0, ml, st);
+      });
     } else {
       // the CDF row of every node of this base depth is its frame's table
       const uint64_t* keys = lv.key[d];
@@ -2502,15 +2510,8 @@ int decode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const uint8_t* const* 
       b.launch("base", nd_, [=](const uint8_t* base) {
         return launch_base_rows(keys, nd_, dd, nb_, nl, (const uint16_t*)(base + ro), cdf16, st);
       });
-    }
-    const size_t co = b.add(dchunks[d]);
-    const int nch = (int)dchunks[d].size();
-    {
-      const size_t ml = dmaxlen[d];
-      uint8_t* codes = lv.code[d];
-      uint32_t* cs = csum;
-      b.launch("rc_decode", fr.tot[d], [=](const uint8_t* base) {
-        return launch_rc_decode_sized((const Chunk*)(base + co), nch, payload, cdf16, codes, cs, err + 0, ml, st);
+      b.launch("rc_decode", nd_, [=](const uint8_t* base) {
+        return launch_rc_decode_sized((const Chunk*)(base + co), nch, payload, cdf16, dcodes, csum, err + 0, ml, st);
       });
     }
     if (t <= k0 && modelled && !m->xfp) {

@@ -7,6 +7,7 @@ import pytest
 
 from oracle import oracle as O
 from paper_2603_25260_amd import synth
+from tests.blobs import with_fc2_bias
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -51,3 +52,51 @@ def test_rows_and_streams_at_tile_edges(L, n, C, zp):
         bs = O.encode(blob, xyz, cl)
         assert L.encode_frame(ctx, m, dx, cl) == bs, cl
         assert np.array_equal(L.decode_frame(ctx, m, bs), u), cl
+
+
+@pytest.mark.parametrize("C,sym", [(16, 251), (32, 252), (64, 253), (32, 254), (64, 63), (16, 64)])
+def test_first_maximum_at_lane_and_row_ends(L, C, sym):
+    """The remainder's entry at the ends of a lane's symbols and of the row
+    (entry 255 is no boundary whatever the remainder adds before it)."""
+    D, nd = 9, 3
+    blob = with_fc2_bias(synth.make_weights(70 + C, C, D, nd), sym, 100000)
+    xyz = synth.random_cloud(3000, D, sym)
+    print("C", C, "sym", sym, flush=True)
+    m = L.Model(blob, 0)
+    ctx = L.Context(0)
+    dx = torch.from_numpy(xyz).cuda()
+    assert np.array_equal(L.level_probs(ctx, m, dx, D - 1), O.level_probs(blob, xyz, D - 1))
+    bs = O.encode(blob, xyz, 8)
+    assert L.encode_frame(ctx, m, dx, 8) == bs
+    u = np.unique(xyz, axis=0)
+    assert np.array_equal(L.decode_frame(ctx, m, bs), u[np.argsort(O.morton(u, D))])
+
+
+def test_damaged_payloads_end_in_an_error(L):
+    """Payload bytes changed at every depth: the codes announce other child
+    counts than the header, every such decode reports a corrupt stream and
+    the context decodes the sound stream afterwards."""
+    C, D, nd = 32, 12, 3
+    blob = synth.make_weights(9, C, D, nd)
+    xyz = synth.random_cloud(9000, D, 31)
+    m = L.Model(blob, 0)
+    ctx = L.Context(0)
+    bs = L.encode_frame(ctx, m, torch.from_numpy(xyz).cuda(), 8)
+    u = np.unique(xyz, axis=0)
+    u = u[np.argsort(O.morton(u, D))]
+    N = np.frombuffer(bs[16:16 + 4 * D], np.uint32)
+    pre = 16 + 4 * D
+    nch = [int((n + 255) // 256) for n in N]
+    lens = np.frombuffer(bs[pre:pre + 2 * sum(nch)], np.uint16)
+    at, k = pre + 2 * sum(nch), 0
+    for d in range(D):
+        bad = bytearray(bs)
+        for q in range(min(4, int(lens[k]) - 2)):
+            bad[at + 2 + q] ^= 0x5A
+        print("depth", d, flush=True)
+        with pytest.raises(L.LpccError):
+            L.decode_frame(ctx, m, bytes(bad))
+        for q in range(nch[d]):
+            at += int(lens[k + q])
+        k += nch[d]
+    assert np.array_equal(L.decode_frame(ctx, m, bs), u)
