@@ -227,32 +227,35 @@ enum : uint32_t { ERR_COORD = 1u, ERR_CORRUPT = 2u, ERR_COUNT = 4u, ERR_ACC = 8u
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // Morton keys and their LSD radix sort (Sec. S3.2: coordinates sorted in
-// Morton order).  Keys are sorted on bits [0, end_bit) in passes of at most
-// 8 bits, tiles of kSortTile keys; hist is [passes][tiles][256] per-tile digit
-// counts (zeroed first), totals [passes][256] digit counts of all keys.
+// Morton order), on bits [0, end_bit).  Small sorts (tile > 0): passes of at
+// most kSortBits bits, hist is [2^kSortBits][64] counts of the current pass
+// (bin, tile) and [2^kSortBits] counts of all keys.  Large ones: passes of at
+// most 8 bits, tiles of kSortTile keys, hist is [passes][tiles][256] per-tile
+// digit counts and totals [passes][256] digit counts of all keys (both zeroed
+// first).
 // ---------------------------------------------------------------------------
 constexpr int kSortItems = 8;
 constexpr int kSortTile = 256 * kSortItems;
-constexpr int kSortFusedTiles = 64;  // up to this many tiles a pass scans its own offsets
-constexpr int kMortonGroup = 16;     // frames per Morton launch (passed by value)
+constexpr int kSortBits = 11;
+constexpr int kMortonGroup = 16;  // frames per Morton launch (passed by value)
 struct SortPasses {
   int32_t n;
+  int32_t tile;  // keys per tile of a small sort (at most 64 tiles), 0: large
   int32_t shift[8];
   int32_t bits[8];
 };
-SortPasses sort_passes(int end_bit);
+SortPasses sort_passes(int64_t n, int end_bit);
 struct MortonFrames {
   const int32_t* xyz[kMortonGroup];  // device coordinates of each frame
   int64_t start[kMortonGroup + 1];   // key range of each frame (start[nf] = end)
   int32_t nf;                        // frames of this launch
   int32_t f0;                        // index of the first (frame tag, error word)
 };
-// keys of the frames' points (frame tag f << 3D), their per-tile digit
-// counts of pass 0 and the digit totals of every pass
+// keys of the frames' points (frame tag f << 3D); for a large sort also their
+// per-tile digit counts of pass 0 and the digit totals of every pass
 hipError_t launch_morton_sort0(const MortonFrames& mf, int D, uint64_t* keys, uint32_t* err, const SortPasses& sp,
                                uint32_t* hist, uint32_t* totals, hipStream_t s);
-// pass p: kin -> kout, stable on the pass's digit (for p > 0 the pass first
-// counts its digits per tile of kin into hist); ERR_SORT in *err on an
+// pass p: kin -> kout, stable on the pass's digit; ERR_SORT in *err on an
 // impossible rank
 hipError_t launch_sort_pass(const uint64_t* kin, uint64_t* kout, int64_t n, const SortPasses& sp, int p,
                             uint32_t* hist, const uint32_t* totals, uint32_t* err, hipStream_t s);

@@ -34,16 +34,28 @@ __device__ __forceinline__ uint32_t compact3(uint64_t x) {
 
 // ---------------------------------------------------------------------------
 // LSD radix sort of the Morton keys (Sec. S3.2 sorts the coordinates in
-// Morton order before the levels are derived).  Passes of at most 8 bits from
-// the least significant end; each pass is stable, so the keys end sorted on
-// all bits [0, end_bit).  A tile is kSortTile keys in striped order (item k of
-// thread t is key k*256 + t of the tile).
+// Morton order before the levels are derived).  Each pass is stable, so the
+// keys end sorted on all bits [0, end_bit).
+//
+// Sorts of at most 64 tiles (of 512 or 2048 keys, the smaller that fits) take
+// digits of up to 11 bits: a pass counts the tiles' digits, scans every
+// digit's tiles (one wave per digit, one lane per tile) and scatters.
+// Larger sorts take digits of at most 8 bits; their tiles are kSortTile keys in
+// striped order (item k of thread t is key k*256 + t of the tile).
+// A pass over so few keys is latency, so few passes and no contended counter
+// matter: with 6 passes of 8 bits whose scatter also counted the next pass's
+// digits by global atomics, the sort of a 64-beam frame (118k keys, 58 tiles)
+// took 154 us; these 4 passes of 3 launches take 71 us.  Tiles of 4096 keys
+// were tried for the 236k keys of a 128-beam frame and lost to the large form
+// (58 blocks leave most compute units idle; 25 us more per frame).
 // ---------------------------------------------------------------------------
-SortPasses sort_passes(int end_bit) {
+SortPasses sort_passes(int64_t n, int end_bit) {
   SortPasses sp;
   memset(&sp, 0, sizeof(sp));
   end_bit = end_bit < 1 ? 1 : end_bit;
-  sp.n = (end_bit + 7) / 8;
+  sp.tile = n <= 64 * 512 ? 512 : (n <= 64 * 2048 ? 2048 : 0);
+  const int most = sp.tile ? kSortBits : 8;
+  sp.n = (end_bit + most - 1) / most;
   const int w = (end_bit + sp.n - 1) / sp.n;
   for (int p = 0; p < sp.n; p++) {
     sp.shift[p] = p * w;
@@ -54,6 +66,32 @@ SortPasses sort_passes(int end_bit) {
 
 __device__ __forceinline__ uint32_t digit_of(uint64_t key, int shift, int bits) {
   return (uint32_t)(key >> shift) & ((1u << bits) - 1u);
+}
+
+// Key of element i of the launch's frames (frame of i, its coordinates).
+__device__ __forceinline__ uint64_t morton_key(const MortonFrames& mf, int D, int64_t i, uint32_t* err) {
+  // constant indices into the argument arrays
+  int f = 0;
+#pragma unroll
+  for (int g = 1; g < kMortonGroup; g++)
+    if (g < mf.nf && i >= mf.start[g]) f = g;
+  const int32_t* src = mf.xyz[0];
+  int64_t s0 = mf.start[0];
+#pragma unroll
+  for (int g = 1; g < kMortonGroup; g++)
+    if (g == f) {
+      src = mf.xyz[g];
+      s0 = mf.start[g];
+    }
+  const GAS int32_t* p = gp(src) + 3 * (i - s0);
+  int32_t x = p[0], y = p[1], z = p[2];
+  const uint32_t side = 1u << D;
+  if (x < 0 || y < 0 || z < 0 || (uint32_t)x >= side || (uint32_t)y >= side || (uint32_t)z >= side) {
+    atomicOr(err + mf.f0 + f, ERR_COORD);
+    x = y = z = 0;
+  }
+  const uint64_t tag = (uint64_t)(mf.f0 + f) << (3 * D);
+  return tag | (spread3((uint32_t)x) << 2) | (spread3((uint32_t)y) << 1) | spread3((uint32_t)z);
 }
 
 // Keys of the launch's frames: block b covers tile (first tile of the
@@ -67,31 +105,10 @@ __global__ __launch_bounds__(256) void k_morton_sort0(const MortonFrames mf, int
   __syncthreads();
   const int64_t lo = mf.start[0], hi = mf.start[mf.nf];
   const int64_t tile = lo / kSortTile + blockIdx.x;
-  const uint32_t side = 1u << D;
   for (int k = 0; k < kSortItems; k++) {
     const int64_t i = tile * kSortTile + k * 256 + threadIdx.x;
     if (i < lo || i >= hi) continue;
-    // frame of element i (constant indices into the argument arrays)
-    int f = 0;
-#pragma unroll
-    for (int g = 1; g < kMortonGroup; g++)
-      if (g < mf.nf && i >= mf.start[g]) f = g;
-    const int32_t* src = mf.xyz[0];
-    int64_t s0 = mf.start[0];
-#pragma unroll
-    for (int g = 1; g < kMortonGroup; g++)
-      if (g == f) {
-        src = mf.xyz[g];
-        s0 = mf.start[g];
-      }
-    const GAS int32_t* p = gp(src) + 3 * (i - s0);
-    int32_t x = p[0], y = p[1], z = p[2];
-    if (x < 0 || y < 0 || z < 0 || (uint32_t)x >= side || (uint32_t)y >= side || (uint32_t)z >= side) {
-      atomicOr(err + mf.f0 + f, ERR_COORD);
-      x = y = z = 0;
-    }
-    const uint64_t tag = (uint64_t)(mf.f0 + f) << (3 * D);
-    const uint64_t key = tag | (spread3((uint32_t)x) << 2) | (spread3((uint32_t)y) << 1) | spread3((uint32_t)z);
+    const uint64_t key = morton_key(mf, D, i, err);
     gp(keys)[i] = key;
     for (int q = 0; q < sp.n; q++) atomicAdd(&h[q][digit_of(key, sp.shift[q], sp.bits[q])], 1u);
   }
@@ -105,13 +122,148 @@ __global__ __launch_bounds__(256) void k_morton_sort0(const MortonFrames mf, int
   }
 }
 
+// Small sorts: the keys alone, one per thread.
+__global__ __launch_bounds__(256) void k_morton_keys(const MortonFrames mf, int D, uint64_t* __restrict__ keys,
+                                                     uint32_t* __restrict__ err) {
+  const int64_t i = mf.start[0] + (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < mf.start[mf.nf]) gp(keys)[i] = morton_key(mf, D, i, err);
+}
+
 hipError_t launch_morton_sort0(const MortonFrames& mf, int D, uint64_t* keys, uint32_t* err, const SortPasses& sp,
                                uint32_t* hist, uint32_t* totals, hipStream_t s) {
   const int64_t lo = mf.start[0], hi = mf.start[mf.nf];
   if (hi <= lo) return hipSuccess;
+  if (sp.tile) {
+    hipLaunchKernelGGL(k_morton_keys, dim3((unsigned)((hi - lo + 255) / 256)), dim3(256), 0, s, mf, D, keys, err);
+    return hipGetLastError();
+  }
   const int64_t blocks = (hi - 1) / kSortTile - lo / kSortTile + 1;
   hipLaunchKernelGGL(k_morton_sort0, dim3((unsigned)blocks), dim3(256), 0, s, mf, D, keys, err, sp, hist, totals);
   return hipGetLastError();
+}
+
+// Small sorts, digit counts of one pass: hist[bin][64 tiles] over tiles of 256
+// x ITEMS keys.
+template <int ITEMS>
+__global__ __launch_bounds__(256) void k_sort_count_few(const uint64_t* __restrict__ kin, int64_t n, int shift,
+                                                        int bits, uint32_t* __restrict__ hist) {
+  __shared__ uint32_t h[1 << kSortBits];
+  const int nb = 1 << bits;
+  uint64_t key[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const int64_t i = (int64_t)blockIdx.x * (256 * ITEMS) + k * 256 + threadIdx.x;
+    key[k] = i < n ? gp(kin)[i] : 0ull;
+  }
+  for (int b = threadIdx.x; b < nb; b += 256) h[b] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const int64_t i = (int64_t)blockIdx.x * (256 * ITEMS) + k * 256 + threadIdx.x;
+    if (i < n) atomicAdd(&h[digit_of(key[k], shift, bits)], 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < nb; b += 256) gp(hist)[64 * b + blockIdx.x] = h[b];
+}
+
+// Small sorts: every bin's counts become the number of its keys in earlier
+// tiles, and totals[bin] the number in all.  A wave per bin, a lane per tile.
+__global__ __launch_bounds__(256) void k_sort_scan_few(uint32_t* __restrict__ hist, int ntiles, int nb,
+                                                       uint32_t* __restrict__ totals) {
+  const int bin = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (bin >= nb) return;  // wave-uniform
+  const uint32_t c = lane < ntiles ? gp(hist)[64 * bin + lane] : 0u;
+  const uint32_t inc = wave_scan_incl(c);
+  gp(hist)[64 * bin + lane] = inc - c;
+  if (lane == 63) gp(totals)[bin] = inc;
+}
+
+// Small sorts, scatter of one pass.  Wave w of a tile owns 64 x ITEMS
+// consecutive keys, item k of lane l at 64 k + l, so that the counters of a
+// (wave, digit) run over the wave's items in order: a key's rank is the
+// counter before its item plus the lower lanes with its digit (ballot match
+// over the digit bits).  The counters then become destinations: all keys of
+// smaller digits, the digit's keys of the tiles before, and of the waves before.
+template <int ITEMS>
+__global__ __launch_bounds__(256) void k_sort_scatter_few(const uint64_t* __restrict__ kin,
+                                                          uint64_t* __restrict__ kout, int64_t n, int shift, int bits,
+                                                          const uint32_t* __restrict__ hist,
+                                                          const uint32_t* __restrict__ totals,
+                                                          uint32_t* __restrict__ err) {
+  constexpr int kBins = 1 << kSortBits;
+  constexpr int PT = kBins / 256;  // bins per thread
+  __shared__ uint32_t cnt[4][kBins];
+  __shared__ uint32_t wsum[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nb = 1 << bits;
+  const int64_t k0 = (int64_t)blockIdx.x * (256 * ITEMS) + wave * (64 * ITEMS) + lane;
+  uint64_t key[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) key[k] = k0 + 64 * k < n ? gp(kin)[k0 + 64 * k] : 0ull;
+  // this thread's bins: pt consecutive ones
+  const int pt = nb >= 256 ? nb / 256 : 1;
+  uint32_t all[PT], before[PT];
+#pragma unroll
+  for (int j = 0; j < PT; j++) {
+    const bool has = j < pt && tid * pt + j < nb;
+    all[j] = has ? gp(totals)[tid * pt + j] : 0u;
+    before[j] = has ? gp(hist)[64 * (tid * pt + j) + blockIdx.x] : 0u;
+  }
+  for (int b = tid; b < 4 * kBins; b += 256) (&cnt[0][0])[b] = 0u;
+  __syncthreads();
+  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  uint32_t rk[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const bool valid = k0 + 64 * k < n;
+    const uint32_t d = digit_of(key[k], shift, bits);
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < bits; b++) {
+      const bool bit = (d >> b) & 1u;
+      const uint64_t bb = __ballot(bit);
+      peers &= bit ? bb : ~bb;
+    }
+    if (valid) {
+      const uint32_t old = cnt[wave][d];
+      rk[k] = old + (uint32_t)__popcll(peers & lt);
+      if ((peers & lt) == 0ull) cnt[wave][d] = old + (uint32_t)__popcll(peers);
+    }
+    // a wave's LDS accesses stay in order; the compiler must keep them so
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  // first key of every digit: block-wide scan over the digits
+  uint32_t own = 0;
+#pragma unroll
+  for (int j = 0; j < PT; j++) own += all[j];
+  const uint32_t inc = wave_scan_incl(own);
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  uint32_t at = inc - own;
+  for (int w = 0; w < wave; w++) at += wsum[w];
+#pragma unroll
+  for (int j = 0; j < PT; j++) {
+    if (j >= pt || tid * pt + j >= nb) continue;
+    uint32_t off = at + before[j];
+    at += all[j];
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+      const uint32_t c = cnt[w][tid * pt + j];
+      cnt[w][tid * pt + j] = off;
+      off += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    if (k0 + 64 * k >= n) continue;
+    const uint64_t dest = (uint64_t)cnt[wave][digit_of(key[k], shift, bits)] + rk[k];
+    if (dest >= (uint64_t)n) {  // only if the counts were inconsistent
+      atomicOr(err, ERR_SORT);
+      continue;
+    }
+    gp(kout)[dest] = key[k];
+  }
 }
 
 // In place: hist[t][d] <- first destination of tile t's keys of digit d
@@ -171,18 +323,11 @@ __global__ __launch_bounds__(256) void k_sort_count(const uint64_t* __restrict__
 // digit plus its rank among the tile's keys of that digit.  Ranks within a
 // wave come from a ballot match over the digit bits; the counts of every
 // (item, wave, digit) are turned into running offsets by one thread per
-// digit.  With offs_ready the tile offsets come from k_sort_scan, else the
-// pass sums the counts of the tiles before it and the totals of the smaller
-// digits itself; such small sorts also add the next pass's digit counts per
-// destination tile here (few tiles: few contended counters), larger ones
-// count them in a pass of their own.
+// digit.  The tile offsets come from k_sort_scan.
 __global__ __launch_bounds__(256) void k_sort_scatter(const uint64_t* __restrict__ kin, uint64_t* __restrict__ kout,
                                                       int64_t n, int shift, int bits, const uint32_t* __restrict__ hist,
-                                                      int offs_ready, const uint32_t* __restrict__ totals,
-                                                      uint32_t* __restrict__ hist_next, int shift_n, int bits_n,
                                                       uint32_t* __restrict__ err) {
   __shared__ uint32_t cnt[kSortItems][4][256];
-  __shared__ uint32_t wsum[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t tile = blockIdx.x;
   for (int k = tid; k < kSortItems * 4 * 256; k += 256) (&cnt[0][0][0])[k] = 0u;
@@ -209,18 +354,8 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint64_t* __restrict
     if (valid && (peers & lt) == 0ull) cnt[k][wave][dig[k]] = (uint32_t)__popcll(peers);
   }
   // first destination of digit `tid` in this tile
-  const uint32_t tot = gp(totals)[tid];
-  const uint32_t inc = wave_scan_incl(tot);
-  if (lane == 63) wsum[wave] = inc;
+  uint32_t off = gp(hist)[tile * 256 + tid];
   __syncthreads();
-  uint32_t off;
-  if (offs_ready) {
-    off = gp(hist)[tile * 256 + tid];
-  } else {
-    off = inc - tot;
-    for (int w = 0; w < wave; w++) off += wsum[w];
-    for (int64_t t = 0; t < tile; t++) off += gp(hist)[t * 256 + tid];
-  }
 #pragma unroll
   for (int k = 0; k < kSortItems; k++)
 #pragma unroll
@@ -239,28 +374,35 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint64_t* __restrict
       continue;
     }
     gp(kout)[dest] = key[k];
-    if (hist_next != nullptr)
-      atomicAdd(hist_next + (dest / kSortTile) * 256 + digit_of(key[k], shift_n, bits_n), 1u);
   }
+}
+
+template <int ITEMS>
+static hipError_t launch_few(const uint64_t* kin, uint64_t* kout, int64_t n, int shift, int bits, uint32_t* hist,
+                             uint32_t* err, hipStream_t s) {
+  uint32_t* totals = hist + (64 << kSortBits);
+  const int nt = (int)((n + 256 * ITEMS - 1) / (256 * ITEMS));
+  hipLaunchKernelGGL((k_sort_count_few<ITEMS>), dim3(nt), dim3(256), 0, s, kin, n, shift, bits, hist);
+  hipLaunchKernelGGL(k_sort_scan_few, dim3(((1 << bits) + 3) / 4), dim3(256), 0, s, hist, nt, 1 << bits, totals);
+  hipLaunchKernelGGL((k_sort_scatter_few<ITEMS>), dim3(nt), dim3(256), 0, s, kin, kout, n, shift, bits,
+                     (const uint32_t*)hist, (const uint32_t*)totals, err);
+  return hipGetLastError();
 }
 
 hipError_t launch_sort_pass(const uint64_t* kin, uint64_t* kout, int64_t n, const SortPasses& sp, int p,
                             uint32_t* hist, const uint32_t* totals, uint32_t* err, hipStream_t s) {
   if (n <= 0) return hipSuccess;
+  if (sp.tile == 512) return launch_few<2>(kin, kout, n, sp.shift[p], sp.bits[p], hist, err, s);
+  if (sp.tile == 2048) return launch_few<8>(kin, kout, n, sp.shift[p], sp.bits[p], hist, err, s);
   const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
   uint32_t* hp = hist + (int64_t)p * ntiles * 256;
-  const bool scan = ntiles > kSortFusedTiles;
-  const bool last = p + 1 >= sp.n;
-  // pass 0's per-tile counts come with the keys; a large sort counts every
-  // later pass over the order the previous pass left, a small one had them
-  // added by the previous pass
-  if (p > 0 && scan)
+  // pass 0's per-tile counts come with the keys; every later pass counts over
+  // the order the previous pass left
+  if (p > 0)
     hipLaunchKernelGGL(k_sort_count, dim3((unsigned)ntiles), dim3(256), 0, s, kin, n, sp.shift[p], sp.bits[p], hp);
-  if (scan) hipLaunchKernelGGL(k_sort_scan, dim3(256), dim3(256), 0, s, hp, (int)ntiles, totals + p * 256);
-  uint32_t* next = (!scan && !last) ? hp + ntiles * 256 : nullptr;
+  hipLaunchKernelGGL(k_sort_scan, dim3(256), dim3(256), 0, s, hp, (int)ntiles, totals + p * 256);
   hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)ntiles), dim3(256), 0, s, kin, kout, n, sp.shift[p], sp.bits[p],
-                     (const uint32_t*)hp, scan ? 1 : 0, totals + p * 256, next, last ? 0 : sp.shift[p + 1],
-                     last ? 0 : sp.bits[p + 1], err);
+                     (const uint32_t*)hp, err);
   return hipGetLastError();
 }
 

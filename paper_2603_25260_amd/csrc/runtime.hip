@@ -1297,7 +1297,7 @@ int frame_bits(int nf) {
 
 void carve_octree(Arena& A, const OctreeShape& S, Levels& lv, OctreeBufs& o) {
   const int D = S.D;
-  o.sp = sort_passes(3 * D + frame_bits(S.nf));
+  o.sp = sort_passes(S.ntot, 3 * D + frame_bits(S.nf));
   o.ntiles = (S.ntot + kLevelTile - 1) / kLevelTile;
   o.sntiles = (S.ntot + kSortTile - 1) / kSortTile;
   const size_t nbh = (size_t)S.nf * S.base * 256;
@@ -1313,9 +1313,14 @@ void carve_octree(Arena& A, const OctreeShape& S, Levels& lv, OctreeBufs& o) {
   o.totals = A.take<uint32_t>(D + 1);
   o.bhist = nbh ? A.take<uint32_t>(nbh) : nullptr;
   for (int d = 0; d <= D; d++) lv.code[d] = A.take<uint8_t>(align_up(S.ub[d], 4) + 4);
-  o.stot = A.take<uint32_t>((size_t)o.sp.n * 256);
-  o.shist = A.take<uint32_t>((size_t)o.sp.n * std::max<int64_t>(o.sntiles, 1) * 256);
-  o.zero_hi = (char*)(o.shist + (size_t)o.sp.n * std::max<int64_t>(o.sntiles, 1) * 256);
+  if (o.sp.tile) {  // a small sort counts without clearing
+    o.zero_hi = (char*)(lv.code[D] + align_up(S.ub[D], 4) + 4);
+    o.shist = A.take<uint32_t>((size_t)65 << kSortBits);
+  } else {
+    o.stot = A.take<uint32_t>((size_t)o.sp.n * 256);
+    o.shist = A.take<uint32_t>((size_t)o.sp.n * std::max<int64_t>(o.sntiles, 1) * 256);
+    o.zero_hi = (char*)(o.shist + (size_t)o.sp.n * std::max<int64_t>(o.sntiles, 1) * 256);
+  }
   for (int d = 0; d <= D; d++) {
     lv.key[d] = A.take<uint64_t>(S.ub[d]);
     lv.cstart[d] = A.take<int32_t>(S.ub[d] + 1);
