@@ -28,15 +28,17 @@ struct LayerDev {
   const int8_t* Wr;     // row-major W[taps][cin][cout] (VALU paths)
   const int32_t* bias;  // [Npad]; dense layers carry -z_in * colsum folded in
   const int32_t* zc;    // [taps][Npad] = -z_in * sum_c W[t][c][o] for sparse layers, or null
+  const int32_t* biasz; // bias + the sum of zc over all taps (bias without zc)
   int32_t m_pos, m_neg;  // multipliers (with r = 0 at most 256: the same function)
   int32_t r, z_out;
   int32_t taps, cin, cout;
   int32_t ksteps;       // Kpad / 64
   int32_t npad;
   int32_t a_lo, a_hi;   // accumulator range outside which the output saturates
-  int32_t rqf;          // 1: requant_f computes this layer's requantisation
+  int32_t z_in;
+  int32_t rqf;          // 1: requant_f computes this layer's requantisation, 2: requant_p
   int32_t f_lo, f_hi;   // requant_f: accumulator clamp, multiplier and rounding term
-  int32_t f_m, f_rnd;
+  int32_t f_m, f_mn, f_rnd;
   int64_t rnd;          // 2^(r-1) for r > 0, else 0 (half-up rounding term)
 };
 
@@ -64,6 +66,12 @@ __device__ __forceinline__ int requant_l(int acc, const LayerDev& L) {
 __device__ __forceinline__ int requant_f(int acc, const LayerDev& L) {
   const int a = min(max(acc, L.f_lo), L.f_hi);
   return (__mul24(a, L.f_m) + L.f_rnd) >> L.r;
+}
+
+// The same for a second multiplier below zero (PReLU), rqf = 2.
+__device__ __forceinline__ int requant_p(int acc, const LayerDev& L) {
+  const int a = min(max(acc, L.f_lo), L.f_hi);
+  return (__mul24(a, a >= 0 ? L.f_m : L.f_mn) + L.f_rnd) >> L.r;
 }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -97,10 +105,13 @@ __device__ __forceinline__ LayerDev load_layer(const LayerDev* p) {
   L.npad = q->npad;
   L.a_lo = q->a_lo;
   L.a_hi = q->a_hi;
+  L.biasz = q->biasz;
+  L.z_in = q->z_in;
   L.rqf = q->rqf;
   L.f_lo = q->f_lo;
   L.f_hi = q->f_hi;
   L.f_m = q->f_m;
+  L.f_mn = q->f_mn;
   L.f_rnd = q->f_rnd;
   L.rnd = q->rnd;
   return L;
@@ -139,12 +150,8 @@ struct Tile {
 
 // Gather-GEMM segment: out[row] = epilogue(sum over taps of in[src(row,t)] W[t])
 struct GemmSeg {
-  const int8_t* in;        // input rows (channels below `split`)
-  int64_t in_stride;       // bytes between input rows
-  const int8_t* in2;       // channels from `split` on, when split < cin: [in | in2]
-  int64_t in2_stride;
-  int32_t split;           // first channel read from in2 (cin when unused)
-  int32_t pad_;
+  const int8_t* in;        // input rows
+  const int8_t* in2;       // cin = 2 cout: the rows [in | in2]
   const int32_t* kmap;     // conv: [28][kstride]: 27 tap rows of source rows (-1 = empty), presence masks
   int64_t kstride;
   const uint8_t* ccode;    // down: when set, child c reads row ccode[c] of `in` (a table indexed by code)
@@ -152,9 +159,7 @@ struct GemmSeg {
   const int32_t* cstart;   // down/up: first child row of each parent
   const LayerDev* L;
   int8_t* out;
-  int64_t out_stride;
   const int8_t* resid;     // optional residual added after requantisation
-  int64_t resid_stride;
   int32_t rows;
   int32_t child_rows;      // rows of the child depth (bounds of cstart-derived indices)
 };
@@ -179,7 +184,7 @@ struct GemmArg {
   GemmSeg seg;
   LayerDev L;
   int32_t one;
-  int32_t pad_;
+  int32_t fl;  // flavour of the sparse and dense layers' kernels (model.hip)
 };
 struct PredArg {
   PredSeg seg;
@@ -290,24 +295,29 @@ hipError_t launch_kmap(const uint64_t* keys, int64_t n, int j, const uint64_t* t
 hipError_t launch_kmap_tree(const int32_t* pkmap, int64_t np, const uint8_t* pcode, const int32_t* pcstart,
                             int32_t* kmap, int64_t n, hipStream_t s);
 
-// GEMM families; `mode` selects the row source
+// GEMM families (features in row-major arrays of the output width)
 enum GemmMode { G_CONV = 0, G_DENSE = 1, G_DOWN = 2 };
-// rb: 16-row blocks per wave (1, 2 or 4); tiles then cover 64 * rb rows
-hipError_t launch_gemm(int mode, int cin, int cout, const GemmSeg* segs_dev, const Tile* tiles_dev,
-                       int ntiles, const GemmArg& one, int rb, hipStream_t s);
-// the same over every tap (absent neighbours and child slots contribute
-// zeros): the dense variant the autotuner weighs against the compacted one
-hipError_t launch_gemm_dense(int mode, int cin, int cout, const GemmSeg* segs_dev, const Tile* tiles_dev,
-                             int ntiles, const GemmArg& one, int rb, hipStream_t s);
+// 3x3x3 convolution over the present taps; rb: 16-row blocks per wave (1, 2 or
+// 4), tiles of 64 rb rows
+hipError_t launch_conv(int cin, int cout, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles,
+                       const GemmArg& one, int rb, hipStream_t s);
+// the same with every tap, shared by the four waves of a block; tiles of 16 rb rows
+hipError_t launch_conv_split(int cin, int cout, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles,
+                             const GemmArg& one, int rb, hipStream_t s);
+// dense layer on [in | in2]; tiles of 64 rb rows
+hipError_t launch_dense(int cin, int cout, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles,
+                        const GemmArg& one, int rb, hipStream_t s);
+// child convolution (C -> C); tpw: 16-parent tiles per wave (1 or kDownTiles),
+// tiles of 64 tpw parents
+constexpr int kDownTiles = 8;
+hipError_t launch_down(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one, int tpw,
+                       hipStream_t s);
+// upsampling, every slot of 16-parent blocks; tiles of 64 rb parents
 hipError_t launch_up(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
                      int rb, hipStream_t s);
 // the same over the occupied children only; tiles of P = 128 or 512 parents
 hipError_t launch_up_cx(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
                         int P, hipStream_t s);
-// child convolution (C -> C) over the occupied children only; tiles of P = 64
-// or 128 parents
-hipError_t launch_down_cx(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
-                          int P, hipStream_t s);
 // tile of the compacted child-slot kernels: the large one once a launch has
 // this many of its blocks, else the small one (more blocks in flight)
 constexpr int kSlotTileBlocks = 512;
@@ -320,6 +330,9 @@ hipError_t launch_predict(int C, int mode, const PredSeg* segs_dev, const Tile* 
 // groups of 16 nodes a wave of a launch over this many rows takes (tiles of
 // 64 x that many rows)
 int predict_groups(int64_t rows);
+// output channel of MFMA row m of column block nb of a layer of width C (per
+// child slot for the upsampling)
+inline int out_channel(int nb, int m, int C) { return C / 4 * (m >> 2) + 4 * nb + (m & 3); }
 // row order of the logit layer's weights (symbol of MFMA row m of block b) and
 // its K order (channel of byte j of lane group g; -1 past the width)
 inline int logit_symbol(int b, int m) { return 64 * (m >> 2) + 4 * b + (m & 3); }

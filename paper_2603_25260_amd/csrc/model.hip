@@ -19,6 +19,12 @@ namespace lpcc {
 
 __device__ __forceinline__ v4i ld16(const int8_t* p) { return *(const GAS v4i*)p; }
 
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // N int8 values (N a multiple of 4; p aligned to 4 N bytes up to 16) as one
 // vector access of N/4 32-bit words
 template <int N>
@@ -29,61 +35,6 @@ template <>
 struct Words<8> { typedef int T __attribute__((ext_vector_type(2))); };
 template <>
 struct Words<16> { typedef int T __attribute__((ext_vector_type(4))); };
-
-template <int N>
-__device__ __forceinline__ void ld_bytes(const int8_t* p, int8_t (&v)[N]) {
-  const typename Words<N>::T x = *(const GAS typename Words<N>::T*)p;
-#pragma unroll
-  for (int w = 0; w < N / 4; w++)
-#pragma unroll
-    for (int b = 0; b < 4; b++) v[4 * w + b] = (int8_t)((uint32_t)x[w] >> (8 * b));
-}
-template <int N>
-__device__ __forceinline__ void st_bytes(int8_t* p, const int8_t (&v)[N]) {
-  typename Words<N>::T x;
-#pragma unroll
-  for (int w = 0; w < N / 4; w++) {
-    uint32_t y = 0;
-#pragma unroll
-    for (int b = 0; b < 4; b++) y |= ((uint32_t)(uint8_t)v[4 * w + b]) << (8 * b);
-    x[w] = (int)y;
-  }
-  *(GAS typename Words<N>::T*)p = x;
-}
-
-// Epilogue: one wave's 16 x COUT int32 tile staged in LDS, then every lane
-// handles a contiguous run of COUT/4 columns of one row.
-template <int COUT>
-struct Stage {
-  int32_t v[16][COUT];
-};
-
-// ---------------------------------------------------------------------------
-// Gather-GEMM: out[row][o] = rq(bias[o] + sum_t sum_c in[src(row,t)][c] W[t][c][o]
-//                               + sum over present taps of zc[t][o]) (+ resid)
-// MODE G_CONV : src(row,t) = kmap[t][row]            (27 taps)
-// MODE G_DENSE: src(row,0) = row                      (1 tap)
-// MODE G_DOWN : src(row,o) = child in slot o of parent row, if occupied (8 taps)
-// ---------------------------------------------------------------------------
-template <int MODE>
-struct Taps;
-template <>
-struct Taps<G_CONV> { static constexpr int n = 27; };
-template <>
-struct Taps<G_DENSE> { static constexpr int n = 1; };
-template <>
-struct Taps<G_DOWN> { static constexpr int n = 8; };
-
-template <int MODE>
-__device__ __forceinline__ int src_row(const GemmSeg& S, int row, int tap) {
-  if (MODE == G_CONV) return gp(S.kmap)[(int64_t)tap * S.kstride + row];
-  if (MODE == G_DENSE) return row;
-  uint32_t code = gp(S.code)[row];
-  if (!((code >> tap) & 1u)) return -1;
-  const int cr = gp(S.cstart)[row] + __popc(code & ((1u << tap) - 1u));
-  if (cr >= S.child_rows) return -1;  // only for a corrupt stream
-  return S.ccode != nullptr ? (int)gp(S.ccode)[cr] : cr;  // the embedding table is indexed by the child's code
-}
 
 // Workgroups are dispatched round-robin over the 8 XCDs (block b on XCD
 // b % 8), each with its own L2.  Tile t of a launch goes to the block that
@@ -112,127 +63,138 @@ __device__ __forceinline__ int pick_seg(const GemmSeg* __restrict__ segs, const 
   return tl.row0;
 }
 
-template <int MODE, int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_gemm(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
+// ---------------------------------------------------------------------------
+// All sparse and dense layers of width C form their products transposed: the
+// weights are the MFMA row operand, the gathered rows its columns.  The row
+// order of the packed weights (out_channel) leaves lane (r, g) with the C/4
+// consecutive channels C/4 g .. of ONE output row, r, so a lane requantises
+// and writes its share of the row directly, whole vectors at a time, with no
+// LDS stage, and the biases start in the accumulators.
+//
+// FL is the launch's flavour: F_FAST: requant_f or requant_p serves every
+// segment, no input zero points; F_GENERAL: any requantisation, no input zero
+// points; F_ANY: anything.  Absent inputs must contribute nothing, also with a
+// zero point z (Eq. 13: present inputs contribute (q - z) W).  Their rows are
+// gathered as zeros, or as z with F_ANY, and then every row's sum over the taps
+// the wave multiplies is too large by z times those taps' weights, one number
+// per channel (zc), not per row.
+// ---------------------------------------------------------------------------
+enum { F_GENERAL = 0, F_FAST = 1, F_ANY = 2 };
+
+template <int FL, bool PRELU>
+__device__ __forceinline__ int rq(int acc, const LayerDev& L) {
+  if (FL != F_FAST) return requant_l(acc, L);
+  return PRELU ? requant_p(acc, L) : requant_f(acc, L);
+}
+
+__device__ __forceinline__ uint32_t pack4(int y0, int y1, int y2, int y3) {  // low bytes
+  const uint32_t lo = __builtin_amdgcn_perm((uint32_t)y1, (uint32_t)y0, 0x0C0C0400u);
+  const uint32_t hi = __builtin_amdgcn_perm((uint32_t)y3, (uint32_t)y2, 0x0C0C0400u);
+  return lo | (hi << 16);
+}
+
+// C/4 bytes of a row
+template <int C>
+struct RowPart {
+  typedef typename Words<C / 4>::T T;
+};
+
+// Buffer descriptor of `bytes` bytes at p (below 2^31, wave-uniform): loads
+// past the end return 0 and touch no memory, which is how absent rows are
+// gathered.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, int64_t bytes) {
+  const uint64_t a = (uint64_t)p;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  const int n = __builtin_amdgcn_readfirstlane((int)bytes);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, n, 0x00027000);
+}
+// offset past the end of every descriptor
+constexpr uint32_t kNoRow = 0x80000000u;
+// byte offset of row `row` of width C in an array below 2^31 bytes, kNoRow for -1
+template <int C>
+__device__ __forceinline__ uint32_t row_off(int row) {
+  return min((uint32_t)row, kNoRow / (uint32_t)C) * (uint32_t)C;
+}
+// F_ANY: 16 bytes from channel c of row `row` of an array of any size; zs for
+// an absent row (-1), 0 for padding (-2)
+template <int C>
+__device__ __forceinline__ v4i any_row(const int8_t* in, int row, uint32_t c, int zs) {
+  v4i x = ld16(in + (int64_t)max(row, 0) * C + c);
+  const int f = row == -1 ? zs : 0;
+#pragma unroll
+  for (int q = 0; q < 4; q++) x[q] = row >= 0 ? x[q] : f;
+  return x;
+}
+
+// Epilogue of one row block: the row's share of this lane, requantised, the
+// residual (when res is given) added and clamped.
+template <int C, int FL, bool PRELU>
+__device__ __forceinline__ typename RowPart<C>::T row_out(const v4i (&acc)[C / 16], const LayerDev& L, bool has_res,
+                                                          typename RowPart<C>::T res) {
+  typename RowPart<C>::T w;
+#pragma unroll
+  for (int nb = 0; nb < C / 16; nb++) {
+    int y[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) y[i] = rq<FL, PRELU>(acc[nb][i], L);
+    if (has_res) {
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        y[i] += (int)(int8_t)((uint32_t)res[nb] >> (8 * i));
+        y[i] = min(max(y[i], -128), 127);
+      }
+    }
+    w[nb] = (int)pack4(y[0], y[1], y[2], y[3]);
+  }
+  return w;
+}
+
+// Accumulators of a lane's channels, started with bias (+ extra).
+template <int C>
+__device__ __forceinline__ void acc_bias(v4i (&acc)[C / 16], const int32_t* bias, int g) {
+#pragma unroll
+  for (int nb = 0; nb < C / 16; nb++) acc[nb] = *(const GAS v4i*)(bias + C / 4 * g + 4 * nb);
+}
+
+// ---------------------------------------------------------------------------
+// 3x3x3 submanifold convolution over the present taps only, and dense layers:
+// out[row] = rq(bias + sum_t in[kmap[t][row]] W[t]) (+ resid), in = one array
+// (CIN = C) or two side by side (CIN = 2 C: [in | in2]).
+//
+// A wave owns 16 RB output rows.  Every row has a mask of its present taps
+// (stored after the 27 tap rows); the OR over the wave's rows lists the taps
+// the wave multiplies, in rank order (the tap of rank i sits in lane i of a
+// register, read with readlane); a tap that no row has costs nothing.  The
+// table rows of the present taps are staged straight from global memory into
+// LDS.  A step is one MFMA depth (64): 64 / C taps (one for C = 64) of one
+// input array.  Steps are software-pipelined: the gathers and weights of step
+// v + 1 are in flight behind the products of step v, and the table rows of the
+// step after are read ahead of them.
+//
+// Bound: latency of the gathers (mostly L2) at the occupancy the accumulators
+// leave, and vector issue.  With the gathered rows as the row operand, the
+// accumulators staged through LDS, the 64-bit requantisation and selects that
+// zeroed absent rows and weights, a wave of 64 rows issued 2640 vector
+// instructions (56 % of the issue slots of the launch).
+// ---------------------------------------------------------------------------
+template <int MODE>
+struct Taps;
+template <>
+struct Taps<G_CONV> { static constexpr int n = 27; };
+template <>
+struct Taps<G_DENSE> { static constexpr int n = 1; };
+
+template <int MODE, int CIN, int C, int RB, int FL>
+__global__ __launch_bounds__(256) void k_conv(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
                                               const GemmArg A) {
   constexpr int TAPS = Taps<MODE>::n;
-  constexpr int K = TAPS * CIN;
-  constexpr int KS = (K + 63) / 64;
-  constexpr int NB = COUT / 16;
-  static_assert(CIN % 16 == 0 && COUT % 16 == 0, "widths must be multiples of 16");
-  __shared__ Stage<COUT> st[4];
-
-  GemmSeg S;
-  LayerDev L;
-  const int tile_row0 = pick_seg(segs, tiles, A, S, L);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = lane & 15, g = lane >> 4;
-  const int row0 = tile_row0 + wave * 16;
-  const int row = row0 + r;
-  const bool rv = row < S.rows;
-
-  // epilogue operands first, so that their latency overlaps the main loop
-  constexpr int PER = COUT / 4;
-  const int er = lane >> 2;           // epilogue row within the wave's 16
-  const int ec = (lane & 3) * PER;    // first column
-  const int orow = row0 + er;
-  const bool ov = orow < S.rows;
-  int bia[PER];
-#pragma unroll
-  for (int q = 0; q < PER; q++) bia[q] = gp(L.bias)[ec + q];
-  int8_t res[PER];
-#pragma unroll
-  for (int q = 0; q < PER; q++) res[q] = 0;
-  if (S.resid != nullptr && ov) {
-    ld_bytes<PER>(S.resid + (int64_t)orow * S.resid_stride + ec, res);
-  }
-
-  v4i acc[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; nb++) acc[nb] = v4i{0, 0, 0, 0};
-
-  // source row of every k-step for this lane (taps beyond TAPS are padding)
-  int src[KS];
-#pragma unroll
-  for (int s = 0; s < KS; s++) {
-    const int k0 = 64 * s + 16 * g;
-    const int tap = k0 / CIN;
-    src[s] = (rv && tap < TAPS) ? src_row<MODE>(S, row, tap) : -1;
-  }
-  const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  // software pipeline: the loads of step s + PD - 1 are issued before the
-  // MFMAs of step s; absent neighbours read row 0 and are zeroed afterwards
-  constexpr int PD = 3;
-  v4i abuf[PD], bbuf[PD][NB];
-  auto load_step = [&](int s, v4i& a, v4i (&b)[NB]) {
-    const int k0 = 64 * s + 16 * g;
-    const int c0 = k0 % CIN;
-    const int64_t ur = src[s] >= 0 ? src[s] : 0;
-    const v4i v = c0 < S.split ? ld16(S.in + ur * S.in_stride + c0) : ld16(S.in2 + ur * S.in2_stride + (c0 - S.split));
-    a = src[s] >= 0 ? v : v4i{0, 0, 0, 0};
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++) b[nb] = Wp[((int64_t)s * NB + nb) * 64 + lane];
-  };
-#pragma unroll
-  for (int p = 0; p < PD - 1; p++)
-    if (p < KS) load_step(p, abuf[p], bbuf[p]);
-#pragma unroll
-  for (int s = 0; s < KS; s++) {
-    if (s + PD - 1 < KS) load_step(s + PD - 1, abuf[(s + PD - 1) % PD], bbuf[(s + PD - 1) % PD]);
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++) acc[nb] = mfma16(abuf[s % PD], bbuf[s % PD][nb], acc[nb]);
-  }
-
-  // stage the tile, then requantise row-contiguous runs
-#pragma unroll
-  for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-    for (int i = 0; i < 4; i++) st[wave].v[4 * g + i][16 * nb + r] = acc[nb][i];
-  __syncthreads();
-  if (ov) {
-    int zsum[PER];
-#pragma unroll
-    for (int q = 0; q < PER; q++) zsum[q] = 0;
-    if (L.zc != nullptr) {
-      for (int t = 0; t < TAPS; t++) {
-        if (src_row<MODE>(S, orow, t) < 0) continue;
-#pragma unroll
-        for (int q = 0; q < PER; q++) zsum[q] += gp(L.zc)[t * L.npad + ec + q];
-      }
-    }
-    int8_t outv[PER];
-#pragma unroll
-    for (int q = 0; q < PER; q++) {
-      int a = st[wave].v[er][ec + q] + bia[q] + zsum[q];
-      int y = requant_l(a, L);
-      if (S.resid != nullptr) {
-        y += res[q];
-        y = y < -128 ? -128 : (y > 127 ? 127 : y);
-      }
-      outv[q] = (int8_t)y;
-    }
-    st_bytes<PER>(S.out + (int64_t)orow * S.out_stride + ec, outv);
-  }
-}
-
-// Register-blocked variant for large launches: a wave computes RB blocks of
-// 16 rows, so every weight fragment it loads serves RB MFMAs (the weights
-// are re-read from L2 by every wave; with RB = 1 that traffic exceeds the
-// gathered activations several times over for C >= 32).  The neighbour
-// table of the wave's rows is staged in LDS first (one coalesced load per
-// tap), then each k-step gathers the RB A fragments through it.
-template <int MODE, int CIN, int COUT, int RB>
-__global__ __launch_bounds__(256) void k_gemm_rb(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
-                                                 const GemmArg A) {
-  constexpr int TAPS = Taps<MODE>::n;
-  constexpr int K = TAPS * CIN;
-  constexpr int KS = (K + 63) / 64;
-  constexpr int NB = COUT / 16;
-  constexpr int WR = 16 * RB;  // rows per wave
-  static_assert(CIN % 16 == 0 && COUT % 16 == 0 && (CIN & (CIN - 1)) == 0, "widths");
-  static_assert(WR <= 64, "at most 64 rows per wave");
-  __shared__ Stage<COUT> st[4];
-  __shared__ int32_t skm[MODE == G_CONV ? 4 : 1][MODE == G_CONV ? TAPS : 1][WR];
+  constexpr int NB = C / 16;
+  constexpr int NA = CIN / C;     // input arrays
+  constexpr int TPS = 64 / C;     // taps per step
+  constexpr int WR = 16 * RB;     // rows per wave
+  static_assert((CIN == C || CIN == 2 * C) && (C == 16 || C == 32 || C == 64) && WR <= 64, "shape");
+  __shared__ int32_t skm_all[MODE == G_CONV ? 4 * 28 * WR : 1];
 
   GemmSeg S;
   LayerDev L;
@@ -240,225 +202,27 @@ __global__ __launch_bounds__(256) void k_gemm_rb(const GemmSeg* __restrict__ seg
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
   const int wrow0 = tile_row0 + wave * WR;
+  int32_t* skm = skm_all + (MODE == G_CONV ? wave * 28 * WR : 0);  // [rank][WR], one rank of padding
 
-  // epilogue operands first
-  constexpr int PER = COUT / 4;
-  const int er = lane >> 2, ec = (lane & 3) * PER;
-  int bia[PER];
-#pragma unroll
-  for (int q = 0; q < PER; q++) bia[q] = gp(L.bias)[ec + q];
-  int8_t res[RB][PER];
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-    const int orow = wrow0 + 16 * rb + er;
-#pragma unroll
-    for (int q = 0; q < PER; q++) res[rb][q] = 0;
-    if (S.resid != nullptr && orow < S.rows) {
-      ld_bytes<PER>(S.resid + (int64_t)orow * S.resid_stride + ec, res[rb]);
-    }
-  }
-
-  // per row block: the row of this lane, and for the child convolution its
-  // parent's code and first child
-  uint32_t pcode[RB];
-  int pcs[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-    const int row = wrow0 + 16 * rb + r;
-    pcode[rb] = 0u;
-    pcs[rb] = 0;
-    if (MODE == G_DOWN && row < S.rows) {
-      pcode[rb] = gp(S.code)[row];
-      pcs[rb] = gp(S.cstart)[row];
-    }
-  }
-  if (MODE == G_CONV) {
-    if (lane < WR) {
-      const int row = wrow0 + lane;
-      const bool ok = row < S.rows;
-#pragma unroll
-      for (int t = 0; t < TAPS; t++) skm[wave][t][lane] = ok ? gp(S.kmap)[(int64_t)t * S.kstride + row] : -1;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  auto src_of = [&](int rb, int tap) -> int {
-    const int row = wrow0 + 16 * rb + r;
-    if (tap >= TAPS || row >= S.rows) return -1;
-    if (MODE == G_CONV) return skm[MODE == G_CONV ? wave : 0][MODE == G_CONV ? tap : 0][16 * rb + r];
-    if (MODE == G_DENSE) return row;
-    if (!((pcode[rb] >> tap) & 1u)) return -1;
-    const int cr = pcs[rb] + __popc(pcode[rb] & ((1u << tap) - 1u));
-    if (cr >= S.child_rows) return -1;
-    return S.ccode != nullptr ? (int)gp(S.ccode)[cr] : cr;  // the embedding table is indexed by the child's code
-  };
-
-  v4i acc[RB][NB];
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++)
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++) acc[rb][nb] = v4i{0, 0, 0, 0};
-  const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  constexpr int LC = __builtin_ctz(CIN);
-  // [in | in2] layers (the ResBlock at k0 on [F | G]) are exactly those with
-  // cin = 2 cout, split at cout; the feature arrays stay below 2^31 bytes
-  // (checked on the host), so row offsets are 32-bit
-  constexpr int SPLIT = CIN == 2 * COUT ? COUT : CIN;
-  const GAS int8_t* in1 = gp(S.in);
-  const GAS int8_t* in2 = gp(S.in2);
-  const uint32_t st1 = (uint32_t)S.in_stride, st2 = (uint32_t)S.in2_stride;
-  // Software pipeline over the k-steps: the gathers and weight fragments of
-  // step s + PD - 1 are issued before the MFMAs of step s, so PD - 1 steps of
-  // loads are in flight behind the math instead of one load latency per
-  // step.  Absent neighbours read row 0 (every launch has one) and are
-  // zeroed after the load, which keeps the gathers free of branches.
-  constexpr int PD = 3;
-  v4i abuf[PD][RB], bbuf[PD][NB];
-  auto load_step = [&](int s, v4i (&a)[RB], v4i (&b)[NB]) {
-    const int k0 = 64 * s + 16 * g;
-    const int tap = k0 >> LC, c0 = k0 & (CIN - 1);
-#pragma unroll
-    for (int rb = 0; rb < RB; rb++) {
-      const int sr = src_of(rb, tap);
-      const uint32_t ur = sr >= 0 ? (uint32_t)sr : 0u;
-      const v4i v = c0 < SPLIT ? *(const GAS v4i*)(in1 + (ur * st1 + (uint32_t)c0))
-                               : *(const GAS v4i*)(in2 + (ur * st2 + (uint32_t)(c0 - SPLIT)));
-      a[rb] = sr >= 0 ? v : v4i{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++) b[nb] = Wp[((int64_t)s * NB + nb) * 64 + lane];
-  };
-#pragma unroll
-  for (int p = 0; p < PD - 1; p++)
-    if (p < KS) load_step(p, abuf[p], bbuf[p]);
-#pragma unroll
-  for (int s = 0; s < KS; s++) {
-    if (s + PD - 1 < KS) load_step(s + PD - 1, abuf[(s + PD - 1) % PD], bbuf[(s + PD - 1) % PD]);
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-      for (int rb = 0; rb < RB; rb++) acc[rb][nb] = mfma16(abuf[s % PD][rb], bbuf[s % PD][nb], acc[rb][nb]);
-  }
-
-  // epilogue, one row block at a time through the wave's LDS stage
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) st[wave].v[4 * g + i][16 * nb + r] = acc[rb][nb][i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int orow = wrow0 + 16 * rb + er;
-    if (orow < S.rows) {
-      int zsum[PER];
-#pragma unroll
-      for (int q = 0; q < PER; q++) zsum[q] = 0;
-      if (L.zc != nullptr) {
-        for (int t = 0; t < TAPS; t++) {
-          int present;
-          if (MODE == G_CONV) present = skm[MODE == G_CONV ? wave : 0][MODE == G_CONV ? t : 0][16 * rb + er] >= 0;
-          else present = src_row<MODE>(S, orow, t) >= 0;
-          if (!present) continue;
-#pragma unroll
-          for (int q = 0; q < PER; q++) zsum[q] += gp(L.zc)[t * L.npad + ec + q];
-        }
-      }
-      int8_t outv[PER];
-#pragma unroll
-      for (int q = 0; q < PER; q++) {
-        int y = requant_l(st[wave].v[er][ec + q] + bia[q] + zsum[q], L);
-        if (S.resid != nullptr) {
-          y += res[rb][q];
-          y = y < -128 ? -128 : (y > 127 ? 127 : y);
-        }
-        outv[q] = (int8_t)y;
-      }
-      st_bytes<PER>(S.out + (int64_t)orow * S.out_stride + ec, outv);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Gather-GEMM over the present taps only (kernel-map compaction) for the
-// 3x3x3 convolution and the child convolution.  A wave owns WR = 16 RB
-// output rows.  Every row has a bit mask of its present taps: the presence
-// mask the neighbour-table kernel stores after the 27 tap rows, or for the
-// child convolution the parent's occupancy code.  The OR of the masks over
-// the wave's rows sets the wave's K dimension: its nt taps, ranked by tap
-// index, times CIN channels, in k-steps of 64.  A tap that no row of the
-// wave has costs nothing (no table read, weight load, gather or MFMA); rows
-// without a present tap contribute a zero A fragment.  Only the table rows
-// of the present taps are staged, straight from global memory into LDS.
-// The tap of rank i sits in lane i of a register (read with readlane), and
-// the weights of tap t, channel c are rows k = t CIN + c of the packed
-// layout, so any tap's B fragment is addressed directly.  The sums are exact
-// int32, so the order of the taps does not change the result.
-// ---------------------------------------------------------------------------
-template <int MODE, int CIN, int COUT, int RB>
-__global__ __launch_bounds__(256) void k_gemm_cx(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
-                                                 const GemmArg A) {
-  constexpr int TAPS = Taps<MODE>::n;
-  constexpr int NB = COUT / 16;
-  constexpr int WR = 16 * RB;  // rows per wave
-  static_assert(MODE == G_CONV || MODE == G_DOWN, "tap-compacted modes");
-  static_assert(CIN % 16 == 0 && COUT % 16 == 0 && (CIN & (CIN - 1)) == 0, "widths");
-  static_assert(WR <= 64 && TAPS <= 32, "shape");
-  // Per wave, one LDS region holds first the neighbour rows of the wave's
-  // rows (slot i = the tap of rank i, lane l = row wrow0 + l), then, after
-  // the k-loop, the accumulator stage of the epilogue.
-  constexpr int KMW = MODE == G_CONV ? TAPS * WR : 0;
-  constexpr int RW = KMW > 16 * COUT ? KMW : 16 * COUT;  // words per wave
-  __shared__ __attribute__((aligned(16))) int32_t smem[4 * RW];
-
-  GemmSeg S;
-  LayerDev L;
-  const int tile_row0 = pick_seg(segs, tiles, A, S, L, 4 * WR);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = lane & 15, g = lane >> 4;
-  const int wrow0 = tile_row0 + wave * WR;
-  int32_t* skm = smem + wave * RW;  // [slot][WR]
-  Stage<COUT>* st = (Stage<COUT>*)(smem + wave * RW);
-
-  // presence masks: the table's (one load per row) or the parents' codes
-  uint32_t pcode[RB];
-  int pcs[RB];
-  uint32_t mine = 0u;
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-    const int row = wrow0 + 16 * rb + r;
-    pcode[rb] = 0u;
-    pcs[rb] = 0;
-    if (MODE == G_DOWN && row < S.rows) {
-      pcode[rb] = gp(S.code)[row] & 0xFFu;
-      pcs[rb] = gp(S.cstart)[row];
-    }
-    mine |= pcode[rb];
-  }
+  // the union of the rows' taps, and lane i: the tap of rank i
   const int myrow = wrow0 + lane;
-  if (MODE == G_CONV && lane < WR && myrow < S.rows) mine = (uint32_t)gp(S.kmap)[27 * S.kstride + myrow];
-  uint32_t U = mine;
+  uint32_t U = MODE == G_DENSE ? 1u : 0u;
+  int tapof = 0;
+  if (MODE == G_CONV) {
+    if (lane < WR && myrow < S.rows) U = (uint32_t)gp(S.kmap)[27 * S.kstride + myrow];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) U |= (uint32_t)__shfl_xor((int)U, o);
-  U = (uint32_t)__builtin_amdgcn_readfirstlane((int)U);
+    for (int o = 1; o < 64; o <<= 1) U |= (uint32_t)__shfl_xor((int)U, o);
+    U = (uint32_t)__builtin_amdgcn_readfirstlane((int)U);
+  }
   const int nt = __popc(U);
-  // lane i: the tap of rank i (255 past the last); the owner of each set bit
-  // sends its tap to the lane of its rank
-  int tapof;
-  {
+  if (MODE == G_CONV) {
+    // the owner of each set bit sends its tap to the lane of its rank
     const bool own = lane < TAPS && ((U >> (lane & 31)) & 1u);
     const int rk = __popc(U & ((1u << (lane & 31)) - 1u));
     const int got = __builtin_amdgcn_ds_permute((own ? rk : 63) * 4, lane);
-    tapof = lane < nt ? got : 255;
-  }
-  if (MODE == G_CONV) {
+    tapof = lane < nt ? got : 0;
     // table rows of the present taps, straight into LDS (rows past the end
-    // read the last row; they are never used)
+    // read the last row; they are never written out)
     const int crow = min(myrow, S.rows - 1);
     uint32_t rem = U;
     if (lane < WR) {
@@ -469,205 +233,391 @@ __global__ __launch_bounds__(256) void k_gemm_cx(const GemmSeg* __restrict__ seg
                                          (__attribute__((address_space(3))) void*)(skm + i * WR), 4, 0, 0);
       }
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the staged rows have landed
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-  // source row of block rb for the tap of rank `slot` (tap `tap`), or -1
-  auto src_of = [&](int rb, int slot, int tap) -> int {
-    const int row = wrow0 + 16 * rb + r;
-    if (row >= S.rows) return -1;
-    if (MODE == G_CONV) return skm[slot * WR + 16 * rb + r];
-    if (!((pcode[rb] >> tap) & 1u)) return -1;
-    const int cr = pcs[rb] + __popc(pcode[rb] & ((1u << tap) - 1u));
-    if (cr >= S.child_rows) return -1;  // only for a corrupt stream
-    return S.ccode != nullptr ? (int)gp(S.ccode)[cr] : cr;  // the embedding table is indexed by the child's code
-  };
-
+  // accumulators: biases, with zero points the correction of the wave's taps
   v4i acc[RB][NB];
+  acc_bias<C>(acc[0], L.bias, g);
+  if (MODE == G_CONV && FL == F_ANY && L.zc != nullptr) {
+    for (int i = 0; i < nt; i++) {
+      const int32_t* z = L.zc + (int64_t)__builtin_amdgcn_readlane(tapof, i) * L.npad;
+      v4i zz[NB];
+      acc_bias<C>(zz, z, g);
 #pragma unroll
-  for (int rb = 0; rb < RB; rb++)
+      for (int nb = 0; nb < NB; nb++) acc[0][nb] += zz[nb];
+    }
+  }
 #pragma unroll
-    for (int nb = 0; nb < NB; nb++) acc[rb][nb] = v4i{0, 0, 0, 0};
-  const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  constexpr int LC = __builtin_ctz(CIN);
-  constexpr int SPLIT = CIN == 2 * COUT ? COUT : CIN;  // [in | in2] layers have cin = 2 cout
-  // taps per k-step (CIN < 64: lane group g takes slot base + (16 g >> LC))
-  constexpr int SPS = CIN >= 64 ? 1 : 64 / CIN;
-  const GAS int8_t* in1 = gp(S.in);
-  const GAS int8_t* in2 = gp(S.in2);
-  const uint32_t st1 = (uint32_t)S.in_stride, st2 = (uint32_t)S.in2_stride;
-  const int KV = (nt * CIN + 63) >> 6;  // k-steps over the present taps (wave-uniform)
+  for (int rb = 1; rb < RB; rb++)
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) acc[rb][nb] = acc[0][nb];
+  const int zs = FL == F_ANY ? (L.z_in & 0xFF) * 0x01010101 : 0;
 
-  // Software pipeline over the k-steps, one step of loads in flight behind
-  // the MFMAs.  The loop body is straight-line code: steps past the last
-  // present tap, and rows without the step's tap, load from row 0 and the
-  // first weight fragment and are zeroed after the load.
-  constexpr int PD = 2;
-  v4i abuf[PD][RB], bbuf[PD][NB];
-  auto load_step = [&](int v, v4i (&a)[RB], v4i (&b)[NB]) {
-    const int kk = 64 * v + 16 * g;
-    const int c0 = kk & (CIN - 1);
-    int slot, tap;
-    if (SPS == 1) {
-      slot = min((64 * v) >> LC, 31);
-      tap = __builtin_amdgcn_readlane(tapof, slot);
-    } else {
-      const int base = min(v * SPS, 28);
-      int tk[SPS];
-#pragma unroll
-      for (int k = 0; k < SPS; k++) tk[k] = __builtin_amdgcn_readlane(tapof, base + k);
-      const int k = (16 * g) >> LC;
-      slot = base + k;
-      tap = tk[0];
-#pragma unroll
-      for (int q = 1; q < SPS; q++) tap = k == q ? tk[q] : tap;
-    }
-    const bool tv = tap < TAPS;
-    const int ko = tv ? tap * CIN + c0 : 0;
-    const GAS v4i* w = Wp + (int64_t)(ko >> 6) * NB * 64 + ((ko >> 4) & 3) * 16 + r;
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++) {
-      const v4i x = w[nb * 64];
-      b[nb] = tv ? x : v4i{0, 0, 0, 0};
-    }
+  // a dense layer's descriptors cover the wave's rows alone
+  const int dbase = MODE == G_DENSE ? min(wrow0, S.rows) : 0;
+  const int64_t in_bytes = (int64_t)(MODE == G_DENSE ? min(S.rows - dbase, WR) : S.rows) * C;
+  const __amdgpu_buffer_rsrc_t b1 = rsrc_of(S.in + (int64_t)dbase * C, in_bytes);
+  const __amdgpu_buffer_rsrc_t b2 = rsrc_of((NA == 2 ? S.in2 : S.in) + (int64_t)dbase * C, in_bytes);
+  const uint32_t c0 = (uint32_t)((16 * g) & (C - 1));  // first channel of this lane's slice
+  const int kt = (16 * g) / C;                         // this lane's tap within the step (0 for C = 64)
+  const int ng = (nt + TPS - 1) / TPS;                 // groups of TPS taps
+  const int KV = ng * NA;
+
+  if (MODE == G_CONV) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the staged rows have landed
+  wave_lds_sync();
+
+  // byte offsets of this lane's source rows for tap group i (kNoRow for absent
+  // rows and taps past the last); F_ANY: the rows (-1, -2)
+  auto rows_of = [&](int i, uint32_t (&o)[RB]) {
+    const int slot = min(i * TPS + kt, 27);
+    const bool tv = i * TPS + kt < nt;
 #pragma unroll
     for (int rb = 0; rb < RB; rb++) {
-      const int sr = tv ? src_of(rb, slot, tap) : -1;
-      const bool present = sr >= 0;
-      const uint32_t ur = present ? (uint32_t)sr : 0u;
-      const v4i x = c0 < SPLIT ? *(const GAS v4i*)(in1 + (ur * st1 + (uint32_t)c0))
-                               : *(const GAS v4i*)(in2 + (ur * st2 + (uint32_t)(c0 - SPLIT)));
-      a[rb] = present ? x : v4i{0, 0, 0, 0};
+      int row = MODE == G_CONV ? skm[slot * WR + 16 * rb + r] : 16 * rb + r;
+      row = tv ? row : (FL == F_ANY ? -2 : -1);
+      o[rb] = FL == F_ANY ? (uint32_t)row : row_off<C>(row);
     }
   };
+  // this lane's weights of step (i, h): rows k = tap CIN + h C + c of the
+  // packed layout
+  auto weights = [&](int i, int h, v4i (&w)[NB]) {
+    if (C == 64) {
+      const int tap = MODE == G_CONV ? __builtin_amdgcn_readlane(tapof, min(i, 63)) : 0;
+      const GAS int8_t* p = gp(L.Wp) + (int64_t)(tap * NA + h) * (NB * 1024) + 16 * (uint32_t)lane;
 #pragma unroll
-  for (int p = 0; p < PD - 1; p++) load_step(p, abuf[p], bbuf[p]);
-  for (int v0 = 0; v0 < KV; v0 += PD) {
+      for (int nb = 0; nb < NB; nb++) w[nb] = *(const GAS v4i*)(p + 1024 * nb);
+    } else {
+      int tap = 0;
+      if (MODE == G_CONV) {
+        const int base = min(i * TPS, 60);
+        tap = __builtin_amdgcn_readlane(tapof, base);
 #pragma unroll
-    for (int u = 0; u < PD; u++) {
-      load_step(v0 + u + PD - 1, abuf[(u + PD - 1) % PD], bbuf[(u + PD - 1) % PD]);
+        for (int q = 1; q < TPS; q++) {
+          const int tq = __builtin_amdgcn_readlane(tapof, base + q);
+          tap = kt == q ? tq : tap;
+        }
+      }
+      const int k = tap * CIN + h * C + (int)c0;
+      const GAS int8_t* p = gp(L.Wp) + (int64_t)(k >> 6) * (NB * 1024) + (((k >> 4) & 3) * 16 + r) * 16;
 #pragma unroll
-      for (int rb = 0; rb < RB; rb++)
+      for (int nb = 0; nb < NB; nb++) w[nb] = *(const GAS v4i*)(p + 1024 * nb);
+    }
+  };
+  auto gather = [&](int h, const uint32_t (&o)[RB], v4i (&x)[RB]) {
 #pragma unroll
-        for (int nb = 0; nb < NB; nb++) acc[rb][nb] = mfma16(abuf[u][rb], bbuf[u][nb], acc[rb][nb]);
+    for (int rb = 0; rb < RB; rb++) {
+      if (FL == F_ANY) x[rb] = any_row<C>(h == 0 ? S.in : S.in2, (int)o[rb], c0, zs);
+      else x[rb] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(h == 0 ? b1 : b2, o[rb] + c0, 0, 0);
+    }
+  };
+
+  // two steps per iteration (for two arrays: both arrays of one tap group;
+  // else two groups), each loading the next one's operands first
+  uint32_t o0[RB], o1[RB];
+  v4i x0[RB], x1[RB], w0[NB], w1[NB];
+  auto mul = [&](const v4i (&x)[RB], const v4i (&w)[NB]) {
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) acc[rb][nb] = mfma16(w[nb], x[rb], acc[rb][nb]);
+  };
+  rows_of(0, o0);
+  weights(0, 0, w0);
+  gather(0, o0, x0);
+  for (int v = 0; v < KV; v += 2) {
+    if (NA == 2) {
+      weights(v / 2, 1, w1);
+      gather(1, o0, x1);
+      rows_of(v / 2 + 1, o0);
+      mul(x0, w0);
+      weights(v / 2 + 1, 0, w0);
+      gather(0, o0, x0);
+      mul(x1, w1);
+    } else {
+      rows_of(v + 1, o1);
+      weights(v + 1, 0, w1);
+      gather(0, o1, x1);
+      mul(x0, w0);
+      rows_of(v + 2, o0);
+      weights(v + 2, 0, w0);
+      gather(0, o0, x0);
+      mul(x1, w1);
     }
   }
 
-  // epilogue, one row block at a time through the wave's LDS stage, which
-  // reuses the region of the staged neighbour rows (its operands are loaded
-  // only now: registers, not latency, bound the k-loop)
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  constexpr int PER = COUT / 4;
-  const int er = lane >> 2, ec = (lane & 3) * PER;
-  int bia[PER];
-#pragma unroll
-  for (int q = 0; q < PER; q++) bia[q] = gp(L.bias)[ec + q];
+  typedef typename RowPart<C>::T P;
 #pragma unroll
   for (int rb = 0; rb < RB; rb++) {
-    int8_t res[PER];
+    const int row = wrow0 + 16 * rb + r;
+    if (row >= S.rows) continue;
+    const int64_t at = (int64_t)row * C + C / 4 * g;
+    P res;
+    if (S.resid != nullptr) res = *(const GAS P*)(gp(S.resid) + at);
+    const P w = S.resid != nullptr ? row_out<C, FL, false>(acc[rb], L, true, res)
+                                   : row_out<C, FL, false>(acc[rb], L, false, res);
+    *(GAS P*)(gp(S.out) + at) = w;
+  }
+}
+
+// The same convolution for launches of few rows: a block owns 16 RB rows and
+// its four waves share the taps (tap groups w, w + 4, ...; every tap, present
+// or not), so the serial chain of gathers is a quarter as long and the chip
+// has four times the waves.  The partial sums meet in LDS.
+template <int CIN, int C, int RB, int FL>
+__global__ __launch_bounds__(256) void k_conv_split(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
+                                                    const GemmArg A) {
+  constexpr int NB = C / 16;
+  constexpr int NA = CIN / C;
+  constexpr int TPS = 64 / C;
+  constexpr int WR = 16 * RB;
+  constexpr int NG = (27 + TPS - 1) / TPS;   // groups of TPS taps
+  constexpr int GW = (NG + 3) / 4;           // groups per wave
+  static_assert((CIN == C || CIN == 2 * C) && (C == 16 || C == 32 || C == 64), "shape");
+  __shared__ v4i part[3][RB][NB][64];
+
+  GemmSeg S;
+  LayerDev L;
+  const int row0 = pick_seg(segs, tiles, A, S, L, WR);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  const uint32_t c0 = (uint32_t)((16 * g) & (C - 1));
+  const int kt = (16 * g) / C;
+  const int zs = FL == F_ANY ? (L.z_in & 0xFF) * 0x01010101 : 0;
+  const int64_t in_bytes = (int64_t)S.rows * C;
+  const __amdgpu_buffer_rsrc_t b1 = rsrc_of(S.in, in_bytes);
+  const __amdgpu_buffer_rsrc_t b2 = rsrc_of(NA == 2 ? S.in2 : S.in, in_bytes);
+
+  // source rows of all the wave's groups first (one round trip)
+  uint32_t o[GW][RB];
 #pragma unroll
-    for (int q = 0; q < PER; q++) res[q] = 0;
-    if (S.resid != nullptr && wrow0 + 16 * rb + er < S.rows) {
-      ld_bytes<PER>(S.resid + (int64_t)(wrow0 + 16 * rb + er) * S.resid_stride + ec, res);
+  for (int q = 0; q < GW; q++) {
+    const int tap = (wave + 4 * q) * TPS + kt;
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++) {
+      const int row = row0 + 16 * rb + r;
+      const int src = tap < 27 && row < S.rows ? gp(S.kmap)[(int64_t)tap * S.kstride + row] : (tap < 27 ? -1 : -2);
+      o[q][rb] = FL == F_ANY ? (uint32_t)src : row_off<C>(src);
     }
+  }
+  v4i acc[RB][NB];
+#pragma unroll
+  for (int rb = 0; rb < RB; rb++) {
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) acc[rb][nb] = v4i{0, 0, 0, 0};
+    if (wave == 0) acc_bias<C>(acc[rb], FL == F_ANY ? L.biasz : L.bias, g);
+  }
+#pragma unroll
+  for (int q = 0; q < GW; q++) {
+    const int tap = min((wave + 4 * q) * TPS + kt, 26);
+#pragma unroll
+    for (int h = 0; h < NA; h++) {
+      const int k = tap * CIN + h * C + (int)c0;
+      const GAS int8_t* p = gp(L.Wp) + (int64_t)(k >> 6) * (NB * 1024) + (((k >> 4) & 3) * 16 + r) * 16;
+      v4i w[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) w[nb] = *(const GAS v4i*)(p + 1024 * nb);
+#pragma unroll
+      for (int rb = 0; rb < RB; rb++) {
+        v4i x;
+        if (FL == F_ANY) x = any_row<C>(h == 0 ? S.in : S.in2, (int)o[q][rb], c0, zs);
+        else x = (v4i)__builtin_amdgcn_raw_buffer_load_b128(h == 0 ? b1 : b2, o[q][rb] + c0, 0, 0);
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++) acc[rb][nb] = mfma16(w[nb], x, acc[rb][nb]);
+      }
+    }
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) part[wave - 1][rb][nb][lane] = acc[rb][nb];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  typedef typename RowPart<C>::T P;
+#pragma unroll
+  for (int rb = 0; rb < RB; rb++) {
 #pragma unroll
     for (int nb = 0; nb < NB; nb++)
 #pragma unroll
-      for (int i = 0; i < 4; i++) st->v[4 * g + i][16 * nb + r] = acc[rb][nb][i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int orow = wrow0 + 16 * rb + er;
-    // presence mask of the epilogue row (zero-point correction over its taps)
-    const uint32_t omask = MODE == G_CONV ? (uint32_t)__shfl((int)mine, (16 * rb + er) & 63) : 0u;
-    if (orow < S.rows) {
-      int zsum[PER];
+      for (int w = 0; w < 3; w++) acc[rb][nb] += part[w][rb][nb][lane];
+    const int row = row0 + 16 * rb + r;
+    if (row >= S.rows) continue;
+    const int64_t at = (int64_t)row * C + C / 4 * g;
+    P res;
+    if (S.resid != nullptr) res = *(const GAS P*)(gp(S.resid) + at);
+    const P w = S.resid != nullptr ? row_out<C, FL, false>(acc[rb], L, true, res)
+                                   : row_out<C, FL, false>(acc[rb], L, false, res);
+    *(GAS P*)(gp(S.out) + at) = w;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Child convolution (the stride-2 step of the re-densification, Eq. 4):
+// out[q] = rq(b + sum over children c of q of in[c] W[slot(c)]).  With `ccode`
+// set, child c reads row ccode[c] of `in`: the occupancy embedding of depth j
+// depends on the code alone, so the first step reads a 256-row table.
+//
+// A wave keeps the whole layer (8 slots: 8 C^2 bytes, 128 registers at C = 64)
+// and takes 16 parents at a time, one per column, over all eight slots: an
+// absent child is gathered as zeros, at no memory cost.  The zeros cost matrix
+// cycles (1.1 to 2 of 8 slots are occupied; 512 cycles per 16 parents at C =
+// 64), but no compaction, no LDS and no atomics: the form with lists of the
+// occupied children per slot, 16-entry groups and int32 accumulators in LDS
+// spent 920 vector instructions and 150 LDS ones per wave and 128 parents and
+// took 1.62 ms for the 8-frame 128-beam batch (14 M parents).
+// ---------------------------------------------------------------------------
+template <int C, int TPW, int FL>
+__global__ __launch_bounds__(256) void k_down(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
+                                              const GemmArg A) {
+  constexpr int NB = C / 16;
+  constexpr int SPS = 64 / C;       // slots per step
+  constexpr int KS = 8 / SPS;       // steps
+  static_assert(C == 16 || C == 32 || C == 64, "C");
+  GemmSeg S;
+  LayerDev L;
+  const int q0 = pick_seg(segs, tiles, A, S, L, 64 * TPW);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  const uint32_t c0 = (uint32_t)((16 * g) & (C - 1));
+  const int kt = (16 * g) / C;      // this lane's slot within a step
+  const int wrow0 = q0 + wave * 16 * TPW;
+  if (wrow0 >= S.rows) return;      // wave-uniform, no barrier below
+  // the children of consecutive parents are consecutive rows: descriptors of
+  // the wave's alone (their first row, at most 8 per parent)
+  const bool table = S.ccode != nullptr;
+  const int cbase = min(__builtin_amdgcn_readfirstlane(gp(S.cstart)[wrow0]), S.child_rows);
+  const int crows = min(S.child_rows - cbase, 128 * TPW);
+  const __amdgpu_buffer_rsrc_t bin =
+      table ? rsrc_of(S.in, 256 * C) : rsrc_of(S.in + (int64_t)cbase * C, (int64_t)crows * C);
+  const __amdgpu_buffer_rsrc_t bcc = rsrc_of(table ? S.ccode + cbase : S.code, table ? crows : 0);
+  const int zs = FL == F_ANY ? (L.z_in & 0xFF) * 0x01010101 : 0;
+
+  v4i w[KS][NB], bias[NB];
+  {
+    const GAS int8_t* p = gp(L.Wp) + 16 * (uint32_t)lane;
 #pragma unroll
-      for (int q = 0; q < PER; q++) zsum[q] = 0;
-      if (L.zc != nullptr) {
-        for (int t = 0; t < TAPS; t++) {
-          const int present = MODE == G_CONV ? (int)((omask >> t) & 1u) : (int)(src_row<MODE>(S, orow, t) >= 0);
-          if (!present) continue;
+    for (int s = 0; s < KS; s++)
 #pragma unroll
-          for (int q = 0; q < PER; q++) zsum[q] += gp(L.zc)[t * L.npad + ec + q];
-        }
-      }
-      int8_t outv[PER];
+      for (int nb = 0; nb < NB; nb++) w[s][nb] = *(const GAS v4i*)(p + 1024 * (s * NB + nb));
+  }
+  acc_bias<C>(bias, FL == F_ANY ? L.biasz : L.bias, g);
+
+  // children of the wave's tile t: the lane's row offsets, by step (kNoRow
+  // where the child is absent, or past the depth in a corrupt stream)
+  auto rows_of = [&](int t, uint32_t (&o)[KS]) {
+    const int q = wrow0 + 16 * t + r;
+    const uint32_t code = q < S.rows ? (uint32_t)gp(S.code)[q] : 0u;
+    const int first = q < S.rows ? gp(S.cstart)[q] - cbase : 0;
 #pragma unroll
-      for (int q = 0; q < PER; q++) {
-        int y = requant_l(st->v[er][ec + q] + bia[q] + zsum[q], L);
-        if (S.resid != nullptr) {
-          y += res[q];
-          y = y < -128 ? -128 : (y > 127 ? 127 : y);
-        }
-        outv[q] = (int8_t)y;
-      }
-      st_bytes<PER>(S.out + (int64_t)orow * S.out_stride + ec, outv);
+    for (int s = 0; s < KS; s++) {
+      const int slot = s * SPS + kt;
+      const int c = first + __popc(code & ((1u << slot) - 1u));
+      const bool has = ((code >> slot) & 1u) && c < crows;
+      o[s] = has ? (uint32_t)c * (table ? 1u : (uint32_t)C) : kNoRow;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (table) {  // uniform
+#pragma unroll
+      for (int s = 0; s < KS; s++) {
+        const uint32_t e = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(bcc, o[s], 0, 0);
+        o[s] = o[s] == kNoRow ? kNoRow : e * (uint32_t)C;
+      }
+    }
+  };
+  auto gather = [&](const uint32_t (&o)[KS], v4i (&x)[KS]) {
+#pragma unroll
+    for (int s = 0; s < KS; s++) {
+      x[s] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(bin, o[s] + c0, 0, 0);
+      if (FL == F_ANY) {
+#pragma unroll
+        for (int z = 0; z < 4; z++) x[s][z] = o[s] != kNoRow ? x[s][z] : zs;
+      }
+    }
+  };
+  typedef typename RowPart<C>::T P;
+  uint32_t o[KS];
+  v4i x[KS];
+  rows_of(0, o);
+  gather(o, x);
+  for (int t = 0; t < TPW; t++) {
+    const int q = wrow0 + 16 * t + r;
+    if (wrow0 + 16 * t >= S.rows) break;  // wave-uniform
+    if (t + 1 < TPW) rows_of(t + 1, o);
+    v4i acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) acc[nb] = bias[nb];
+#pragma unroll
+    for (int s = 0; s < KS; s++)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) acc[nb] = mfma16(w[s][nb], x[s], acc[nb]);
+    if (t + 1 < TPW) gather(o, x);
+    if (q < S.rows) {
+      P none;
+      *(GAS P*)(gp(S.out) + (int64_t)q * C + C / 4 * g) = row_out<C, FL, false>(acc, L, false, none);
+    }
   }
 }
 
-template <int MODE>
-static hipError_t launch_gemm_mode(int cin, int cout, const GemmSeg* segs, const Tile* tiles, int ntiles,
-                                   const GemmArg& A, int rb, hipStream_t s) {
-#define LPCC_G(CI, CO)                                                                                    \
-  if (cin == CI && cout == CO) {                                                                          \
-    if (rb == 4)                                                                                          \
-      hipLaunchKernelGGL((k_gemm_rb<MODE, CI, CO, 4>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);    \
-    else if (rb == 2)                                                                                     \
-      hipLaunchKernelGGL((k_gemm_rb<MODE, CI, CO, 2>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);    \
-    else                                                                                                  \
-      hipLaunchKernelGGL((k_gemm<MODE, CI, CO>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);          \
-    return hipGetLastError();                                                                             \
-  }
-  LPCC_G(16, 16) LPCC_G(32, 16) LPCC_G(32, 32) LPCC_G(64, 32) LPCC_G(64, 64) LPCC_G(128, 64)
-#undef LPCC_G
-  return hipErrorInvalidValue;
-}
+// flavour of a launch's layers
+#define LPCC_FL(K, ...)                                                                                    \
+  if (A.fl == F_FAST) hipLaunchKernelGGL((K<__VA_ARGS__, F_FAST>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A); \
+  else if (A.fl == F_ANY) hipLaunchKernelGGL((K<__VA_ARGS__, F_ANY>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A); \
+  else hipLaunchKernelGGL((K<__VA_ARGS__, F_GENERAL>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);      \
+  return hipGetLastError();
 
-// the 3x3x3 and child convolutions: (C, C) layers, and (2C, C) for the
-// ResBlock's first convolution on [F | G]
-template <int MODE>
-static hipError_t launch_gemm_cx(int cin, int cout, const GemmSeg* segs, const Tile* tiles, int ntiles,
-                                 const GemmArg& A, int rb, hipStream_t s) {
-#define LPCC_C(CI, CO)                                                                                    \
-  if (cin == CI && cout == CO) {                                                                          \
-    if (rb == 4)                                                                                          \
-      hipLaunchKernelGGL((k_gemm_cx<MODE, CI, CO, 4>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);    \
-    else if (rb == 2)                                                                                     \
-      hipLaunchKernelGGL((k_gemm_cx<MODE, CI, CO, 2>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);    \
-    else                                                                                                  \
-      hipLaunchKernelGGL((k_gemm_cx<MODE, CI, CO, 1>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);    \
-    return hipGetLastError();                                                                             \
+hipError_t launch_conv(int cin, int cout, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, int rb,
+                       hipStream_t s) {
+  if (ntiles <= 0) return hipSuccess;
+#define LPCC_C(CI, CO)                                                     \
+  if (cin == CI && cout == CO) {                                           \
+    if (rb == 4) { LPCC_FL(k_conv, G_CONV, CI, CO, 4) }                    \
+    if (rb == 2) { LPCC_FL(k_conv, G_CONV, CI, CO, 2) }                    \
+    LPCC_FL(k_conv, G_CONV, CI, CO, 1)                                     \
   }
   LPCC_C(16, 16) LPCC_C(32, 16) LPCC_C(32, 32) LPCC_C(64, 32) LPCC_C(64, 64) LPCC_C(128, 64)
 #undef LPCC_C
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_dense(int mode, int cin, int cout, const GemmSeg* segs, const Tile* tiles, int ntiles,
-                             const GemmArg& A, int rb, hipStream_t s) {
+hipError_t launch_conv_split(int cin, int cout, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A,
+                             int rb, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (mode == G_CONV) return launch_gemm_mode<G_CONV>(cin, cout, segs, tiles, ntiles, A, rb, s);
-  if (mode == G_DENSE) return launch_gemm_mode<G_DENSE>(cin, cout, segs, tiles, ntiles, A, rb, s);
-  if (mode == G_DOWN) return launch_gemm_mode<G_DOWN>(cin, cout, segs, tiles, ntiles, A, rb, s);
+#define LPCC_C(CI, CO)                                                     \
+  if (cin == CI && cout == CO) {                                           \
+    if (rb == 4) { LPCC_FL(k_conv_split, CI, CO, 4) }                      \
+    if (rb == 2) { LPCC_FL(k_conv_split, CI, CO, 2) }                      \
+    LPCC_FL(k_conv_split, CI, CO, 1)                                       \
+  }
+  LPCC_C(16, 16) LPCC_C(32, 16) LPCC_C(32, 32) LPCC_C(64, 32) LPCC_C(64, 64) LPCC_C(128, 64)
+#undef LPCC_C
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm(int mode, int cin, int cout, const GemmSeg* segs, const Tile* tiles, int ntiles,
-                       const GemmArg& A, int rb, hipStream_t s) {
+hipError_t launch_dense(int cin, int cout, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A,
+                        int rb, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (mode == G_CONV) return launch_gemm_cx<G_CONV>(cin, cout, segs, tiles, ntiles, A, rb, s);
-  if (mode == G_DENSE) return launch_gemm_mode<G_DENSE>(cin, cout, segs, tiles, ntiles, A, rb, s);
-  if (mode == G_DOWN) return launch_gemm_cx<G_DOWN>(cin, cout, segs, tiles, ntiles, A, rb, s);
+  // a dense layer's zero point is in its bias
+#define LPCC_C(CI, CO, R)                                                                                       \
+  if (cin == CI && cout == CO && rb == R) {                                                                     \
+    if (A.fl == F_FAST)                                                                                         \
+      hipLaunchKernelGGL((k_conv<G_DENSE, CI, CO, R, F_FAST>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);  \
+    else                                                                                                        \
+      hipLaunchKernelGGL((k_conv<G_DENSE, CI, CO, R, F_GENERAL>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A); \
+    return hipGetLastError();                                                                                   \
+  }
+  LPCC_C(32, 16, 1) LPCC_C(32, 16, 2) LPCC_C(32, 16, 4) LPCC_C(64, 32, 1) LPCC_C(64, 32, 2) LPCC_C(64, 32, 4)
+  LPCC_C(128, 64, 1) LPCC_C(128, 64, 2) LPCC_C(128, 64, 4)
+#undef LPCC_C
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_down(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, int tpw,
+                       hipStream_t s) {
+  if (ntiles <= 0) return hipSuccess;
+#define LPCC_D(CC, TT) \
+  if (C == CC && tpw == TT) { LPCC_FL(k_down, CC, TT) }
+  LPCC_D(16, 1) LPCC_D(16, kDownTiles) LPCC_D(32, 1) LPCC_D(32, kDownTiles) LPCC_D(64, 1) LPCC_D(64, kDownTiles)
+#undef LPCC_D
   return hipErrorInvalidValue;
 }
 
@@ -676,12 +626,20 @@ hipError_t launch_gemm(int mode, int cin, int cout, const GemmSeg* segs, const T
 // out block o (columns oC..oC+C-1) is child slot o; occupied slots only,
 // child row = cstart[p] + rank of o among the set bits.
 //
-// The product is formed transposed (weights as the MFMA row operand,
-// parents as columns), so that every lane ends with four consecutive output
-// channels of one parent: it requantises them and writes one 32-bit word of
-// the child row directly, with no staging of the accumulators.
+// Two forms: every slot of every parent (small launches), and the occupied
+// children only.
 // ---------------------------------------------------------------------------
-template <int C, int RB>
+__device__ __forceinline__ v4i occupancy(uint32_t code) {  // bits as int8 {0, 127}
+  uint32_t w0 = 0, w1 = 0;
+#pragma unroll
+  for (int b = 0; b < 4; b++) {
+    if ((code >> b) & 1u) w0 |= 127u << (8 * b);
+    if ((code >> (b + 4)) & 1u) w1 |= 127u << (8 * b);
+  }
+  return v4i{(int)w0, (int)w1, 0, 0};
+}
+
+template <int C, int RB, int FL>
 __global__ __launch_bounds__(256) void k_up(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
                                             const GemmArg A) {
   constexpr int KS = (C + 8 + 63) / 64;
@@ -717,29 +675,20 @@ __global__ __launch_bounds__(256) void k_up(const GemmSeg* __restrict__ segs, co
       const int k0 = 64 * s + 16 * g;
       a[rb][s] = v4i{0, 0, 0, 0};
       if (rv && k0 < C) {
-        a[rb][s] = ld16(S.in + (int64_t)row * S.in_stride + k0);
+        a[rb][s] = ld16(S.in + (int64_t)row * C + k0);
       } else if (rv && k0 == C) {  // occupancy bits as int8 {0,127}, then zeros
-        uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-        for (int b = 0; b < 4; b++) {
-          if ((code[rb] >> b) & 1u) w0 |= 127u << (8 * b);
-          if ((code[rb] >> (b + 4)) & 1u) w1 |= 127u << (8 * b);
-        }
-        a[rb][s] = v4i{(int)w0, (int)w1, 0, 0};
+        a[rb][s] = occupancy(code[rb]);
       }
     }
   }
   const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  const GAS v4i* Bp = (const GAS v4i*)L.bias;
-  // weights and biases of slot o+1 are in flight while slot o is computed;
-  // lane (r, g) holds the bias of channels 16 nb + 4g .. +3
+  // weights and biases of slot o+1 are in flight while slot o is computed
   v4i wb[2][KS][NBS], bb[2][NBS];
 #pragma unroll
   for (int s = 0; s < KS; s++)
 #pragma unroll
     for (int nb = 0; nb < NBS; nb++) wb[0][s][nb] = Wp[((int64_t)s * NBT + nb) * 64 + lane];
-#pragma unroll
-  for (int nb = 0; nb < NBS; nb++) bb[0][nb] = Bp[(16 * nb + 4 * g) / 4];
+  acc_bias<C>(bb[0], L.bias, g);
 
 #pragma unroll
   for (int o = 0; o < 8; o++) {
@@ -749,8 +698,7 @@ __global__ __launch_bounds__(256) void k_up(const GemmSeg* __restrict__ segs, co
 #pragma unroll
         for (int nb = 0; nb < NBS; nb++)
           wb[(o + 1) & 1][s][nb] = Wp[((int64_t)s * NBT + (o + 1) * NBS + nb) * 64 + lane];
-#pragma unroll
-      for (int nb = 0; nb < NBS; nb++) bb[(o + 1) & 1][nb] = Bp[((o + 1) * C + 16 * nb + 4 * g) / 4];
+      acc_bias<C>(bb[(o + 1) & 1], L.bias + (o + 1) * C, g);
     }
 #pragma unroll
     for (int rb = 0; rb < RB; rb++) {
@@ -758,7 +706,7 @@ __global__ __launch_bounds__(256) void k_up(const GemmSeg* __restrict__ segs, co
       if (__ballot(has) == 0ull) continue;  // no parent of the block has child o
       v4i acc[NBS];
 #pragma unroll
-      for (int nb = 0; nb < NBS; nb++) acc[nb] = v4i{0, 0, 0, 0};
+      for (int nb = 0; nb < NBS; nb++) acc[nb] = bb[o & 1][nb];
 #pragma unroll
       for (int s = 0; s < KS; s++)
 #pragma unroll
@@ -766,148 +714,9 @@ __global__ __launch_bounds__(256) void k_up(const GemmSeg* __restrict__ segs, co
       if (!has) continue;
       const int crow = first[rb] + __popc(code[rb] & ((1u << o) - 1u));
       if (crow >= S.child_rows) continue;  // only for a corrupt stream
-      GAS uint32_t* dst = (GAS uint32_t*)(gp(S.out) + (int64_t)crow * S.out_stride + 4 * g);
-#pragma unroll
-      for (int nb = 0; nb < NBS; nb++) {
-        uint32_t packed = 0;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const int y = requant_l(acc[nb][i] + bb[o & 1][nb][i], L);
-          packed |= ((uint32_t)y & 0xFFu) << (8 * i);
-        }
-        dst[4 * nb] = packed;
-      }
-    }
-  }
-}
-
-// Staged variant for C = 64: the accumulators of a slot go through LDS and
-// only the occupied (parent, slot) outputs are requantised, RPP child rows
-// per pass.  At the sparse depths most slots hold few children, and this
-// compaction saves more requantisation work than the staging costs; at
-// C <= 32 the direct form above is faster.
-template <int C, int RB>
-__global__ __launch_bounds__(256) void k_up_staged(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
-                                            const GemmArg A) {
-  constexpr int KS = (C + 8 + 63) / 64;
-  constexpr int NBS = C / 16;          // column blocks per child slot
-  constexpr int NBT = 8 * NBS;         // column blocks of the layer
-  constexpr int WR = 16 * RB;          // parent rows per wave
-  // per wave: the accumulator tile of one slot, and the parents' codes / first children
-  __shared__ int32_t st[4][16][C + 1];
-  __shared__ uint32_t pc[4][WR];
-  __shared__ int32_t ps[4][WR];
-
-  GemmSeg S;
-  LayerDev L;
-  const int tile_row0 = pick_seg(segs, tiles, A, S, L, 4 * WR);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = lane & 15, g = lane >> 4;
-  const int wrow0 = tile_row0 + wave * WR;
-  uint32_t code[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-    const int row = wrow0 + 16 * rb + r;
-    code[rb] = row < S.rows ? gp(S.code)[row] : 0u;
-    if (g == 0) {
-      pc[wave][16 * rb + r] = code[rb];
-      ps[wave][16 * rb + r] = row < S.rows ? gp(S.cstart)[row] : 0;
-    }
-  }
-  // output: 4 consecutive columns per lane, C/4 lanes per child row
-  static_assert(C % 4 == 0 && 64 % (C / 4) == 0, "C");
-  constexpr int LPR = C / 4, RPP = 64 / LPR;
-  const int jl = lane / LPR, c4 = (lane % LPR) * 4;
-  int bia[8][4];
-#pragma unroll
-  for (int o = 0; o < 8; o++)
-#pragma unroll
-    for (int q = 0; q < 4; q++) bia[o][q] = gp(L.bias)[o * C + c4 + q];
-
-  v4i a[RB][KS];
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-    const int row = wrow0 + 16 * rb + r;
-    const bool rv = row < S.rows;
-#pragma unroll
-    for (int s = 0; s < KS; s++) {
-      const int k0 = 64 * s + 16 * g;
-      a[rb][s] = v4i{0, 0, 0, 0};
-      if (rv && k0 < C) {
-        a[rb][s] = ld16(S.in + (int64_t)row * S.in_stride + k0);
-      } else if (rv && k0 == C) {  // occupancy bits as int8 {0,127}, then zeros
-        uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-        for (int b = 0; b < 4; b++) {
-          if ((code[rb] >> b) & 1u) w0 |= 127u << (8 * b);
-          if ((code[rb] >> (b + 4)) & 1u) w1 |= 127u << (8 * b);
-        }
-        a[rb][s] = v4i{(int)w0, (int)w1, 0, 0};
-      }
-    }
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  // weights of slot o+1 are in flight while slot o is computed
-  v4i wb[2][KS][NBS];
-#pragma unroll
-  for (int s = 0; s < KS; s++)
-#pragma unroll
-    for (int nb = 0; nb < NBS; nb++) wb[0][s][nb] = Wp[((int64_t)s * NBT + nb) * 64 + lane];
-
-#pragma unroll
-  for (int o = 0; o < 8; o++) {
-    if (o + 1 < 8) {
-#pragma unroll
-      for (int s = 0; s < KS; s++)
-#pragma unroll
-        for (int nb = 0; nb < NBS; nb++)
-          wb[(o + 1) & 1][s][nb] = Wp[((int64_t)s * NBT + (o + 1) * NBS + nb) * 64 + lane];
-    }
-#pragma unroll
-    for (int rb = 0; rb < RB; rb++) {
-      // rows of this block whose parent has child slot o (wave-uniform)
-      const uint32_t m = (uint32_t)(__ballot((code[rb] >> o) & 1u) & 0xFFFFull);
-      if (m == 0u) continue;
-      v4i acc[NBS];
-#pragma unroll
-      for (int nb = 0; nb < NBS; nb++) acc[nb] = v4i{0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < KS; s++)
-#pragma unroll
-        for (int nb = 0; nb < NBS; nb++) acc[nb] = mfma16(a[rb][s], wb[o & 1][s][nb], acc[nb]);
-#pragma unroll
-      for (int nb = 0; nb < NBS; nb++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) st[wave][4 * g + i][16 * nb + r] = acc[nb][i];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // only the occupied (row, slot) outputs: k rows of C columns, RPP rows
-      // per pass, 4 columns (one 32-bit store) per lane
-      const int k = __popc(m);
-      for (int j = jl; j < k; j += RPP) {
-        // row of the j-th set bit of m
-        int pos = 0;
-#pragma unroll
-        for (int w = 8; w >= 1; w >>= 1)
-          if (__popc(m & ((1u << (pos + w)) - 1u)) <= j) pos += w;
-        const uint32_t pcode = pc[wave][16 * rb + pos];
-        const int crow = ps[wave][16 * rb + pos] + __popc(pcode & ((1u << o) - 1u));
-        if (crow >= S.child_rows) continue;  // only for a corrupt stream
-        uint32_t packed = 0;
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const int y = requant_l(st[wave][pos][c4 + q] + bia[o][q], L);
-          packed |= ((uint32_t)y & 0xFFu) << (8 * q);
-        }
-        *(GAS uint32_t*)(gp(S.out) + (int64_t)crow * S.out_stride + c4) = packed;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      typedef typename RowPart<C>::T P;
+      P none;
+      *(GAS P*)(gp(S.out) + (int64_t)crow * C + C / 4 * g) = row_out<C, FL, true>(acc, L, false, none);
     }
   }
 }
@@ -916,18 +725,17 @@ __global__ __launch_bounds__(256) void k_up_staged(const GemmSeg* __restrict__ s
 // (128 or 512) consecutive parents and compacts them, per child slot o, into a
 // list of the parents that have child o (wave ballot and prefix count, then
 // the per-wave totals: the list keeps parent order).  The lists are cut into
-// groups of 16 entries; a wave computes one group with one MFMA column block
-// per 16 output channels: the weights of slot o as the row operand, the 16
-// parents' inputs [Z | bits(X)] as the columns, so that every lane ends with
-// four consecutive output channels of one child and writes them as one word.
-// Only the last group of each slot is partly empty.  Groups are dealt to the
-// waves in slot order, so a wave keeps a slot's weights across its groups.
+// groups of 16 entries; a wave computes one group: the weights of slot o as
+// the row operand, the 16 parents' inputs [Z | bits(X)] as the columns, and a
+// lane writes its C/4 channels of one child row.  Only the last group of each
+// slot is partly empty.  Groups are dealt to the waves in slot order, so a wave
+// keeps a slot's weights across its groups.
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {  // set bits of m below this lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-template <int C, int P>
+template <int C, int P, int FL>
 __global__ __launch_bounds__(256) void k_up_cx(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
                                                const GemmArg A) {
   constexpr int KS = (C + 8 + 63) / 64;
@@ -940,8 +748,6 @@ __global__ __launch_bounds__(256) void k_up_cx(const GemmSeg* __restrict__ segs,
   __shared__ uint32_t wtot[8][4 * PPT];
   __shared__ uint32_t cnt[8];
   __shared__ uint32_t goff[9];
-  __shared__ uint32_t ost[4][16][C / 4 + 4];  // output stage of every wave (16 rows)
-  __shared__ int32_t ocrow[4][16];
 
   GemmSeg S;
   LayerDev L;
@@ -994,7 +800,6 @@ __global__ __launch_bounds__(256) void k_up_cx(const GemmSeg* __restrict__ segs,
   __syncthreads();
 
   const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  const GAS v4i* Bp = (const GAS v4i*)L.bias;
   const int G = (int)goff[8];
   // wave w takes the contiguous groups [G w / 4, G (w + 1) / 4)
   const int gb = (G * wave) / 4, ge = (G * (wave + 1)) / 4;
@@ -1022,15 +827,9 @@ __global__ __launch_bounds__(256) void k_up_cx(const GemmSeg* __restrict__ segs,
       const int k0 = 64 * s + 16 * g;
       x.a[s] = v4i{0, 0, 0, 0};
       if (x.ev && k0 < C) {
-        x.a[s] = ld16(S.in + (int64_t)x.p * S.in_stride + k0);
+        x.a[s] = ld16(S.in + (int64_t)x.p * C + k0);
       } else if (x.ev && k0 == C) {  // occupancy bits as int8 {0,127}, then zeros
-        uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-        for (int b = 0; b < 4; b++) {
-          if ((x.pc >> b) & 1u) w0 |= 127u << (8 * b);
-          if ((x.pc >> (b + 4)) & 1u) w1 |= 127u << (8 * b);
-        }
-        x.a[s] = v4i{(int)w0, (int)w1, 0, 0};
+        x.a[s] = occupancy(x.pc);
       }
     }
     x.first = x.ev ? gp(S.cstart)[x.p] : 0;
@@ -1051,244 +850,35 @@ __global__ __launch_bounds__(256) void k_up_cx(const GemmSeg* __restrict__ segs,
       for (int s = 0; s < KS; s++)
 #pragma unroll
         for (int nb = 0; nb < NBS; nb++) wb[s][nb] = Wp[((int64_t)s * NBT + o * NBS + nb) * 64 + lane];
-#pragma unroll
-      for (int nb = 0; nb < NBS; nb++) bb[nb] = Bp[(o * C + 16 * nb + 4 * g) / 4];
+      acc_bias<C>(bb, L.bias + o * C, g);
     }
     if (gi + 1 < ge) fetch(gi + 1, nx);
-    const bool ev = x.ev;
-    const int p = x.p;
-    const uint32_t pc = x.pc;
-    const int first = x.first;
-    (void)p;
     v4i acc[NBS];
 #pragma unroll
-    for (int nb = 0; nb < NBS; nb++) acc[nb] = v4i{0, 0, 0, 0};
+    for (int nb = 0; nb < NBS; nb++) acc[nb] = bb[nb];
 #pragma unroll
     for (int s = 0; s < KS; s++)
 #pragma unroll
       for (int nb = 0; nb < NBS; nb++) acc[nb] = mfma16(wb[s][nb], x.a[s], acc[nb]);
-    // the group's 16 child rows go through the wave's LDS stage, so that
-    // every row leaves as whole 16-byte stores (lane (r, g) holds channels
-    // 16 nb + 4 g .. + 3 of column r)
-    int crow = ev ? first + __popc(pc & ((1u << o) - 1u)) : -1;
-    if (crow >= S.child_rows) crow = -1;  // only for a corrupt stream
-    if (g == 0) ocrow[wave][r] = crow;
-#pragma unroll
-    for (int nb = 0; nb < NBS; nb++) {
-      uint32_t packed = 0;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int y = requant_l(acc[nb][i] + bb[nb][i], L);
-        packed |= ((uint32_t)y & 0xFFu) << (8 * i);
-      }
-      ost[wave][r][4 * nb + g] = packed;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane < 16 * NBS) {
-      const int row = lane / NBS, part = lane % NBS;
-      const int cr = ocrow[wave][row];
-      if (cr >= 0) {
-        const uint32_t* w = &ost[wave][row][4 * part];
-        *(GAS v4i*)(gp(S.out) + (int64_t)cr * S.out_stride + 16 * part) =
-            v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
-
-// Child convolution (the stride-2 step of the re-densification, Eq. 4) over
-// the occupied children only: out[q] = rq(b + sum over children c of q of
-// in[c] W[slot(c)]).  A block takes P (64 or 128) consecutive parents, compacts
-// them per child slot as the upsampling does, and multiplies 16-entry groups
-// of one slot (the slot's weights as the row operand, the 16 children's
-// input rows as the columns).  Each lane then holds four consecutive output
-// channels of one child's contribution and adds them into its parent's
-// int32 accumulator row in LDS (a parent with several children collects one
-// contribution per slot; integer adds, so the order does not matter).  The
-// accumulators are requantised once all groups are done.  With `ccode` set,
-// child c reads row ccode[c] of `in`: the occupancy embedding of depth j
-// depends on the code alone, so the first step reads a 256-row table.
-template <int C, int P>
-__global__ __launch_bounds__(256) void k_down_cx(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
-                                                 const GemmArg A) {
-  constexpr int NB = C / 16;
-  constexpr int KS = (C + 63) / 64;
-  static_assert(C % 16 == 0 && P <= 256 && P % 64 == 0, "shape");
-  __shared__ int32_t accs[P][C + 1];
-  __shared__ uint8_t list[8][P];
-  __shared__ uint8_t pcode[P];
-  __shared__ int32_t pfirst[P];
-  __shared__ uint32_t wtot[8][P / 64];
-  __shared__ uint32_t cnt[8];
-  __shared__ uint32_t goff[9];
-
-  GemmSeg S;
-  LayerDev L;
-  const int q0 = pick_seg(segs, tiles, A, S, L, P);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = lane & 15, g = lane >> 4;
-
-  for (int k = threadIdx.x; k < P * (C + 1); k += 256) (&accs[0][0])[k] = 0;
-  uint32_t code = 0u, rk[8];
-  if ((int)threadIdx.x < P) {
-    const int q = q0 + (int)threadIdx.x;
-    code = q < S.rows ? ((uint32_t)gp(S.code)[q] & 0xFFu) : 0u;
-    pcode[threadIdx.x] = (uint8_t)code;
-    pfirst[threadIdx.x] = q < S.rows ? gp(S.cstart)[q] : 0;
-#pragma unroll
-    for (int o = 0; o < 8; o++) {
-      const uint64_t m = __ballot((code >> o) & 1u);
-      rk[o] = lanes_below(m);
-      if (lane == 0) wtot[o][wave] = (uint32_t)__popcll(m);
+    const int crow = x.first + __popc(x.pc & ((1u << o) - 1u));
+    if (x.ev && crow < S.child_rows) {  // past the depth only for a corrupt stream
+      typedef typename RowPart<C>::T T;
+      T none;
+      *(GAS T*)(gp(S.out) + (int64_t)crow * C + C / 4 * g) = row_out<C, FL, true>(acc, L, false, none);
     }
   }
-  __syncthreads();
-  if ((int)threadIdx.x < P) {
-#pragma unroll
-    for (int o = 0; o < 8; o++) {
-      if (!((code >> o) & 1u)) continue;
-      uint32_t before = rk[o];
-      for (int w = 0; w < wave; w++) before += wtot[o][w];
-      list[o][before] = (uint8_t)threadIdx.x;
-    }
-  }
-  if (threadIdx.x < 8) {
-    uint32_t n = 0;
-    for (int w = 0; w < P / 64; w++) n += wtot[threadIdx.x][w];
-    cnt[threadIdx.x] = n;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t gsum = 0;
-    for (int o = 0; o < 8; o++) {
-      goff[o] = gsum;
-      gsum += (cnt[o] + 15) / 16;
-    }
-    goff[8] = gsum;
-  }
-  __syncthreads();
-
-  const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  const int G = (int)goff[8];
-  const int gb = (G * wave) / 4, ge = (G * (wave + 1)) / 4;
-  // operands of group gi: its slot, the column's parent and child, the
-  // child's input slice (fetched one group ahead of the MFMAs)
-  struct Op {
-    int o, t;
-    bool cv;
-    v4i a[KS];
-  };
-  auto fetch = [&](int gi, Op& x) {
-    int o = 0;
-#pragma unroll
-    for (int q = 1; q < 8; q++) o += gi >= (int)goff[q] ? 1 : 0;
-    const int e = 16 * (gi - (int)goff[o]) + r;  // entry of column r
-    const bool ev = e < (int)cnt[o];
-    const int t = ev ? (int)list[o][e] : 0;
-    const uint32_t pc = pcode[t];
-    const int c = pfirst[t] + __popc(pc & ((1u << o) - 1u));
-    x.o = o;
-    x.t = t;
-    x.cv = ev && c < S.child_rows;  // out of range only for a corrupt stream
-    const int64_t src = !x.cv ? 0 : (S.ccode != nullptr ? (int64_t)gp(S.ccode)[c] : (int64_t)c);
-#pragma unroll
-    for (int s = 0; s < KS; s++) {
-      const int k0 = 64 * s + 16 * g;
-      x.a[s] = v4i{0, 0, 0, 0};
-      if (x.cv && k0 < C) x.a[s] = ld16(S.in + src * S.in_stride + k0);
-    }
-  };
-  int cur = -1;
-  v4i wb[KS][NB];
-  Op nx;
-  if (gb < ge) fetch(gb, nx);
-  for (int gi = gb; gi < ge; gi++) {
-    const Op x = nx;
-    const int o = x.o;
-    // the slot's weights (rows k = o C + c of the packed layout), requested
-    // before the next group's operands so that waiting for them leaves the
-    // prefetch in flight (the memory counter drains in order)
-    if (o != cur) {
-      cur = o;
-#pragma unroll
-      for (int s = 0; s < KS; s++) {
-        const bool kv = 64 * s + 16 * g < C;
-        const int ko = kv ? o * C + 64 * s + 16 * g : 0;
-        const GAS v4i* w = Wp + (int64_t)(ko >> 6) * NB * 64 + ((ko >> 4) & 3) * 16 + r;
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++) {
-          const v4i y = w[kv ? nb * 64 : 0];
-          wb[s][nb] = kv ? y : v4i{0, 0, 0, 0};
-        }
-      }
-    }
-    if (gi + 1 < ge) fetch(gi + 1, nx);
-    const int t = x.t;
-    const bool cv = x.cv;
-    v4i acc[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++) acc[nb] = v4i{0, 0, 0, 0};
-#pragma unroll
-    for (int s = 0; s < KS; s++)
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++) acc[nb] = mfma16(wb[s][nb], x.a[s], acc[nb]);
-    if (!cv) continue;
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) atomicAdd(&accs[t][16 * nb + 4 * g + i], acc[nb][i]);
-  }
-  __syncthreads();
-
-  // requantise: thread (row, 4-channel group), rows in steps of 256 / (C / 4)
-  constexpr int LPR = C / 4;
-  const int c4 = (threadIdx.x % LPR) * 4;
-  int bia[4];
-#pragma unroll
-  for (int q = 0; q < 4; q++) bia[q] = gp(L.bias)[c4 + q];
-  for (int t = threadIdx.x / LPR; t < P; t += 256 / LPR) {
-    const int q = q0 + t;
-    if (q >= S.rows) break;
-    const uint32_t pc = pcode[t];
-    uint32_t packed = 0;
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-      int a = accs[t][c4 + k] + bia[k];
-      if (L.zc != nullptr) {
-        for (int o = 0; o < 8; o++)
-          if ((pc >> o) & 1u) a += gp(L.zc)[o * L.npad + c4 + k];
-      }
-      packed |= ((uint32_t)requant_l(a, L) & 0xFFu) << (8 * k);
-    }
-    *(GAS uint32_t*)(gp(S.out) + (int64_t)q * S.out_stride + c4) = packed;
-  }
-}
-
-hipError_t launch_down_cx(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, int P,
-                          hipStream_t s) {
-  if (ntiles <= 0) return hipSuccess;
-#define LPCC_D(CC, PP)                                                                                 \
-  if (C == CC && P == PP) {                                                                            \
-    hipLaunchKernelGGL((k_down_cx<CC, PP>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);            \
-    return hipGetLastError();                                                                          \
-  }
-  LPCC_D(16, 64) LPCC_D(16, 128) LPCC_D(32, 64) LPCC_D(32, 128) LPCC_D(64, 64) LPCC_D(64, 128)
-#undef LPCC_D
-  return hipErrorInvalidValue;
 }
 
 hipError_t launch_up_cx(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, int P,
                         hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-#define LPCC_U(CC, PP)                                                                                 \
-  if (C == CC && P == PP) {                                                                            \
-    hipLaunchKernelGGL((k_up_cx<CC, PP>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);              \
-    return hipGetLastError();                                                                          \
+#define LPCC_U(CC, PP)                                                                                        \
+  if (C == CC && P == PP) {                                                                                   \
+    if (A.fl == F_FAST)                                                                                       \
+      hipLaunchKernelGGL((k_up_cx<CC, PP, F_FAST>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);           \
+    else                                                                                                      \
+      hipLaunchKernelGGL((k_up_cx<CC, PP, F_GENERAL>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);        \
+    return hipGetLastError();                                                                                 \
   }
   LPCC_U(16, 128) LPCC_U(16, 512) LPCC_U(32, 128) LPCC_U(32, 512) LPCC_U(64, 128) LPCC_U(64, 512)
 #undef LPCC_U
@@ -1298,21 +888,17 @@ hipError_t launch_up_cx(int C, const GemmSeg* segs, const Tile* tiles, int ntile
 hipError_t launch_up(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, int rb,
                      hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-#define LPCC_U(CC)                                                                                 \
-  if (C == CC) {                                                                                   \
-    if (rb == 4) hipLaunchKernelGGL((k_up<CC, 4>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A); \
-    else if (rb == 2) hipLaunchKernelGGL((k_up<CC, 2>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A); \
-    else hipLaunchKernelGGL((k_up<CC, 1>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);         \
-    return hipGetLastError();                                                                      \
+#define LPCC_U(CC, RR)                                                                                        \
+  if (C == CC && rb == RR) {                                                                                  \
+    if (A.fl == F_FAST)                                                                                       \
+      hipLaunchKernelGGL((k_up<CC, RR, F_FAST>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);              \
+    else                                                                                                      \
+      hipLaunchKernelGGL((k_up<CC, RR, F_GENERAL>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);           \
+    return hipGetLastError();                                                                                 \
   }
-  LPCC_U(16) LPCC_U(32)
+  LPCC_U(16, 1) LPCC_U(16, 2) LPCC_U(16, 4) LPCC_U(32, 1) LPCC_U(32, 2) LPCC_U(32, 4)
+  LPCC_U(64, 1) LPCC_U(64, 2) LPCC_U(64, 4)
 #undef LPCC_U
-  if (C == 64) {
-    if (rb == 4) hipLaunchKernelGGL((k_up_staged<64, 4>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);
-    else if (rb == 2) hipLaunchKernelGGL((k_up_staged<64, 2>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);
-    else hipLaunchKernelGGL((k_up_staged<64, 1>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);
-    return hipGetLastError();
-  }
   return hipErrorInvalidValue;
 }
 
@@ -1349,7 +935,7 @@ __global__ __launch_bounds__(256) void k_emb(const GemmSeg* __restrict__ segs, c
     int acc = bias;
 #pragma unroll
     for (int b = 0; b < 8; b++) acc += ((code[k] >> b) & 1u) ? w[b] : 0;
-    gp(S.out)[(int64_t)row * S.out_stride + o] = (int8_t)requant_l(acc, L);
+    gp(S.out)[(int64_t)row * C + o] = (int8_t)requant_l(acc, L);
   }
 }
 
@@ -1458,12 +1044,6 @@ __device__ __forceinline__ uint32_t node_before(uint32_t v, int lane) {
   sum = (uint32_t)a[0] + (uint32_t)a[1];
   a = __builtin_amdgcn_permlane32_swap(sum, sum, false, false);
   return off + ((lane & 32) ? (uint32_t)a[0] : 0u);
-}
-
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Per-node results of the logits, held by each of the node's lanes.

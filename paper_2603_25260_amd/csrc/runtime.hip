@@ -230,27 +230,28 @@ RqBounds requant_bounds(int32_t m_pos, int32_t m_neg, int r, int z) {
   return B;
 }
 
-// requant_f's parameters of a layer whose requant_bounds are set, and whether
-// it computes the same function: one multiplier (identity) or none below zero
-// (ReLU: the accumulator is clamped from below at 0), 24-bit operands, a m +
-// rnd + z 2^r inside int32 on the clamped range, outputs inside int8 at its
-// ends (the function is monotone).
+// requant_f's and requant_p's parameters of a layer whose requant_bounds are
+// set, and which of them computes the same function: one multiplier (identity)
+// or none below zero (ReLU: the accumulator is clamped from below at 0), or two
+// (PReLU); 24-bit operands, a m + rnd + z 2^r inside int32 on the clamped
+// range, outputs inside int8 at its ends (the function is monotone).
 void requant_fast(LayerDev& F) {
   F.rqf = 0;
   F.f_lo = F.m_neg == 0 ? 0 : F.a_lo;
   F.f_hi = F.a_hi;
   F.f_m = F.m_pos;
+  F.f_mn = F.m_neg;
   F.f_rnd = 0;
-  if (F.m_neg != 0 && F.m_neg != F.m_pos) return;
+  const bool single = F.m_neg == 0 || F.m_neg == F.m_pos;
   if (F.r < 0 || F.r > 30) return;
   const int64_t rnd = F.rnd + (int64_t)F.z_out * (1ll << F.r);
   const int64_t top = 1ll << 31, lim = 1ll << 23;
-  const int64_t lo = (int64_t)F.f_lo * F.f_m + rnd, hi = (int64_t)F.f_hi * F.f_m + rnd;
-  if (F.f_m >= lim || F.f_hi >= lim || -(int64_t)F.f_lo > lim) return;
+  const int64_t lo = (int64_t)F.f_lo * F.m_neg + rnd, hi = (int64_t)F.f_hi * F.m_pos + rnd;
+  if (F.f_m >= lim || F.f_mn >= lim || F.f_hi >= lim || -(int64_t)F.f_lo > lim) return;
   if (rnd < -top || rnd >= top || lo < -top || lo >= top || hi < -top || hi >= top) return;
   if ((lo >> F.r) < -128 || (hi >> F.r) > 127) return;
   F.f_rnd = (int32_t)rnd;
-  F.rqf = 1;
+  F.rqf = single ? 1 : 2;
 }
 
 // Frequencies of a base depth from the counts n_s of its 255 codes (the
@@ -277,7 +278,7 @@ void base_cdf(const uint32_t* n, int32_t* cdf) {
 
 struct LayerImage {
   std::vector<int8_t> packed;
-  std::vector<int32_t> bias, zc;
+  std::vector<int32_t> bias, zc, biasz;
   int ksteps, npad;
 };
 
@@ -298,8 +299,11 @@ LayerImage build_image(const HostLayer& L) {
           if (L.kind == K_FC2) {  // the predictor's order of symbols and channels
             const int sy = logit_symbol(nb, lane % 16), ch = logit_channel(lane / 16, i, L.cin);
             if (ch >= 0 && sy < L.cout) v = L.W[(size_t)ch * L.cout + sy];
-          } else if (k < K && col < L.cout) {
+          } else if (k < K && L.kind == K_FC1) {
             v = L.W[(size_t)k * L.cout + col];
+          } else if (k < K) {  // rows in out_channel order, per child slot for the upsampling
+            const int C = L.kind == K_UP ? L.cout / 8 : L.cout, per = C / 16;
+            v = L.W[(size_t)k * L.cout + nb / per * C + out_channel(nb % per, lane % 16, C)];
           }
           im.packed[(((size_t)s * NB + nb) * 64 + lane) * 16 + i] = v;
         }
@@ -322,6 +326,9 @@ LayerImage build_image(const HostLayer& L) {
         for (int c = 0; c < L.cin; c++) cs += L.W[((size_t)t * L.cin + c) * L.cout + o];
         im.zc[(size_t)t * im.npad + o] = (int32_t)(-(int64_t)L.z_in * cs);
       }
+    im.biasz = im.bias;
+    for (int t = 0; t < L.taps; t++)
+      for (int o = 0; o < L.cout; o++) im.biasz[o] += im.zc[(size_t)t * im.npad + o];
   }
   return im;
 }
@@ -642,19 +649,23 @@ int64_t count_tiles(const std::vector<int64_t>& rows, int rows_per_tile = 64) {
 }
 
 // ---- kernel autotuner ----
-// Variant codes: for the 3x3x3 and other GEMM launches rb (1, 2, 4: the
-// compacted gather-GEMM, or the dense one for layers without taps) or
-// 10 + rb (the dense gather-GEMM over all taps); for the child convolution
-// 100 + 1/2 (compacted, tiles of 64 / 128 parents) or 110 + rb (dense); for
-// the upsampling 200 + 1/2 (compacted, tiles of 128 / 512 parents) or
+// Variant codes.  3x3x3 convolution: rb (1, 2, 4: the present taps, rb blocks
+// of 16 rows per wave) or 10 + rb (every tap, shared by a block's four waves,
+// rb blocks of 16 rows per block).  Dense layers: rb.  Child convolution: 101 /
+// 102 (64 / 512 parents per block); 110 + rb are further names of 101.
+// Upsampling: 200 + 1/2 (occupied children, tiles of 128 / 512 parents) or
 // 210 + rb (all child slots of every parent).
 struct Variant {
   int code, tile_rows;
 };
-std::vector<Variant> variants(bool up, int mode) {
+// the codes of a kind, or those the tuner times
+std::vector<Variant> variants(bool up, int mode, bool tuned = false) {
   if (up) return {{201, 128}, {202, 512}, {211, 64}, {212, 128}, {214, 256}};
-  if (mode == G_DOWN) return {{101, 64}, {102, 128}, {111, 64}, {112, 128}, {114, 256}};
-  if (mode == G_CONV) return {{1, 64}, {2, 128}, {4, 256}, {11, 64}, {12, 128}, {14, 256}};
+  if (mode == G_DOWN) {
+    if (tuned) return {{101, 64}, {102, 64 * kDownTiles}};
+    return {{101, 64}, {102, 64 * kDownTiles}, {111, 64}, {112, 64}, {114, 64}};
+  }
+  if (mode == G_CONV) return {{1, 64}, {2, 128}, {4, 256}, {11, 16}, {12, 32}, {14, 64}};
   return {{1, 64}, {2, 128}, {4, 256}};
 }
 // the variant a fixed tiling selects
@@ -665,11 +676,10 @@ Variant fixed_variant(bool up, int mode, int tiling, int64_t rows) {
     if (dense) return {210 + rb, 64 * rb};
     return count_tiles({rows}, 512) >= kSlotTileBlocks ? Variant{202, 512} : Variant{201, 128};
   }
-  if (mode == G_DOWN) {
-    if (dense) return {110 + rb, 64 * rb};
-    return count_tiles({rows}, 128) >= kSlotTileBlocks ? Variant{102, 128} : Variant{101, 64};
-  }
-  if (mode == G_CONV) return {tiling, 64 * rb};
+  if (mode == G_DOWN)
+    return !dense && count_tiles({rows}, 64 * kDownTiles) >= kSlotTileBlocks ? Variant{102, 64 * kDownTiles}
+                                                                            : Variant{101, 64};
+  if (mode == G_CONV) return {tiling, dense ? 16 * rb : 64 * rb};
   return {rb, 64 * rb};
 }
 hipError_t launch_variant(int code, bool up, int mode, int cin, int cout, const GemmSeg* S, const Tile* T, int nt,
@@ -678,12 +688,10 @@ hipError_t launch_variant(int code, bool up, int mode, int cin, int cout, const 
     if (code < 210) return launch_up_cx(cout, S, T, nt, one, code == 201 ? 128 : 512, st);
     return launch_up(cout, S, T, nt, one, code - 210, st);
   }
-  if (mode == G_DOWN) {
-    if (code < 110) return launch_down_cx(cout, S, T, nt, one, code == 101 ? 64 : 128, st);
-    return launch_gemm_dense(mode, cin, cout, S, T, nt, one, code - 110, st);
-  }
-  if (code > 10) return launch_gemm_dense(mode, cin, cout, S, T, nt, one, code - 10, st);
-  return launch_gemm(mode, cin, cout, S, T, nt, one, code, st);
+  if (mode == G_DOWN) return launch_down(cout, S, T, nt, one, code == 102 ? kDownTiles : 1, st);
+  if (mode == G_DENSE) return launch_dense(cin, cout, S, T, nt, one, code, st);
+  if (code > 10) return launch_conv_split(cin, cout, S, T, nt, one, code - 10, st);
+  return launch_conv(cin, cout, S, T, nt, one, code, st);
 }
 
 hipError_t tune_event(lpcc_ctx* c, hipEvent_t* e) {
@@ -836,7 +844,6 @@ const LayerDev* dlayer(const lpcc_model* m, int d, int k) { return m->d_layers +
 GemmSeg seg0() {
   GemmSeg s;
   memset(&s, 0, sizeof(s));
-  s.split = 1 << 30;  // single input unless set
   return s;
 }
 
@@ -924,6 +931,17 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
   std::string f(fam);
   GemmArg one;
   memset(&one, 0, sizeof(one));
+  // the flavour: 2 where a sparse layer has an input zero point or an array
+  // that a convolution gathers from is beyond a buffer descriptor; else 1 where
+  // the 24-bit requantisation serves every layer (requant_p also computes what
+  // requant_f does)
+  bool fast = true, any = false;
+  for (auto& s : segs) {
+    const LayerDev& F = hlayer(m, s.L);
+    fast = fast && (f == "up" ? F.rqf != 0 : F.rqf == 1);
+    any = any || F.zc != nullptr || (mode == G_CONV && f != "up" && (int64_t)s.rows * cout >= (1ll << 31));
+  }
+  one.fl = any ? 2 : (fast ? 1 : 0);
   size_t so = 0;
   if (segs.size() == 1) {  // by value: no descriptor loads in the kernel
     one.seg = segs[0];
@@ -945,7 +963,7 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
   lpcc_ctx* c = b.ctx;
   const bool up = f == "up";
   lpcc_ctx::TuneRec* rec = nullptr;
-  const std::vector<Variant> all = variants(up, mode);
+  const std::vector<Variant> all = variants(up, mode), timed_ones = variants(up, mode, true);
   std::vector<Variant> cands;
   auto of_code = [&](int code) {
     for (const Variant& v : all)
@@ -962,9 +980,9 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
     if (rec->best) {
       cands = {of_code(rec->best)};
     } else {
-      cands = all;
-      rec->ncand = (int)all.size();
-      for (size_t k = 0; k < all.size(); k++) rec->cand[k] = all[k].code;
+      cands = timed_ones;
+      rec->ncand = (int)cands.size();
+      for (size_t k = 0; k < cands.size(); k++) rec->cand[k] = cands[k].code;
     }
   }
   std::vector<std::pair<int, size_t>> plan;  // (variant code, tile offset)
@@ -1017,26 +1035,22 @@ void plan_shallow_convs(Batch& b, const lpcc_model* m, const Levels& lv, const F
     e.code = lv.code[j];
     e.L = dlayer(m, d, li++);
     e.out = B.E;
-    e.out_stride = C;
     e.rows = rows;
     plan_gemm(b, m, "emb", 0, 8, C, {e}, st);
     x = B.E;
   }
   GemmSeg s = seg0();
   s.in = x;
-  s.in_stride = C;
   s.kmap = B.kmap[j];
   s.kstride = fr.tot[j];
   s.L = dlayer(m, d, li);
   s.out = B.h;
-  s.out_stride = C;
   s.rows = rows;
   plan_gemm(b, m, "conv", G_CONV, C, C, {s}, st);
   s.in = B.h;
   s.L = dlayer(m, d, li + 1);
   s.out = B.S;
   s.resid = x;
-  s.resid_stride = C;
   plan_gemm(b, m, "conv", G_CONV, C, C, {s}, st);
 }
 
@@ -1048,12 +1062,10 @@ void plan_shallow_up(Batch& b, const lpcc_model* m, const Levels& lv, const Fram
   const int rows = (int)fr.tot[j];
   GemmSeg u = seg0();
   u.in = B.S;
-  u.in_stride = C;
   u.code = lv.code[j];
   u.cstart = lv.cstart[j];
   u.L = dlayer(m, d, m->xfp ? 2 : 3);
   u.out = B.F[d];
-  u.out_stride = C;
   u.rows = rows;
   u.child_rows = (int)fr.tot[d];
   plan_gemm(b, m, "up", 0, C, C, {u}, st);
@@ -1105,10 +1117,7 @@ void plan_deep(Batch& b, const lpcc_model* m, const Levels& lv, const Frames& fr
                const std::vector<int>& dset, hipStream_t st, int part = 0) {
   if (dset.empty()) return;
   const int C = m->C, k0 = m->k0;
-  auto Gout = [&](int d, int j) -> std::pair<int8_t*, int64_t> {  // destination of depth-j G of target d
-    if (j == k0) return {B.Gk[d], C};
-    return {B.G[d][j], C};
-  };
+  auto Gout = [&](int d, int j) { return j == k0 ? B.Gk[d] : B.G[d][j]; };  // destination of depth-j G of target d
   if (part != 2) {
   // occupancy embedding at depth d-1
   {
@@ -1118,9 +1127,7 @@ void plan_deep(Batch& b, const lpcc_model* m, const Levels& lv, const Frames& fr
       const bool table = d - 1 > k0;  // every code's embedding (code = row)
       s.code = table ? nullptr : lv.code[d - 1];
       s.L = dlayer(m, d, 0);
-      auto o = Gout(d, d - 1);
-      s.out = o.first;
-      s.out_stride = o.second;
+      s.out = Gout(d, d - 1);
       s.rows = table ? 256 : (int)fr.tot[d - 1];
       v.push_back(s);
     }
@@ -1136,14 +1143,11 @@ void plan_deep(Batch& b, const lpcc_model* m, const Levels& lv, const Frames& fr
       if (j <= k0) continue;
       GemmSeg s = seg0();
       s.in = B.G[d][j];
-      s.in_stride = C;
       if (j == d - 1) s.ccode = lv.code[j];  // the embedding table, indexed by the child's code
       s.code = lv.code[j - 1];
       s.cstart = lv.cstart[j - 1];
       s.L = dlayer(m, d, t);
-      auto o = Gout(d, j - 1);
-      s.out = o.first;
-      s.out_stride = o.second;
+      s.out = Gout(d, j - 1);
       s.rows = (int)fr.tot[j - 1];
       s.child_rows = (int)fr.tot[j];
       v.push_back(s);
@@ -1161,42 +1165,30 @@ void plan_deep(Batch& b, const lpcc_model* m, const Levels& lv, const Frames& fr
     GemmSeg s = seg0();
     if (xfp) {
       s.in = B.F[k0];  // [F_k0 | G] without materialising the concatenation
-      s.in_stride = C;
       s.in2 = B.Gk[d];
-      s.in2_stride = C;
-      s.split = C;
     } else {
       s.in = B.Gk[d];
-      s.in_stride = C;
     }
     s.kmap = B.kmap[k0];
     s.kstride = fr.tot[k0];
     s.L = dlayer(m, d, base);
     s.out = B.dh[d];
-    s.out_stride = C;
     s.rows = (int)fr.tot[k0];
     c1.push_back(s);
     GemmSeg k = seg0();
     k.in = B.F[k0];
-    k.in_stride = C;
     k.in2 = B.Gk[d];
-    k.in2_stride = C;
-    k.split = C;
     k.L = dlayer(m, d, base + 2);
     k.out = B.ds[d];
-    k.out_stride = C;
     k.rows = (int)fr.tot[k0];
     sk.push_back(k);
     GemmSeg s2 = seg0();
     s2.in = B.dh[d];
-    s2.in_stride = C;
     s2.kmap = B.kmap[k0];
     s2.kstride = fr.tot[k0];
     s2.L = dlayer(m, d, base + 1);
     s2.out = B.Z[d][k0];
-    s2.out_stride = C;
     s2.resid = xfp ? B.ds[d] : B.Gk[d];
-    s2.resid_stride = C;
     s2.rows = (int)fr.tot[k0];
     c2.push_back(s2);
   }
@@ -1218,12 +1210,10 @@ void plan_deep(Batch& b, const lpcc_model* m, const Levels& lv, const Frames& fr
       const int base = 1 + (d - 1 - k0) + (xfp ? 3 : 2);  // first up layer
       GemmSeg u = seg0();
       u.in = B.Z[d][j];
-      u.in_stride = C;
       u.code = lv.code[j];
       u.cstart = lv.cstart[j];
       u.L = dlayer(m, d, base + t);
       u.out = B.Z[d][j + 1];
-      u.out_stride = C;
       u.rows = (int)fr.tot[j];
       u.child_rows = (int)fr.tot[j + 1];
       v.push_back(u);
@@ -1250,7 +1240,7 @@ void plan_predict(Batch& b, const lpcc_model* m, const std::vector<PredSeg>& seg
   memset(&one, 0, sizeof(one));
   // requantisation by one 24-bit multiply-add where it serves every layer
   bool fits = true;
-  for (auto& s : segs) fits = fits && hlayer(m, s.fc1).rqf && hlayer(m, s.fc2).rqf;
+  for (auto& s : segs) fits = fits && hlayer(m, s.fc1).rqf == 1 && hlayer(m, s.fc2).rqf == 1;
   one.rqf = fits ? 1 : 0;
   size_t so = 0, to = 0;
   if (segs.size() == 1) {
@@ -2501,7 +2491,7 @@ int decode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const uint8_t* const* 
       p.F = features_of(m, B, d);
       p.fc1 = hlayer(m, dlayer(m, d, m->first[d + 1] - m->first[d] - 2));
       p.fc2 = hlayer(m, dlayer(m, d, m->first[d + 1] - m->first[d] - 1));
-      p.rqf = p.fc1.rqf && p.fc2.rqf ? 1 : 0;
+      p.rqf = p.fc1.rqf == 1 && p.fc2.rqf == 1 ? 1 : 0;
       const int32_t* lut = m->d_lut;
       b.launch("decode", fr.tot[d], [=](const uint8_t* base) {
         return launch_decode_chunks(C, (const Chunk*)(base + co), nch, payload, lut, p, dcodes, csum, err + 0, ml, st);
@@ -2637,7 +2627,8 @@ int lpcc_model_load(const void* blob, size_t len, int device, lpcc_model** out) 
     im.push_back(build_image(L));
     const bool own = L.owner == (int)i;  // shared weights are placed once, with their owner
     bytes += (own ? align_up(im.back().packed.size(), 256) + align_up(L.W.size(), 256) : 0) +
-             align_up(im.back().bias.size() * 4, 256) + align_up(im.back().zc.size() * 4, 256);
+             align_up(im.back().bias.size() * 4, 256) + align_up(im.back().zc.size() * 4, 256) +
+             align_up(im.back().biasz.size() * 4, 256);
   }
   bytes += 1024 + align_up(m->host.size() * sizeof(LayerDev), 256);
   std::vector<uint8_t> host(bytes, 0);
@@ -2664,6 +2655,8 @@ int lpcc_model_load(const void* blob, size_t len, int device, lpcc_model** out) 
     }
     D.bias = (const int32_t*)put(im[i].bias.data(), im[i].bias.size() * 4);
     D.zc = im[i].zc.empty() ? nullptr : (const int32_t*)put(im[i].zc.data(), im[i].zc.size() * 4);
+    D.biasz = im[i].biasz.empty() ? D.bias : (const int32_t*)put(im[i].biasz.data(), im[i].biasz.size() * 4);
+    D.z_in = L.z_in;
     const RqBounds rq = requant_bounds(L.m_pos, L.m_neg, L.r, L.z_out);
     D.m_pos = rq.m_pos;
     D.m_neg = rq.m_neg;

@@ -1,0 +1,50 @@
+"""Convolution, child convolution and upsampling at the edges of their row
+tiles (16-row blocks, 64- to 512-row tiles) in every variant: the frequency
+rows of the depths around the edge equal the oracle's, which they do only if
+every layer's integers do."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2603_25260_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_25260_amd import lpcc
+    lpcc.lib()
+    return lpcc
+
+
+def cloud(n, D, seed):
+    """Points whose octree has exactly n nodes at depth D - 2, with one to
+    eight children each."""
+    rng = np.random.default_rng(seed)
+    side = 2 ** (D - 2)
+    cells = rng.choice(side ** 3, size=n, replace=False)
+    c = np.stack([cells // side ** 2, cells // side % side, cells % side], 1) * 4
+    p = np.concatenate([c] + [c[rng.integers(0, n, size=n // k + 1)] for k in (1, 2)])
+    return (p + rng.integers(0, 4, size=p.shape)).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 65, 127, 129, 255, 257, 511, 513])
+@pytest.mark.parametrize("C,n_deep,zp", [(16, 3, False), (32, 2, True), (32, 3, False), (64, 3, True), (64, 2, False)])
+def test_every_variant_at_tile_edges(L, n, C, n_deep, zp):
+    D = 6
+    blob = synth.make_weights(90 + C, C, D, n_deep, zero_points=zp)
+    xyz = cloud(n, D, n + C)
+    print("n", n, "C", C, "n_deep", n_deep, "zp", zp, flush=True)
+    m = L.Model(blob, 0)
+    dx = torch.from_numpy(xyz).cuda()
+    want = {d: O.level_probs(blob, xyz, d) for d in range(D - n_deep - 1, D)}
+    assert len(want[D - 2]) == n
+    for tiling in (1, 2, 4, 11, 12, 14):
+        ctx = L.Context(0)
+        ctx.set_tiling(tiling)
+        for d, w in want.items():
+            assert np.array_equal(L.level_probs(ctx, m, dx, d), w), (tiling, d)
