@@ -36,9 +36,11 @@ struct LayerDev {
   int32_t npad;
   int32_t a_lo, a_hi;   // accumulator range outside which the output saturates
   int32_t z_in;
-  int32_t rqf;          // 1: requant_f computes this layer's requantisation, 2: requant_p
+  int32_t rqf;          // 1: requant_f computes this layer's requantisation
   int32_t f_lo, f_hi;   // requant_f: accumulator clamp, multiplier and rounding term
-  int32_t f_m, f_mn, f_rnd;
+  int32_t f_m, f_rnd;
+  int32_t rqt;          // 1: requant_top computes it with one multiplier, 2: with two (PReLU)
+  int32_t t_m, t_mn, t_rnd;
   int64_t rnd;          // 2^(r-1) for r > 0, else 0 (half-up rounding term)
 };
 
@@ -68,10 +70,13 @@ __device__ __forceinline__ int requant_f(int acc, const LayerDev& L) {
   return (__mul24(a, L.f_m) + L.f_rnd) >> L.r;
 }
 
-// The same for a second multiplier below zero (PReLU), rqf = 2.
-__device__ __forceinline__ int requant_p(int acc, const LayerDev& L) {
+// The same function scaled by 2^24 (rqt): multiplier(s) and rounding term are
+// multiplied by 2^(24 - r), so the int8 output is the top byte and needs no
+// shift (fractions stay below it).
+template <bool PRELU>
+__device__ __forceinline__ int requant_top(int acc, const LayerDev& L) {
   const int a = min(max(acc, L.f_lo), L.f_hi);
-  return (__mul24(a, a >= 0 ? L.f_m : L.f_mn) + L.f_rnd) >> L.r;
+  return (int)((uint32_t)__mul24(a, PRELU && a < 0 ? L.t_mn : L.t_m) + (uint32_t)L.t_rnd);
 }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -111,8 +116,11 @@ __device__ __forceinline__ LayerDev load_layer(const LayerDev* p) {
   L.f_lo = q->f_lo;
   L.f_hi = q->f_hi;
   L.f_m = q->f_m;
-  L.f_mn = q->f_mn;
   L.f_rnd = q->f_rnd;
+  L.rqt = q->rqt;
+  L.t_m = q->t_m;
+  L.t_mn = q->t_mn;
+  L.t_rnd = q->t_rnd;
   L.rnd = q->rnd;
   return L;
 }
@@ -184,7 +192,9 @@ struct GemmArg {
   GemmSeg seg;
   LayerDev L;
   int32_t one;
-  int32_t fl;  // flavour of the sparse and dense layers' kernels (model.hip)
+  int32_t fl;     // flavour of the sparse and dense layers' kernels (model.hip)
+  int32_t tpw;    // down: 16-parent tiles per wave
+  int32_t table;  // down: every segment reads its children through ccode
 };
 struct PredArg {
   PredSeg seg;
@@ -307,10 +317,8 @@ hipError_t launch_conv_split(int cin, int cout, const GemmSeg* segs_dev, const T
 // dense layer on [in | in2]; tiles of 64 rb rows
 hipError_t launch_dense(int cin, int cout, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles,
                         const GemmArg& one, int rb, hipStream_t s);
-// child convolution (C -> C); tpw: 16-parent tiles per wave (1 or kDownTiles),
-// tiles of 64 tpw parents
-constexpr int kDownTiles = 8;
-hipError_t launch_down(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one, int tpw,
+// child convolution (C -> C); tiles of 64 one.tpw parents
+hipError_t launch_down(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
                        hipStream_t s);
 // upsampling, every slot of 16-parent blocks; tiles of 64 rb parents
 hipError_t launch_up(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,

@@ -71,7 +71,7 @@ __device__ __forceinline__ int pick_seg(const GemmSeg* __restrict__ segs, const 
 // and writes its share of the row directly, whole vectors at a time, with no
 // LDS stage, and the biases start in the accumulators.
 //
-// FL is the launch's flavour: F_FAST: requant_f or requant_p serves every
+// FL is the launch's flavour: F_FAST: requant_top serves every
 // segment, no input zero points; F_GENERAL: any requantisation, no input zero
 // points; F_ANY: anything.  Absent inputs must contribute nothing, also with a
 // zero point z (Eq. 13: present inputs contribute (q - z) W).  Their rows are
@@ -81,15 +81,10 @@ __device__ __forceinline__ int pick_seg(const GemmSeg* __restrict__ segs, const 
 // ---------------------------------------------------------------------------
 enum { F_GENERAL = 0, F_FAST = 1, F_ANY = 2 };
 
-template <int FL, bool PRELU>
-__device__ __forceinline__ int rq(int acc, const LayerDev& L) {
-  if (FL != F_FAST) return requant_l(acc, L);
-  return PRELU ? requant_p(acc, L) : requant_f(acc, L);
-}
-
-__device__ __forceinline__ uint32_t pack4(int y0, int y1, int y2, int y3) {  // low bytes
-  const uint32_t lo = __builtin_amdgcn_perm((uint32_t)y1, (uint32_t)y0, 0x0C0C0400u);
-  const uint32_t hi = __builtin_amdgcn_perm((uint32_t)y3, (uint32_t)y2, 0x0C0C0400u);
+template <bool TOP>
+__device__ __forceinline__ uint32_t pack4(int y0, int y1, int y2, int y3) {  // low or top bytes
+  const uint32_t lo = __builtin_amdgcn_perm((uint32_t)y1, (uint32_t)y0, TOP ? 0x0C0C0703u : 0x0C0C0400u);
+  const uint32_t hi = __builtin_amdgcn_perm((uint32_t)y3, (uint32_t)y2, TOP ? 0x0C0C0703u : 0x0C0C0400u);
   return lo | (hi << 16);
 }
 
@@ -137,15 +132,20 @@ __device__ __forceinline__ typename RowPart<C>::T row_out(const v4i (&acc)[C / 1
   for (int nb = 0; nb < C / 16; nb++) {
     int y[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) y[i] = rq<FL, PRELU>(acc[nb][i], L);
+    for (int i = 0; i < 4; i++)
+      y[i] = FL == F_FAST ? requant_top<PRELU>(acc[nb][i], L) : requant_l(acc[nb][i], L);
     if (has_res) {
 #pragma unroll
       for (int i = 0; i < 4; i++) {
-        y[i] += (int)(int8_t)((uint32_t)res[nb] >> (8 * i));
-        y[i] = min(max(y[i], -128), 127);
+        if (FL == F_FAST) {  // the scaled sum saturates where the int8 one does
+          y[i] = __builtin_elementwise_add_sat(y[i], (int)((uint32_t)res[nb] << (24 - 8 * i) & 0xFF000000u));
+        } else {
+          y[i] += (int)(int8_t)((uint32_t)res[nb] >> (8 * i));
+          y[i] = min(max(y[i], -128), 127);
+        }
       }
     }
-    w[nb] = (int)pack4(y[0], y[1], y[2], y[3]);
+    w[nb] = (int)pack4<FL == F_FAST>(y[0], y[1], y[2], y[3]);
   }
   return w;
 }
@@ -462,35 +462,42 @@ __global__ __launch_bounds__(256) void k_conv_split(const GemmSeg* __restrict__ 
 // and takes 16 parents at a time, one per column, over all eight slots: an
 // absent child is gathered as zeros, at no memory cost.  The zeros cost matrix
 // cycles (1.1 to 2 of 8 slots are occupied; 512 cycles per 16 parents at C =
-// 64), but no compaction, no LDS and no atomics: the form with lists of the
-// occupied children per slot, 16-entry groups and int32 accumulators in LDS
-// spent 920 vector instructions and 150 LDS ones per wave and 128 parents and
-// took 1.62 ms for the 8-frame 128-beam batch (14 M parents).
+// 64), but no compaction, no LDS and no atomics.  The weights leave two waves
+// per SIMD, so the gathers are pipelined: a slot's row of the next tile is
+// requested as soon as the slot's products have read this one's, and codes,
+// child positions and table rows are read one and two tiles further ahead.
+//
+// 14 M parents (8 128-beam frames, 18 levels, C = 64): 0.85 ms, against 1.70
+// ms when a tile's gathers were issued together after the products (latency:
+// 32 % of the vector issue slots and 20 % of the matrix cycles used).
 // ---------------------------------------------------------------------------
-template <int C, int TPW, int FL>
-__global__ __launch_bounds__(256) void k_down(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
-                                              const GemmArg A) {
+template <int C, int FL, bool TABLE>
+__global__ __launch_bounds__(256, 2) void k_down(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
+                                                 const GemmArg A) {
   constexpr int NB = C / 16;
   constexpr int SPS = 64 / C;       // slots per step
   constexpr int KS = 8 / SPS;       // steps
   static_assert(C == 16 || C == 32 || C == 64, "C");
   GemmSeg S;
   LayerDev L;
-  const int q0 = pick_seg(segs, tiles, A, S, L, 64 * TPW);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int q0 = pick_seg(segs, tiles, A, S, L, 64 * A.tpw);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
   const uint32_t c0 = (uint32_t)((16 * g) & (C - 1));
   const int kt = (16 * g) / C;      // this lane's slot within a step
-  const int wrow0 = q0 + wave * 16 * TPW;
-  if (wrow0 >= S.rows) return;      // wave-uniform, no barrier below
+  const int wrow0 = q0 + wave * 16 * A.tpw;
+  const int nrow = min(S.rows - wrow0, 16 * A.tpw);
+  if (nrow <= 0) return;            // wave-uniform, no barrier below
   // the children of consecutive parents are consecutive rows: descriptors of
-  // the wave's alone (their first row, at most 8 per parent)
-  const bool table = S.ccode != nullptr;
+  // the wave's parents and children alone (at most 8 per parent; children past
+  // the depth in a corrupt stream are past the end)
   const int cbase = min(__builtin_amdgcn_readfirstlane(gp(S.cstart)[wrow0]), S.child_rows);
-  const int crows = min(S.child_rows - cbase, 128 * TPW);
+  const int crows = min(S.child_rows - cbase, 8 * nrow);
   const __amdgpu_buffer_rsrc_t bin =
-      table ? rsrc_of(S.in, 256 * C) : rsrc_of(S.in + (int64_t)cbase * C, (int64_t)crows * C);
-  const __amdgpu_buffer_rsrc_t bcc = rsrc_of(table ? S.ccode + cbase : S.code, table ? crows : 0);
+      TABLE ? rsrc_of(S.in, 256 * C) : rsrc_of(S.in + (int64_t)cbase * C, (int64_t)crows * C);
+  const __amdgpu_buffer_rsrc_t bcc = rsrc_of(TABLE ? S.ccode + cbase : S.code, TABLE ? crows : 0);
+  const __amdgpu_buffer_rsrc_t bcode = rsrc_of(S.code + wrow0, nrow);
+  const __amdgpu_buffer_rsrc_t bcst = rsrc_of(S.cstart + wrow0, 4ll * nrow);
   const int zs = FL == F_ANY ? (L.z_in & 0xFF) * 0x01010101 : 0;
 
   v4i w[KS][NB], bias[NB];
@@ -503,57 +510,94 @@ __global__ __launch_bounds__(256) void k_down(const GemmSeg* __restrict__ segs, 
   }
   acc_bias<C>(bias, FL == F_ANY ? L.biasz : L.bias, g);
 
-  // children of the wave's tile t: the lane's row offsets, by step (kNoRow
-  // where the child is absent, or past the depth in a corrupt stream)
-  auto rows_of = [&](int t, uint32_t (&o)[KS]) {
-    const int q = wrow0 + 16 * t + r;
-    const uint32_t code = q < S.rows ? (uint32_t)gp(S.code)[q] : 0u;
-    const int first = q < S.rows ? gp(S.cstart)[q] - cbase : 0;
+  // code (0 past the wave's rows) and first child of column r of tile t
+  auto parent = [&](int t, uint32_t& code, uint32_t& first) {
+    const uint32_t q = (uint32_t)(16 * t + r);
+    code = (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(bcode, q, 0, 0);
+    first = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(bcst, 4 * q, 0, 0);
+  };
+  // by step: the lane's child (row index times `scale`, plus c), kNoRow added
+  // where it is absent
+  auto absent = [&](uint32_t code, int s) { return (~code << (31 - s * SPS - kt)) & kNoRow; };
+  auto children = [&](uint32_t code, uint32_t first, uint32_t scale, uint32_t c, uint32_t (&o)[KS]) {
+    uint32_t at = (first - (uint32_t)cbase) * scale + c;
+    if (SPS > 1) at += (uint32_t)__popc(code & ((1u << kt) - 1u)) * scale;
 #pragma unroll
     for (int s = 0; s < KS; s++) {
-      const int slot = s * SPS + kt;
-      const int c = first + __popc(code & ((1u << slot) - 1u));
-      const bool has = ((code >> slot) & 1u) && c < crows;
-      o[s] = has ? (uint32_t)c * (table ? 1u : (uint32_t)C) : kNoRow;
-    }
-    if (table) {  // uniform
-#pragma unroll
-      for (int s = 0; s < KS; s++) {
-        const uint32_t e = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(bcc, o[s], 0, 0);
-        o[s] = o[s] == kNoRow ? kNoRow : e * (uint32_t)C;
-      }
+      o[s] = at | absent(code, s);
+      const uint32_t next = code >> (s * SPS + kt);  // bits of the slots passed on the way to the next step
+      at += (SPS == 1 ? next & 1u : (uint32_t)__popc(next & ((1u << SPS) - 1u))) * scale;
     }
   };
-  auto gather = [&](const uint32_t (&o)[KS], v4i (&x)[KS]) {
-#pragma unroll
-    for (int s = 0; s < KS; s++) {
-      x[s] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(bin, o[s] + c0, 0, 0);
-      if (FL == F_ANY) {
-#pragma unroll
-        for (int z = 0; z < 4; z++) x[s][z] = o[s] != kNoRow ? x[s][z] : zs;
-      }
-    }
-  };
-  typedef typename RowPart<C>::T P;
-  uint32_t o[KS];
+  auto row = [&](uint32_t o) { return (v4i)__builtin_amdgcn_raw_buffer_load_b128(bin, o, 0, 0); };
+
+  // code0: tile t, code1 / first1: tile t + 1, code2 / first2: t + 2 (TABLE
+  // alone), e: table rows of tile t + 1 (in flight)
+  uint32_t code0, code1, code2, first0, first1, first2, o[KS], e[KS];
   v4i x[KS];
-  rows_of(0, o);
-  gather(o, x);
-  for (int t = 0; t < TPW; t++) {
-    const int q = wrow0 + 16 * t + r;
-    if (wrow0 + 16 * t >= S.rows) break;  // wave-uniform
-    if (t + 1 < TPW) rows_of(t + 1, o);
+  auto table_rows = [&](uint32_t code, uint32_t first) {
+    uint32_t ce[KS];
+    children(code, first, 1u, 0u, ce);
+#pragma unroll
+    for (int s = 0; s < KS; s++) e[s] = (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(bcc, ce[s], 0, 0);
+  };
+  auto offsets = [&](uint32_t code, uint32_t first) {
+    if (TABLE) {
+#pragma unroll
+      for (int s = 0; s < KS; s++) o[s] = (e[s] * (uint32_t)C + c0) | absent(code, s);
+    } else {
+      children(code, first, (uint32_t)C, c0, o);
+    }
+  };
+  parent(0, code0, first0);
+  parent(1, code1, first1);
+  if (TABLE) {
+    parent(2, code2, first2);
+    table_rows(code0, first0);
+  }
+  offsets(code0, first0);
+#pragma unroll
+  for (int s = 0; s < KS; s++) x[s] = row(o[s]);
+  if (TABLE) table_rows(code1, first1);
+
+  typedef typename RowPart<C>::T P;
+  const int nt = (nrow + 15) >> 4;
+  for (int t = 0; t < nt; t++) {
+    offsets(code1, first1);
+    uint32_t code, first;
+    if (TABLE) {
+      table_rows(code2, first2);
+      parent(t + 3, code, first);
+    } else {
+      parent(t + 2, code, first);
+    }
     v4i acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; nb++) acc[nb] = bias[nb];
 #pragma unroll
-    for (int s = 0; s < KS; s++)
+    for (int s = 0; s < KS; s++) {
+      if (FL == F_ANY) {
+#pragma unroll
+        for (int z = 0; z < 4; z++) x[s][z] = absent(code0, s) ? zs : x[s][z];
+      }
 #pragma unroll
       for (int nb = 0; nb < NB; nb++) acc[nb] = mfma16(w[s][nb], x[s], acc[nb]);
-    if (t + 1 < TPW) gather(o, x);
-    if (q < S.rows) {
+      x[s] = row(o[s]);
+      __builtin_amdgcn_sched_barrier(0);  // else the gathers sink below all the products
+    }
+    code0 = code1;
+    if (TABLE) {
+      code1 = code2;
+      first1 = first2;
+      code2 = code;
+      first2 = first;
+    } else {
+      code1 = code;
+      first1 = first;
+    }
+    if (16 * t + r < nrow) {
       P none;
-      *(GAS P*)(gp(S.out) + (int64_t)q * C + C / 4 * g) = row_out<C, FL, false>(acc, L, false, none);
+      *(GAS P*)(gp(S.out) + (int64_t)(wrow0 + 16 * t + r) * C + C / 4 * g) = row_out<C, FL, false>(acc, L, false, none);
     }
   }
 }
@@ -611,12 +655,28 @@ hipError_t launch_dense(int cin, int cout, const GemmSeg* segs, const Tile* tile
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_down(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, int tpw,
-                       hipStream_t s) {
+hipError_t launch_down(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-#define LPCC_D(CC, TT) \
-  if (C == CC && tpw == TT) { LPCC_FL(k_down, CC, TT) }
-  LPCC_D(16, 1) LPCC_D(16, kDownTiles) LPCC_D(32, 1) LPCC_D(32, kDownTiles) LPCC_D(64, 1) LPCC_D(64, kDownTiles)
+#define LPCC_D(CC)                                                                                          \
+  if (C == CC) {                                                                                            \
+    if (A.table) {                                                                                          \
+      if (A.fl == F_FAST)                                                                                   \
+        hipLaunchKernelGGL((k_down<CC, F_FAST, true>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);      \
+      else if (A.fl == F_ANY)                                                                               \
+        hipLaunchKernelGGL((k_down<CC, F_ANY, true>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);       \
+      else                                                                                                  \
+        hipLaunchKernelGGL((k_down<CC, F_GENERAL, true>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);   \
+    } else {                                                                                                \
+      if (A.fl == F_FAST)                                                                                   \
+        hipLaunchKernelGGL((k_down<CC, F_FAST, false>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);     \
+      else if (A.fl == F_ANY)                                                                               \
+        hipLaunchKernelGGL((k_down<CC, F_ANY, false>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);      \
+      else                                                                                                  \
+        hipLaunchKernelGGL((k_down<CC, F_GENERAL, false>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);  \
+    }                                                                                                       \
+    return hipGetLastError();                                                                               \
+  }
+  LPCC_D(16) LPCC_D(32) LPCC_D(64)
 #undef LPCC_D
   return hipErrorInvalidValue;
 }

@@ -230,28 +230,36 @@ RqBounds requant_bounds(int32_t m_pos, int32_t m_neg, int r, int z) {
   return B;
 }
 
-// requant_f's and requant_p's parameters of a layer whose requant_bounds are
-// set, and which of them computes the same function: one multiplier (identity)
-// or none below zero (ReLU: the accumulator is clamped from below at 0), or two
-// (PReLU); 24-bit operands, a m + rnd + z 2^r inside int32 on the clamped
-// range, outputs inside int8 at its ends (the function is monotone).
+// requant_f's and requant_top's parameters of a layer whose requant_bounds are
+// set, and whether they compute the same function: one multiplier (identity)
+// or none below zero (ReLU: the accumulator is clamped from below at 0), for
+// requant_top also two (PReLU); 24-bit operands; outputs inside int8 at the
+// ends of the clamped range (the function is monotone); a m + rnd + z 2^r
+// inside int32 on that range (with r <= 24 it then is when scaled by 2^(24-r)
+// too: its top byte is the output).
 void requant_fast(LayerDev& F) {
-  F.rqf = 0;
+  F.rqf = F.rqt = 0;
   F.f_lo = F.m_neg == 0 ? 0 : F.a_lo;
   F.f_hi = F.a_hi;
   F.f_m = F.m_pos;
-  F.f_mn = F.m_neg;
-  F.f_rnd = 0;
+  F.f_rnd = F.t_m = F.t_mn = F.t_rnd = 0;
   const bool single = F.m_neg == 0 || F.m_neg == F.m_pos;
   if (F.r < 0 || F.r > 30) return;
   const int64_t rnd = F.rnd + (int64_t)F.z_out * (1ll << F.r);
   const int64_t top = 1ll << 31, lim = 1ll << 23;
   const int64_t lo = (int64_t)F.f_lo * F.m_neg + rnd, hi = (int64_t)F.f_hi * F.m_pos + rnd;
-  if (F.f_m >= lim || F.f_mn >= lim || F.f_hi >= lim || -(int64_t)F.f_lo > lim) return;
+  if (F.m_pos >= lim || F.m_neg >= lim || F.f_hi >= lim || -(int64_t)F.f_lo > lim) return;
   if (rnd < -top || rnd >= top || lo < -top || lo >= top || hi < -top || hi >= top) return;
   if ((lo >> F.r) < -128 || (hi >> F.r) > 127) return;
   F.f_rnd = (int32_t)rnd;
-  F.rqf = single ? 1 : 2;
+  F.rqf = single ? 1 : 0;
+  if (F.r > 24) return;
+  const int64_t up = 1ll << (24 - F.r);
+  if (F.m_pos * up >= lim || F.m_neg * up >= lim) return;
+  F.t_m = (int32_t)(F.m_pos * up);
+  F.t_mn = (int32_t)(F.m_neg * up);
+  F.t_rnd = (int32_t)(rnd * up);
+  F.rqt = single ? 1 : 2;
 }
 
 // Frequencies of a base depth from the counts n_s of its 255 codes (the
@@ -651,20 +659,17 @@ int64_t count_tiles(const std::vector<int64_t>& rows, int rows_per_tile = 64) {
 // ---- kernel autotuner ----
 // Variant codes.  3x3x3 convolution: rb (1, 2, 4: the present taps, rb blocks
 // of 16 rows per wave) or 10 + rb (every tap, shared by a block's four waves,
-// rb blocks of 16 rows per block).  Dense layers: rb.  Child convolution: 101 /
-// 102 (64 / 512 parents per block); 110 + rb are further names of 101.
+// rb blocks of 16 rows per block).  Dense layers: rb.  Child convolution
+// (parents per block): 101 (64), 111 (128), 112 (256), 114 (512), 102 (1024).
 // Upsampling: 200 + 1/2 (occupied children, tiles of 128 / 512 parents) or
 // 210 + rb (all child slots of every parent).
 struct Variant {
   int code, tile_rows;
 };
-// the codes of a kind, or those the tuner times
-std::vector<Variant> variants(bool up, int mode, bool tuned = false) {
+// the codes of a kind
+std::vector<Variant> variants(bool up, int mode) {
   if (up) return {{201, 128}, {202, 512}, {211, 64}, {212, 128}, {214, 256}};
-  if (mode == G_DOWN) {
-    if (tuned) return {{101, 64}, {102, 64 * kDownTiles}};
-    return {{101, 64}, {102, 64 * kDownTiles}, {111, 64}, {112, 64}, {114, 64}};
-  }
+  if (mode == G_DOWN) return {{101, 64}, {102, 1024}, {111, 128}, {112, 256}, {114, 512}};
   if (mode == G_CONV) return {{1, 64}, {2, 128}, {4, 256}, {11, 16}, {12, 32}, {14, 64}};
   return {{1, 64}, {2, 128}, {4, 256}};
 }
@@ -676,19 +681,23 @@ Variant fixed_variant(bool up, int mode, int tiling, int64_t rows) {
     if (dense) return {210 + rb, 64 * rb};
     return count_tiles({rows}, 512) >= kSlotTileBlocks ? Variant{202, 512} : Variant{201, 128};
   }
-  if (mode == G_DOWN)
-    return !dense && count_tiles({rows}, 64 * kDownTiles) >= kSlotTileBlocks ? Variant{102, 64 * kDownTiles}
-                                                                            : Variant{101, 64};
+  if (mode == G_DOWN) {
+    if (dense) return {tiling + 100, 128 * rb};
+    return count_tiles({rows}, 1024) >= kSlotTileBlocks ? Variant{102, 1024} : Variant{101, 64};
+  }
   if (mode == G_CONV) return {tiling, dense ? 16 * rb : 64 * rb};
   return {rb, 64 * rb};
 }
-hipError_t launch_variant(int code, bool up, int mode, int cin, int cout, const GemmSeg* S, const Tile* T, int nt,
-                          const GemmArg& one, hipStream_t st) {
+hipError_t launch_variant(const Variant& v, bool up, int mode, int cin, int cout, const GemmSeg* S, const Tile* T,
+                          int nt, const GemmArg& arg, hipStream_t st) {
+  const int code = v.code;
+  GemmArg one = arg;
+  one.tpw = v.tile_rows / 64;
   if (up) {
     if (code < 210) return launch_up_cx(cout, S, T, nt, one, code == 201 ? 128 : 512, st);
     return launch_up(cout, S, T, nt, one, code - 210, st);
   }
-  if (mode == G_DOWN) return launch_down(cout, S, T, nt, one, code == 102 ? kDownTiles : 1, st);
+  if (mode == G_DOWN) return launch_down(cout, S, T, nt, one, st);
   if (mode == G_DENSE) return launch_dense(cin, cout, S, T, nt, one, code, st);
   if (code > 10) return launch_conv_split(cin, cout, S, T, nt, one, code - 10, st);
   return launch_conv(cin, cout, S, T, nt, one, code, st);
@@ -933,15 +942,15 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
   memset(&one, 0, sizeof(one));
   // the flavour: 2 where a sparse layer has an input zero point or an array
   // that a convolution gathers from is beyond a buffer descriptor; else 1 where
-  // the 24-bit requantisation serves every layer (requant_p also computes what
-  // requant_f does)
+  // requant_top serves every layer (with two multipliers also a layer of one)
   bool fast = true, any = false;
   for (auto& s : segs) {
     const LayerDev& F = hlayer(m, s.L);
-    fast = fast && (f == "up" ? F.rqf != 0 : F.rqf == 1);
+    fast = fast && (f == "up" ? F.rqt != 0 : F.rqt == 1);
     any = any || F.zc != nullptr || (mode == G_CONV && f != "up" && (int64_t)s.rows * cout >= (1ll << 31));
   }
   one.fl = any ? 2 : (fast ? 1 : 0);
+  one.table = segs[0].ccode != nullptr;  // alike in all segments: a step's children are tables or rows
   size_t so = 0;
   if (segs.size() == 1) {  // by value: no descriptor loads in the kernel
     one.seg = segs[0];
@@ -963,7 +972,7 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
   lpcc_ctx* c = b.ctx;
   const bool up = f == "up";
   lpcc_ctx::TuneRec* rec = nullptr;
-  const std::vector<Variant> all = variants(up, mode), timed_ones = variants(up, mode, true);
+  const std::vector<Variant> all = variants(up, mode);
   std::vector<Variant> cands;
   auto of_code = [&](int code) {
     for (const Variant& v : all)
@@ -980,15 +989,15 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
     if (rec->best) {
       cands = {of_code(rec->best)};
     } else {
-      cands = timed_ones;
+      cands = all;
       rec->ncand = (int)cands.size();
       for (size_t k = 0; k < cands.size(); k++) rec->cand[k] = cands[k].code;
     }
   }
-  std::vector<std::pair<int, size_t>> plan;  // (variant code, tile offset)
+  std::vector<std::pair<Variant, size_t>> plan;  // (variant, tile offset)
   std::vector<int> ntiles;
   for (const Variant& v : cands) {
-    plan.push_back({v.code, segs.size() == 1 ? 0 : b.add(make_tiles(rows, v.tile_rows))});
+    plan.push_back({v, segs.size() == 1 ? 0 : b.add(make_tiles(rows, v.tile_rows))});
     ntiles.push_back((int)count_tiles(rows, v.tile_rows));
   }
   const bool timed = rec != nullptr && cands.size() > 1;
@@ -1012,7 +1021,7 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
       if (e == hipSuccess) e = hipEventRecord(ez, st);
       if (e != hipSuccess) return e;
       int ci = 0;
-      while (rec->cand[ci] != plan[k].first) ci++;
+      while (rec->cand[ci] != plan[k].first.code) ci++;
       c->pending.push_back({rec, ci, ea, ez});
     }
     return hipSuccess;
@@ -1240,7 +1249,7 @@ void plan_predict(Batch& b, const lpcc_model* m, const std::vector<PredSeg>& seg
   memset(&one, 0, sizeof(one));
   // requantisation by one 24-bit multiply-add where it serves every layer
   bool fits = true;
-  for (auto& s : segs) fits = fits && hlayer(m, s.fc1).rqf == 1 && hlayer(m, s.fc2).rqf == 1;
+  for (auto& s : segs) fits = fits && hlayer(m, s.fc1).rqf && hlayer(m, s.fc2).rqf;
   one.rqf = fits ? 1 : 0;
   size_t so = 0, to = 0;
   if (segs.size() == 1) {
@@ -2491,7 +2500,7 @@ int decode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const uint8_t* const* 
       p.F = features_of(m, B, d);
       p.fc1 = hlayer(m, dlayer(m, d, m->first[d + 1] - m->first[d] - 2));
       p.fc2 = hlayer(m, dlayer(m, d, m->first[d + 1] - m->first[d] - 1));
-      p.rqf = p.fc1.rqf == 1 && p.fc2.rqf == 1 ? 1 : 0;
+      p.rqf = p.fc1.rqf && p.fc2.rqf ? 1 : 0;
       const int32_t* lut = m->d_lut;
       b.launch("decode", fr.tot[d], [=](const uint8_t* base) {
         return launch_decode_chunks(C, (const Chunk*)(base + co), nch, payload, lut, p, dcodes, csum, err + 0, ml, st);
