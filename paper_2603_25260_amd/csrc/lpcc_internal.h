@@ -193,7 +193,7 @@ struct GemmArg {
   LayerDev L;
   int32_t one;
   int32_t fl;     // flavour of the sparse and dense layers' kernels (model.hip)
-  int32_t tpw;    // down: 16-parent tiles per wave
+  int32_t tpw;    // down and up: parents per block / 64
   int32_t table;  // down: every segment reads its children through ccode
 };
 struct PredArg {
@@ -323,11 +323,11 @@ hipError_t launch_down(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, in
 // upsampling, every slot of 16-parent blocks; tiles of 64 rb parents
 hipError_t launch_up(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
                      int rb, hipStream_t s);
-// the same over the occupied children only; tiles of P = 128 or 512 parents
-hipError_t launch_up_cx(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
-                        int P, hipStream_t s);
-// tile of the compacted child-slot kernels: the large one once a launch has
-// this many of its blocks, else the small one (more blocks in flight)
+// the same over the occupied children only; tiles of 64 one.tpw parents
+hipError_t launch_up_slots(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
+                           hipStream_t s);
+// the largest tiles of the child-slot kernels serve a launch that has this many
+// of them, the smallest any other (more blocks in flight)
 constexpr int kSlotTileBlocks = 512;
 hipError_t launch_emb(const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, int C, const GemmArg& one,
                       hipStream_t s);

@@ -781,166 +781,178 @@ __global__ __launch_bounds__(256) void k_up(const GemmSeg* __restrict__ segs, co
   }
 }
 
-// Upsampling + pruning over the occupied children only.  A block takes P
-// (128 or 512) consecutive parents and compacts them, per child slot o, into a
-// list of the parents that have child o (wave ballot and prefix count, then
-// the per-wave totals: the list keeps parent order).  The lists are cut into
-// groups of 16 entries; a wave computes one group: the weights of slot o as
-// the row operand, the 16 parents' inputs [Z | bits(X)] as the columns, and a
-// lane writes its C/4 channels of one child row.  Only the last group of each
-// slot is partly empty.  Groups are dealt to the waves in slot order, so a wave
-// keeps a slot's weights across its groups.
-
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {  // set bits of m below this lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-template <int C, int P, int FL>
-__global__ __launch_bounds__(256) void k_up_cx(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
-                                               const GemmArg A) {
+// Upsampling + pruning over the occupied children only.  A block takes a range
+// of 64 A.tpw consecutive parents, and each of its eight waves ONE child slot
+// of it: the wave loads the slot's weights once, scans the parents' codes,
+// lists those that have the child in a list of its own (by ballots), and
+// multiplies the list in groups of 16: the weights are the row operand, the
+// parents' inputs [Z | bits(X)] the columns, and a lane writes its C/4 channels
+// of one child.  No barrier: the waves share nothing but the caches (the same
+// parents' rows, and the two halves of an output line).  A list entry holds
+// all a group needs: the parent (10 bits), its code (8) and the child's row
+// relative to the batch's first child (14; padding and children out of range
+// have the largest value, which is past the end of every output descriptor).
+// The inputs of three groups are in flight behind the products, and the codes
+// of the next batch (1024 parents) behind a batch's groups.
+//
+// Bound: memory and vector issue together (64-byte rows read and written: 1.1 ms
+// of the figure below without the arithmetic, 0.9 ms without the reads or
+// without the writes).  The 28 M children of 8 128-beam frames (18 levels, C =
+// 64) take 1.38 ms; a block's waves sharing one list of all slots, built
+// between barriers, with the weights reloaded at each change of slot, took 1.69
+// ms.  Tiles of 512 / 1024 / 2048 parents: 1.39 / 1.38 / 1.38 ms, and 1.44 /
+// 1.46 / 1.57 ms in the smaller launches of a decode of the same frames; tiles
+// of 256 are for launches that would leave compute units idle.
+constexpr uint32_t kNoChild = 0x3FFFu << 18;
+constexpr int kUpBatch = 1024;
+
+template <int C, int FL>
+__global__ __launch_bounds__(512, 4) void k_up_slots(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
+                                                     const GemmArg A) {
   constexpr int KS = (C + 8 + 63) / 64;
   constexpr int NBS = C / 16;          // column blocks per child slot
   constexpr int NBT = 8 * NBS;         // column blocks of the layer
-  constexpr int PPT = P >= 256 ? P / 256 : 1;  // parents per thread
-  static_assert(C % 16 == 0 && (P % 256 == 0 || P == 128), "shape");
-  __shared__ uint16_t list[8][P];
-  __shared__ uint8_t pcode[P];
-  __shared__ uint32_t wtot[8][4 * PPT];
-  __shared__ uint32_t cnt[8];
-  __shared__ uint32_t goff[9];
+  constexpr int Q = kUpBatch / 256;    // lane l holds parents 256 q + 4 l .. + 3
+  static_assert(C == 16 || C == 32 || C == 64, "C");
+  __shared__ uint32_t lists[8][kUpBatch + 16];
 
   GemmSeg S;
   LayerDev L;
-  const int p0 = pick_seg(segs, tiles, A, S, L, P);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int p0 = pick_seg(segs, tiles, A, S, L, 64 * A.tpw);
+  const int o = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
+  const int pend = min(S.rows, p0 + 64 * A.tpw);
+  uint32_t* list = lists[o];
 
-  // compaction: parent t of the block is thread t % 256, round t / 256
-  uint32_t code[PPT];
-  uint32_t rank[PPT][8];
-#pragma unroll
-  for (int q = 0; q < PPT; q++) {
-    const int t = 256 * q + (int)threadIdx.x;
-    const int p = p0 + t;
-    code[q] = t < P && p < S.rows ? (uint32_t)gp(S.code)[p] : 0u;
-    if (t < P) pcode[t] = (uint8_t)code[q];
-#pragma unroll
-    for (int o = 0; o < 8; o++) {
-      const uint64_t m = __ballot((code[q] >> o) & 1u);
-      rank[q][o] = lanes_below(m);
-      if (lane == 0) wtot[o][4 * q + wave] = (uint32_t)__popcll(m);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < PPT; q++) {
-    const int t = 256 * q + (int)threadIdx.x;
-#pragma unroll
-    for (int o = 0; o < 8; o++) {
-      if (!((code[q] >> o) & 1u)) continue;
-      uint32_t before = rank[q][o];
-      for (int w = 0; w < 4 * q + wave; w++) before += wtot[o][w];
-      list[o][before] = (uint16_t)t;
-    }
-  }
-  if (threadIdx.x < 8) {  // list lengths
-    uint32_t n = 0;
-    for (int w = 0; w < 4 * PPT; w++) n += wtot[threadIdx.x][w];
-    cnt[threadIdx.x] = n;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {  // first group of every slot (16 entries per group)
-    uint32_t gsum = 0;
-    for (int o = 0; o < 8; o++) {
-      goff[o] = gsum;
-      gsum += (cnt[o] + 15) / 16;
-    }
-    goff[8] = gsum;
-  }
-  __syncthreads();
-
-  const GAS v4i* Wp = (const GAS v4i*)L.Wp;
-  const int G = (int)goff[8];
-  // wave w takes the contiguous groups [G w / 4, G (w + 1) / 4)
-  const int gb = (G * wave) / 4, ge = (G * (wave + 1)) / 4;
-  // operands of group gi: its slot, the column's parent, that parent's
-  // input slice and first child (fetched one group ahead of the MFMAs)
-  struct Op {
-    int o, p, first;
-    bool ev;
-    uint32_t pc;
-    v4i a[KS];
-  };
-  auto fetch = [&](int gi, Op& x) {
-    int o = 0;
-#pragma unroll
-    for (int q = 1; q < 8; q++) o += gi >= (int)goff[q] ? 1 : 0;
-    const int e = 16 * (gi - (int)goff[o]) + r;  // entry of column r
-    x.o = o;
-    x.ev = e < (int)cnt[o];
-    const int t = x.ev ? (int)list[o][e] : 0;
-    x.p = p0 + t;
-    x.pc = pcode[t];
-    // column operand: k-slice 16 g of the parent's [Z | bits(X)] row
-#pragma unroll
-    for (int s = 0; s < KS; s++) {
-      const int k0 = 64 * s + 16 * g;
-      x.a[s] = v4i{0, 0, 0, 0};
-      if (x.ev && k0 < C) {
-        x.a[s] = ld16(S.in + (int64_t)x.p * C + k0);
-      } else if (x.ev && k0 == C) {  // occupancy bits as int8 {0,127}, then zeros
-        x.a[s] = occupancy(x.pc);
-      }
-    }
-    x.first = x.ev ? gp(S.cstart)[x.p] : 0;
-  };
-  int cur = -1;
   v4i wb[KS][NBS], bb[NBS];
-  Op nx;
-  if (gb < ge) fetch(gb, nx);
-  for (int gi = gb; gi < ge; gi++) {
-    const Op x = nx;
-    const int o = x.o;
-    // weights and biases of slot o (wave-uniform), requested before the next
-    // group's operands: the memory counter drains in order, so the waits for
-    // these loads then leave the prefetch in flight
-    if (o != cur) {
-      cur = o;
-#pragma unroll
-      for (int s = 0; s < KS; s++)
-#pragma unroll
-        for (int nb = 0; nb < NBS; nb++) wb[s][nb] = Wp[((int64_t)s * NBT + o * NBS + nb) * 64 + lane];
-      acc_bias<C>(bb, L.bias + o * C, g);
-    }
-    if (gi + 1 < ge) fetch(gi + 1, nx);
-    v4i acc[NBS];
-#pragma unroll
-    for (int nb = 0; nb < NBS; nb++) acc[nb] = bb[nb];
+  {
+    const GAS v4i* w = (const GAS v4i*)L.Wp + (int64_t)o * NBS * 64 + lane;
 #pragma unroll
     for (int s = 0; s < KS; s++)
 #pragma unroll
-      for (int nb = 0; nb < NBS; nb++) acc[nb] = mfma16(wb[s][nb], x.a[s], acc[nb]);
-    const int crow = x.first + __popc(x.pc & ((1u << o) - 1u));
-    if (x.ev && crow < S.child_rows) {  // past the depth only for a corrupt stream
+      for (int nb = 0; nb < NBS; nb++) wb[s][nb] = w[(s * NBT + nb) * 64];
+    acc_bias<C>(bb, L.bias + o * C, g);
+  }
+  // codes and first children of the lane's parents of the batch at p (the
+  // arrays are readable to a multiple of 16 bytes past a depth's last row)
+  uint32_t code[Q];
+  v4i first[Q];
+  auto parents = [&](int p) {
+    const int np = min(pend - p, kUpBatch);
+    const __amdgpu_buffer_rsrc_t bcode = rsrc_of(S.code + p, (np + 3) & ~3);
+    const __amdgpu_buffer_rsrc_t bcst = rsrc_of(S.cstart + p, 4ll * ((np + 3) & ~3));
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+      const uint32_t t = 256u * q + 4u * lane;
+      code[q] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(bcode, t, 0, 0);
+      first[q] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(bcst, 4 * t, 0, 0);
+    }
+  };
+  // lanes of the input row's channels, and the lane with the occupancy bits
+  const uint32_t c0 = 16 * g < C ? 16u * g : kNoRow;
+  const uint32_t om = g == (C & 63) / 16 ? 0xFFu : 0u;
+  const uint32_t st0 = (uint32_t)(C / 4 * g);
+  const uint32_t below = (1u << o) - 1u;
+
+  parents(p0);
+  for (; p0 < pend; p0 += kUpBatch) {
+    const int np = min(pend - p0, kUpBatch);
+    const int cfirst = __builtin_amdgcn_readfirstlane(first[0][0]);
+    const int cbase = min(max(cfirst, 0), S.child_rows);
+    const __amdgpu_buffer_rsrc_t bin = rsrc_of(S.in + (int64_t)p0 * C, (int64_t)np * C);
+    const __amdgpu_buffer_rsrc_t bout =
+        rsrc_of(S.out + (int64_t)cbase * C, (int64_t)min(S.child_rows - cbase, 8 * kUpBatch) * C);
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+      if (256 * q >= np) break;
+      const int left = np - (256 * q + 4 * lane);  // parents of this lane inside the batch
+      const uint32_t cw = left >= 4 ? code[q] : (left <= 0 ? 0u : code[q] & ((1u << (8 * left)) - 1u));
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const uint32_t cd = (cw >> (8 * i)) & 0xFFu;
+        const bool has = (cd >> o) & 1u;
+        const uint64_t m = __ballot(has);
+        const uint32_t at = (uint32_t)(first[q][i] - cbase) + (uint32_t)__popc(cd & below);
+        if (has) list[n + (int)lanes_below(m)] = (256u * q + 4u * lane + i) | (cd << 10) | (min(at, 0x3FFFu) << 18);
+        n += __popcll(m);
+      }
+    }
+    if (lane < 16) list[n + lane] = kNoChild;
+    wave_lds_sync();
+    if (p0 + kUpBatch < pend) parents(p0 + kUpBatch);
+    const int G = (n + 15) >> 4;
+    if (G == 0) continue;
+
+    auto entry = [&](int gi) { return list[16 * min(gi, G - 1) + r]; };
+    auto row = [&](uint32_t e) {
+      return (v4i)__builtin_amdgcn_raw_buffer_load_b128(bin, (e & 0x3FFu) * (uint32_t)C + c0, 0, 0);
+    };
+    auto group = [&](uint32_t e, const v4i& x) {
+      // occupancy bits as int8 {0, 127}
+      const uint32_t cd = (e >> 10) & om;
+      const uint32_t lo = __builtin_amdgcn_perm(0u, 0x7F00u, __umul24(cd & 15u, 0x204081u) & 0x01010101u);
+      const uint32_t hi = __builtin_amdgcn_perm(0u, 0x7F00u, __umul24(cd >> 4, 0x204081u) & 0x01010101u);
+      v4i acc[NBS];
+#pragma unroll
+      for (int nb = 0; nb < NBS; nb++) {
+        if (KS == 1) {
+          acc[nb] = mfma16(wb[0][nb], v4i{x[0] | (int)lo, x[1] | (int)hi, x[2], x[3]}, bb[nb]);
+        } else {
+          acc[nb] = mfma16(wb[KS - 1][nb], v4i{(int)lo, (int)hi, 0, 0}, bb[nb]);
+          acc[nb] = mfma16(wb[0][nb], x, acc[nb]);
+        }
+      }
       typedef typename RowPart<C>::T T;
       T none;
-      *(GAS T*)(gp(S.out) + (int64_t)crow * C + C / 4 * g) = row_out<C, FL, true>(acc, L, false, none);
+      const T y = row_out<C, FL, true>(acc, L, false, none);
+      const uint32_t at = (e >> 18) * (uint32_t)C + st0;
+      if constexpr (C == 64) __builtin_amdgcn_raw_buffer_store_b128(y, bout, at, 0, 0);
+      else if constexpr (C == 32) __builtin_amdgcn_raw_buffer_store_b64(y, bout, at, 0, 0);
+      else __builtin_amdgcn_raw_buffer_store_b32(y[0], bout, at, 0, 0);
+    };
+    uint32_t e[3], en;
+    v4i x[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) e[k] = entry(k);
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      x[k] = row(e[k]);
+      __builtin_amdgcn_sched_barrier(0);  // in the order of use
     }
+    int gi = 0;
+    for (; gi + 3 <= G; gi += 3) {
+#pragma unroll
+      for (int k = 0; k < 3; k++) {
+        en = entry(gi + k + 3);
+        group(e[k], x[k]);
+        e[k] = en;
+        x[k] = row(en);
+        __builtin_amdgcn_sched_barrier(0);  // else the loads sink below the next group
+      }
+    }
+    if (gi < G) group(e[0], x[0]);
+    if (gi + 1 < G) group(e[1], x[1]);
+    wave_lds_sync();  // the list is written again
   }
 }
 
-hipError_t launch_up_cx(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A, int P,
-                        hipStream_t s) {
+hipError_t launch_up_slots(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A,
+                           hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-#define LPCC_U(CC, PP)                                                                                        \
-  if (C == CC && P == PP) {                                                                                   \
+#define LPCC_U(CC)                                                                                            \
+  if (C == CC) {                                                                                              \
     if (A.fl == F_FAST)                                                                                       \
-      hipLaunchKernelGGL((k_up_cx<CC, PP, F_FAST>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);           \
+      hipLaunchKernelGGL((k_up_slots<CC, F_FAST>), dim3(ntiles), dim3(512), 0, s, segs, tiles, A);            \
     else                                                                                                      \
-      hipLaunchKernelGGL((k_up_cx<CC, PP, F_GENERAL>), dim3(ntiles), dim3(256), 0, s, segs, tiles, A);        \
+      hipLaunchKernelGGL((k_up_slots<CC, F_GENERAL>), dim3(ntiles), dim3(512), 0, s, segs, tiles, A);         \
     return hipGetLastError();                                                                                 \
   }
-  LPCC_U(16, 128) LPCC_U(16, 512) LPCC_U(32, 128) LPCC_U(32, 512) LPCC_U(64, 128) LPCC_U(64, 512)
+  LPCC_U(16) LPCC_U(32) LPCC_U(64)
 #undef LPCC_U
   return hipErrorInvalidValue;
 }

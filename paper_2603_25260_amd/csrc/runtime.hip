@@ -661,14 +661,15 @@ int64_t count_tiles(const std::vector<int64_t>& rows, int rows_per_tile = 64) {
 // of 16 rows per wave) or 10 + rb (every tap, shared by a block's four waves,
 // rb blocks of 16 rows per block).  Dense layers: rb.  Child convolution
 // (parents per block): 101 (64), 111 (128), 112 (256), 114 (512), 102 (1024).
-// Upsampling: 200 + 1/2 (occupied children, tiles of 128 / 512 parents) or
+// Upsampling: 201 / 202 (occupied children, 256 / 1024 parents per block) or
 // 210 + rb (all child slots of every parent).
+constexpr int kUpSmall = 256, kUpLarge = 1024;
 struct Variant {
   int code, tile_rows;
 };
 // the codes of a kind
 std::vector<Variant> variants(bool up, int mode) {
-  if (up) return {{201, 128}, {202, 512}, {211, 64}, {212, 128}, {214, 256}};
+  if (up) return {{201, kUpSmall}, {202, kUpLarge}, {211, 64}, {212, 128}, {214, 256}};
   if (mode == G_DOWN) return {{101, 64}, {102, 1024}, {111, 128}, {112, 256}, {114, 512}};
   if (mode == G_CONV) return {{1, 64}, {2, 128}, {4, 256}, {11, 16}, {12, 32}, {14, 64}};
   return {{1, 64}, {2, 128}, {4, 256}};
@@ -679,7 +680,7 @@ Variant fixed_variant(bool up, int mode, int tiling, int64_t rows) {
   const int rb = tiling % 10;
   if (up) {
     if (dense) return {210 + rb, 64 * rb};
-    return count_tiles({rows}, 512) >= kSlotTileBlocks ? Variant{202, 512} : Variant{201, 128};
+    return count_tiles({rows}, kUpLarge) >= kSlotTileBlocks ? Variant{202, kUpLarge} : Variant{201, kUpSmall};
   }
   if (mode == G_DOWN) {
     if (dense) return {tiling + 100, 128 * rb};
@@ -694,7 +695,7 @@ hipError_t launch_variant(const Variant& v, bool up, int mode, int cin, int cout
   GemmArg one = arg;
   one.tpw = v.tile_rows / 64;
   if (up) {
-    if (code < 210) return launch_up_cx(cout, S, T, nt, one, code == 201 ? 128 : 512, st);
+    if (code < 210) return launch_up_slots(cout, S, T, nt, one, st);
     return launch_up(cout, S, T, nt, one, code - 210, st);
   }
   if (mode == G_DOWN) return launch_down(cout, S, T, nt, one, st);

@@ -1,5 +1,5 @@
 """Convolution, child convolution and upsampling at the edges of their row
-tiles (16-row blocks, 64- to 512-row tiles) in every variant: the frequency
+tiles (16-row blocks, 64- to 1024-row tiles) in every variant: the frequency
 rows of the depths around the edge equal the oracle's, which they do only if
 every layer's integers do."""
 import numpy as np
@@ -32,7 +32,7 @@ def cloud(n, D, seed):
     return (p + rng.integers(0, 4, size=p.shape)).astype(np.int32)
 
 
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 65, 127, 129, 255, 257, 511, 513])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 65, 127, 129, 255, 257, 511, 513, 1024, 1025])
 @pytest.mark.parametrize("C,n_deep,zp", [(16, 3, False), (32, 2, True), (32, 3, False), (64, 3, True), (64, 2, False)])
 def test_every_variant_at_tile_edges(L, n, C, n_deep, zp):
     D = 6
