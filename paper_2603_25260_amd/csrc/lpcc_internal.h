@@ -289,7 +289,17 @@ hipError_t launch_level_write(const uint64_t* keys, int64_t n, int D, int tile, 
                               const uint32_t* totals, const LevelOut& lo, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
-hipError_t launch_iota_u64(uint64_t* p, int64_t n, hipStream_t s);  // p[i] = i
+// p[i] = i, zero[0..3] = 0
+hipError_t launch_roots(uint64_t* p, int64_t n, uint32_t* zero, hipStream_t s);
+// up to kCopySegs byte ranges (any alignment; device memory or pinned host
+// memory) in one launch: one copy call per range costs the host 5 to 10 us each
+constexpr int kCopySegs = 32;
+struct CopySegs {
+  uint8_t* dst[kCopySegs];
+  const uint8_t* src[kCopySegs];
+  uint64_t n[kCopySegs];
+};
+hipError_t launch_copy_segs(const CopySegs& S, int nseg, hipStream_t s);
 
 hipError_t launch_hash_insert(const uint64_t* keys, int64_t n, uint64_t* table, uint64_t mask, hipStream_t s);
 // All jobs' insertions, then all jobs' neighbour tables (two launches); the
@@ -379,7 +389,19 @@ hipError_t launch_expand_chunks(const Chunk* chunks, int nchunks, const uint64_t
                                 int64_t n, uint32_t* csum, uint64_t* ckeys, int32_t* cstart,
                                 int64_t n_child_expected, uint64_t* table, uint64_t mask, uint32_t* err,
                                 hipStream_t s);
-hipError_t launch_keys_to_xyz(const uint64_t* keys, int64_t n, int D, int32_t* xyz, hipStream_t s);
+// coordinates of up to kXyzFrames frames; with words_out (pinned memory), also
+// words_out[0..3] = words[0..3]
+constexpr int kXyzFrames = 32;
+struct XyzFrames {
+  const uint64_t* keys[kXyzFrames];
+  int32_t* xyz[kXyzFrames];
+  int64_t n[kXyzFrames];
+  uint32_t blk[kXyzFrames + 1];  // first block of each frame
+  int32_t nf, D;
+  const uint32_t* words;
+  uint32_t* words_out;
+};
+hipError_t launch_keys_to_xyz(XyzFrames& X, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Workspace accounting (host): upper bounds of the three arenas (octree,

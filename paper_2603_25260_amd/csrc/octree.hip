@@ -593,13 +593,33 @@ __global__ void k_fill_u64(uint64_t* p, int64_t n, uint64_t v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
-__global__ void k_iota_u64(uint64_t* p, int64_t n) {
+__global__ void k_roots(uint64_t* p, int64_t n, uint32_t* zero) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = (uint64_t)i;
+  if (i < 4) zero[i] = 0;
 }
-hipError_t launch_iota_u64(uint64_t* p, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_iota_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
+hipError_t launch_roots(uint64_t* p, int64_t n, uint32_t* zero, hipStream_t s) {
+  hipLaunchKernelGGL(k_roots, dim3((unsigned)(n / 256 + 1)), dim3(256), 0, s, p, n, zero);
+  return hipGetLastError();
+}
+
+// 16 bytes per thread and step, from and to any alignment
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(1)));
+__global__ __launch_bounds__(256) void k_copy_segs(const CopySegs S) {
+  const GAS uint8_t* src = gp(S.src[blockIdx.y]);
+  GAS uint8_t* dst = gp(S.dst[blockIdx.y]);
+  const uint64_t n = S.n[blockIdx.y], whole = n & ~15ull;
+  const uint64_t i0 = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  for (uint64_t i = 16 * i0; i < whole; i += (uint64_t)gridDim.x * 4096)
+    *(GAS u4_any*)(dst + i) = *(const GAS u4_any*)(src + i);
+  if (i0 < (n & 15u)) dst[whole + i0] = src[whole + i0];
+}
+hipError_t launch_copy_segs(const CopySegs& S, int nseg, hipStream_t s) {
+  if (nseg <= 0) return hipSuccess;
+  uint64_t most = 0;
+  for (int i = 0; i < nseg; i++) most = std::max(most, S.n[i]);
+  const unsigned gx = (unsigned)std::min<uint64_t>(most / 4096 + 1, 256);
+  hipLaunchKernelGGL(k_copy_segs, dim3(gx, (unsigned)nseg), dim3(256), 0, s, S);
   return hipGetLastError();
 }
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s) {
@@ -1064,18 +1084,24 @@ hipError_t launch_base_rows(const uint64_t* keys, int64_t n, int d, int nb, int 
   return hipGetLastError();
 }
 
-__global__ void k_keys_to_xyz(const uint64_t* __restrict__ keys, int64_t n, int D, int32_t* __restrict__ xyz) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  uint64_t k = keys[i] & ((D >= 21) ? ~0ull : ((1ull << (3 * D)) - 1));
-  xyz[3 * i] = (int32_t)compact3(k >> 2);
-  xyz[3 * i + 1] = (int32_t)compact3(k >> 1);
-  xyz[3 * i + 2] = (int32_t)compact3(k);
+__global__ __launch_bounds__(256) void k_keys_to_xyz(const XyzFrames X) {
+  if (X.words_out != nullptr && blockIdx.x == 0 && threadIdx.x < 4) X.words_out[threadIdx.x] = X.words[threadIdx.x];
+  int f = 0;
+  while (f + 1 < X.nf && blockIdx.x >= X.blk[f + 1]) f++;
+  const int64_t i = (int64_t)(blockIdx.x - X.blk[f]) * 256 + threadIdx.x;
+  if (i >= X.n[f]) return;
+  uint64_t k = gp(X.keys[f])[i] & ((X.D >= 21) ? ~0ull : ((1ull << (3 * X.D)) - 1));
+  GAS int32_t* xyz = gp(X.xyz[f]) + 3 * i;
+  xyz[0] = (int32_t)compact3(k >> 2);
+  xyz[1] = (int32_t)compact3(k >> 1);
+  xyz[2] = (int32_t)compact3(k);
 }
 
-hipError_t launch_keys_to_xyz(const uint64_t* keys, int64_t n, int D, int32_t* xyz, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_keys_to_xyz, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, keys, n, D, xyz);
+hipError_t launch_keys_to_xyz(XyzFrames& X, hipStream_t s) {
+  if (X.nf <= 0) return hipSuccess;
+  X.blk[0] = 0;
+  for (int f = 0; f < X.nf; f++) X.blk[f + 1] = X.blk[f] + (uint32_t)((X.n[f] + 255) / 256);
+  hipLaunchKernelGGL(k_keys_to_xyz, dim3(std::max(X.blk[X.nf], 1u)), dim3(256), 0, s, X);
   return hipGetLastError();
 }
 

@@ -522,6 +522,51 @@ bool is_device_ptr(const void* p) {
   return a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged;
 }
 
+// Whether kernels on the context's device may read or write user memory p
+// (p is known to be device memory; a peer's is left to the copy engine).
+bool on_device(const lpcc_ctx* c, const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == c->device;
+}
+
+// Byte ranges to copy on the context's stream: those that a kernel reaches
+// (device memory of this device, the context's staging where it is pinned) in
+// launches of kCopySegs, the others one by one.  32 uneven frames: decode 2.63
+// -> 2.43 ms, encode 1.87 -> 1.80 ms.
+struct Copies {
+  std::vector<std::pair<uint8_t*, const uint8_t*>> at;
+  std::vector<size_t> n;
+  void add(void* dst, const void* src, size_t bytes) {
+    if (bytes == 0) return;
+    at.push_back({(uint8_t*)dst, (const uint8_t*)src});
+    n.push_back(bytes);
+  }
+  hipError_t run(bool kernel, hipMemcpyKind kind, hipStream_t st) const {
+    hipError_t e = hipSuccess;
+    if (!kernel || n.size() < 2) {  // a single range gains nothing
+      for (size_t i = 0; i < n.size() && e == hipSuccess; i++)
+        e = hipMemcpyAsync(at[i].first, at[i].second, n[i], kind, st);
+      return e;
+    }
+    for (size_t i0 = 0; i0 < n.size() && e == hipSuccess; i0 += kCopySegs) {
+      CopySegs S;
+      memset(&S, 0, sizeof(S));
+      const int k = (int)std::min<size_t>(kCopySegs, n.size() - i0);
+      for (int i = 0; i < k; i++) {
+        S.dst[i] = at[i0 + i].first;
+        S.src[i] = at[i0 + i].second;
+        S.n[i] = n[i0 + i];
+      }
+      e = launch_copy_segs(S, k, st);
+    }
+    return e;
+  }
+};
+
 // Descriptor batch: host bytes uploaded in one copy; launches are closures
 // over offsets into the uploaded block.
 struct Batch {
@@ -1888,15 +1933,8 @@ int encode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const int32_t* const* 
         return launch_rc_pack_dev((const Chunk*)(base + co), n_ch, (const int32_t*)(base + fo),
                                   (const PackFrame*)(base + pfo), scratch, lens, st);
       });
-      for (int f = 0; f < nf; f++) {
-        uint8_t* o = os.out[f];
-        const size_t at = ho + hoff[f], n_ = std::min<size_t>(hpre[f], (size_t)os.cap[f]);
-        if (n_ == 0) continue;
-        b.launch("header", 0, [=](const uint8_t* base) {
-          return hipMemcpyAsync(o, base + at, n_, hipMemcpyDeviceToDevice, st);
-        });
-      }
-      // the lengths come back with the same batch, for the totals
+      // headers from the descriptor block; the lengths come back with the same
+      // batch, for the totals
       const size_t lb = align_up(nch * 4, 256);
       s = reserve_pinned(c, desc_off + align_up(b.bytes.size(), 256) + lb);
       if (s) return s;
@@ -1904,7 +1942,22 @@ int encode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const int32_t* const* 
       uint32_t* hl_ = hlens;
       const uint32_t* dl = lens;
       const size_t nb_ = nch * 4;
-      b.launch("lens", 0, [=](const uint8_t*) { return hipMemcpyAsync(hl_, dl, nb_, hipMemcpyDeviceToHost, st); });
+      std::vector<size_t> hn(nf);
+      bool here = !c->fixed, some = false;
+      for (int f = 0; f < nf; f++) {
+        hn[f] = std::min<size_t>(hpre[f], (size_t)os.cap[f]);
+        if (hn[f]) here = here && on_device(c, os.out[f]);
+        some = some || hn[f] > 0;
+      }
+      here = here && some;
+      const std::vector<uint8_t*> outs(os.out, os.out + nf);
+      b.launch("header", 0, [=](const uint8_t* base) {
+        Copies hc, lc;
+        for (int f = 0; f < nf; f++) hc.add(outs[f], base + ho + hoff[f], hn[f]);
+        (here ? hc : lc).add(hl_, dl, nb_);
+        const hipError_t e = hc.run(here, hipMemcpyDeviceToDevice, st);
+        return e != hipSuccess ? e : lc.run(false, hipMemcpyDeviceToHost, st);
+      });
     }
   }
   s = run_batch(c, b, &desc_off);
@@ -2129,8 +2182,14 @@ int read_headers(lpcc_ctx* c, int nf, const uint8_t* const* bs, const size_t* le
   if (need == 0) return LPCC_OK;
   int s = reserve_pinned(c, need);
   if (s) return s;
+  Copies pre;
+  bool here = !c->fixed;
   for (int f = 0; f < nf; f++)
-    if (dev[f] && got[f]) HIPC(hipMemcpyAsync(c->pinned + off[f], bs[f], got[f], hipMemcpyDeviceToHost, c->stream));
+    if (dev[f] && got[f]) {
+      pre.add(c->pinned + off[f], bs[f], got[f]);
+      here = here && on_device(c, bs[f]);
+    }
+  HIPC(pre.run(here, hipMemcpyDeviceToHost, c->stream));
   HIPC(stream_wait(c, c->stream));
   std::vector<int> more;
   std::vector<size_t> want(nf, 0);
@@ -2396,16 +2455,17 @@ int decode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const uint8_t* const* 
   if (live.size() == 1 && is_device_ptr(bs[live[0]])) {
     payload = const_cast<uint8_t*>(bs[live[0]]) + H[live[0]].hdr;
   } else {
+    Copies here, peer, host;
     for (int f : live) {
-      const size_t pl = H[f].total - H[f].hdr;
-      if (!pl) continue;
-      HIPC(hipMemcpyAsync(payload + payoff[f], bs[f] + H[f].hdr, pl,
-                          is_device_ptr(bs[f]) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
+      Copies& to = !is_device_ptr(bs[f]) ? host : (on_device(c, bs[f]) ? here : peer);
+      to.add(payload + payoff[f], bs[f] + H[f].hdr, H[f].total - H[f].hdr);
     }
+    HIPC(here.run(true, hipMemcpyDeviceToDevice, st));
+    HIPC(peer.run(false, hipMemcpyDeviceToDevice, st));
+    HIPC(host.run(false, hipMemcpyHostToDevice, st));
   }
   // V_0: one root per live frame; its key is the frame's position tag
-  HIPC(launch_iota_u64(lv.key[0], (int64_t)live.size(), st));
-  HIPC(launch_fill_u32(err, 4, 0, st));
+  HIPC(launch_roots(lv.key[0], (int64_t)live.size(), err, st));
 
   Batch b;
   b.ctx = c;
@@ -2578,17 +2638,29 @@ int decode_impl(lpcc_ctx* c, const lpcc_model* m, int nf, const uint8_t* const* 
   if (s) return s;
   // coordinates, enqueued before the error words are read (a corrupt frame
   // only writes within its own output; its status then reports the error)
-  for (int f : live) {
-    const uint64_t* keys = lv.key[D] + fr.off[f][D];
-    int32_t* dst = xdev[f] ? xyz_out[f] : xyz_stage + 3 * fr.off[f][D];
-    HIPC(launch_keys_to_xyz(keys, fr.N[f][D], D, dst, st));
-    if (!xdev[f])
-      HIPC(hipMemcpyAsync(xyz_out[f], dst, (size_t)fr.N[f][D] * 12, hipMemcpyDeviceToHost, st));
-  }
+  // together with the error words where the staging is pinned
   s = reserve_pinned(c, desc_off + 256);
   if (s) return s;
   uint32_t* herr = (uint32_t*)(c->pinned + c->pinned_cap - 256);
-  HIPC(hipMemcpyAsync(herr, err, 16, hipMemcpyDeviceToHost, st));
+  for (size_t i0 = 0; i0 < live.size(); i0 += kXyzFrames) {
+    XyzFrames X;
+    memset(&X, 0, sizeof(X));
+    X.D = D;
+    X.nf = (int)std::min<size_t>(kXyzFrames, live.size() - i0);
+    for (int i = 0; i < X.nf; i++) {
+      const int f = live[i0 + i];
+      X.keys[i] = lv.key[D] + fr.off[f][D];
+      X.xyz[i] = xdev[f] ? xyz_out[f] : xyz_stage + 3 * fr.off[f][D];
+      X.n[i] = fr.N[f][D];
+    }
+    X.words = err;
+    X.words_out = c->fixed ? nullptr : herr;
+    HIPC(launch_keys_to_xyz(X, st));
+  }
+  for (int f : live)
+    if (!xdev[f])
+      HIPC(hipMemcpyAsync(xyz_out[f], xyz_stage + 3 * fr.off[f][D], (size_t)fr.N[f][D] * 12, hipMemcpyDeviceToHost, st));
+  if (c->fixed) HIPC(hipMemcpyAsync(herr, err, 16, hipMemcpyDeviceToHost, st));
   HIPC(stream_wait(c, st));
   if (herr[0] | herr[1]) {
     // a corrupt frame misaligns the shared arrays: report per frame by
