@@ -339,6 +339,10 @@ hipError_t launch_up_slots(int C, const GemmSeg* segs_dev, const Tile* tiles_dev
 // the largest tiles of the child-slot kernels serve a launch that has this many
 // of them, the smallest any other (more blocks in flight)
 constexpr int kSlotTileBlocks = 512;
+// rows of the codes through a table in LDS (every segment with codes); tiles of kEmbRows
+constexpr int kEmbRows = 2048;
+hipError_t launch_emb_rows(const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, int C, const GemmArg& one,
+                           hipStream_t s);
 hipError_t launch_emb(const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, int C, const GemmArg& one,
                       hipStream_t s);
 // single-segment predictor launches up to this many rows take 4 rows per wave

@@ -1006,7 +1006,32 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
     so = b.add(segs);
   }
   if (f == "emb") {
-    const size_t to = segs.size() == 1 ? 0 : b.add(make_tiles(rows));
+    // Through the table once its tiles fill the chip; a segment without codes
+    // (the 256 rows of the table the child convolution reads) computes its rows.
+    bool many = count_tiles(rows, kEmbRows) >= 128;
+    std::vector<GemmSeg> left;
+    std::vector<int64_t> lrows;
+    if (many) {
+      std::vector<GemmSeg> coded;
+      std::vector<int64_t> crows;
+      for (auto& s : segs) {
+        (s.code ? coded : left).push_back(s);
+        (s.code ? crows : lrows).push_back(s.rows);
+      }
+      const size_t cs = b.add(coded), ct = b.add(make_tiles(crows, kEmbRows));
+      const int cn = (int)count_tiles(crows, kEmbRows);
+      GemmArg many_arg;
+      memset(&many_arg, 0, sizeof(many_arg));
+      b.launch(f, units, [=](const uint8_t* base) {
+        return launch_emb_rows((const GemmSeg*)(base + cs), (const Tile*)(base + ct), cn, cout, many_arg, st);
+      });
+      if (left.empty()) return;
+      units = 0;
+      so = b.add(left);
+      rows = lrows;
+      one.one = 0;
+    }
+    const size_t to = one.one ? 0 : b.add(make_tiles(rows));
     const int nt = (int)count_tiles(rows);
     b.launch(f, units, [=](const uint8_t* base) {
       return launch_emb((const GemmSeg*)(base + so), (const Tile*)(base + to), nt, cout, one, st);
