@@ -196,19 +196,19 @@ FAMILY_BOUND = {"conv": "hbm", "down": "hbm", "skip": "hbm", "emb": "hbm", "up":
 # what the same counters read for a 256 MiB device copy (fetch x2, write x1).
 # They hold for the library sources whose digest is TRAFFIC_SOURCES; any other
 # source tree reports traffic null.
-TRAFFIC_SOURCES = "4f84387de7fb0e09"
+TRAFFIC_SOURCES = "668293a82610b1ee"
 FAMILY_TRAFFIC = {
-    "conv": (5806464438, 2248017152),
-    "down": (1584201319, 2081497216),
-    "skip": (1708494149, 853240960),
-    "emb": (3487946, 170779264),
-    "up": (4595275146, 4374389462),
-    "predict": (1692923554, 6725538311),
-    "rc_encode": (58749844, 19132036),
-    "rc_decode": (8108543862, 25131215),
-    "hash": (505213627, 806670806),
-    "expand": (136333824, 170685344),
-    "pack": (32347899, 15933342),
+    "conv": (6008226684, 2248017151),
+    "down": (1607387348, 2081497215),
+    "skip": (1707822211, 853240960),
+    "emb": (3185717, 170779340),
+    "up": (3977180695, 4444667148),
+    "predict": (837734373, 52342387),
+    "decode": (854779605, 15637462),
+    "rc_encode": (58726162, 19075567),
+    "hash": (516034354, 808287584),
+    "expand": (136322436, 170685344),
+    "pack": (32340150, 15933325),
 }
 
 

@@ -295,11 +295,12 @@ int lpcc_timing_read(lpcc_ctx* c, int64_t* launches, double* total_ms, int64_t* 
 /*
  * Kernel variants of the gather-GEMM, child-convolution and upsampling
  * launches (the indexed linear transforms of the sparse convolutions,
- * Sec. 3.3, the stride-2 steps of Eq. 4 and the upsampling of Eq. 6).  Each
- * kind has a compacted variant, which works only on the present taps of a
- * wave's rows or the occupied children of a block's parents (wave ballot
- * and prefix count), and a dense one over every tap or child slot (absent
- * ones contribute zeros); a wave computes rb blocks of 16 rows.  rb = 0 (the
+ * Sec. 3.3, the stride-2 steps of Eq. 4 and the upsampling of Eq. 6).  The
+ * gather-GEMMs and the upsampling have a compacted variant, which works only
+ * on the present taps of a wave's rows or the occupied children of a block's
+ * parents, and a dense one over every tap or child slot (absent ones
+ * contribute zeros); the child convolution works on every slot, with a choice
+ * of parents per block.  A wave computes rb blocks of 16 rows.  rb = 0 (the
  * default) autotunes: the first launch of every (kernel, widths, log2 rows)
  * class on this context runs each candidate, timed with HIP events on the
  * context's stream, and later launches of the class use the fastest.  rb =
@@ -312,9 +313,10 @@ int lpcc_timing_read(lpcc_ctx* c, int64_t* launches, double* total_ms, int64_t* 
  * mode, cin, cout, log2 rows, chosen variant or 0 while undecided) into out
  * (host, 6 * cap ints), the number of classes into *n; LPCC_E_CAPACITY when
  * cap is too small (the first cap rows are written).  Variant codes: rb (1,
- * 2, 4) and 10 + rb for the gather-GEMMs, 101/102 (compacted, 64/128 parents
- * per block) and 110 + rb for the child convolution, 201/202 (compacted,
- * 128/512 parents per block) and 210 + rb for the upsampling.
+ * 2, 4) and 10 + rb for the gather-GEMMs, 101, 111, 112, 114, 102 (64, 128,
+ * 256, 512, 1024 parents per block) for the child convolution, 201/202
+ * (occupied children, 256/1024 parents per block) and 210 + rb for the
+ * upsampling.
  *
  * lpcc_ctx_set_tuning imports such a table (host, 6 * n ints, the format
  * lpcc_ctx_tuning writes): each row's class then uses the row's variant

@@ -7,7 +7,7 @@
 //   * the occupancy embedding;
 //   * the predictor (Eq. 7) fused with the integer softmax (Eq. 15) and the
 //     16-bit frequency table that drives the range coder.
-// One wave computes a 16-row tile with v_mfma_i32_16x16x64_i8; int32
+// The products run on v_mfma_i32_16x16x64_i8, weights as rows; int32
 // accumulation is exact, so any summation order gives the same result.
 #include "lpcc_internal.h"
 
@@ -172,11 +172,15 @@ __device__ __forceinline__ void acc_bias(v4i (&acc)[C / 16], const int32_t* bias
 // v + 1 are in flight behind the products of step v, and the table rows of the
 // step after are read ahead of them.
 //
-// Bound: latency of the gathers (mostly L2) at the occupancy the accumulators
-// leave, and vector issue.  With the gathered rows as the row operand, the
-// accumulators staged through LDS, the 64-bit requantisation and selects that
-// zeroed absent rows and weights, a wave of 64 rows issued 2640 vector
-// instructions (56 % of the issue slots of the launch).
+// Bound: the 64 bytes per clock between a CU and its L1.  Gathers and weights
+// take half each (4 KB per 64 rows and 64 of K); the texture units are busy
+// 97 % of the time, the matrix cores 27 %.  The 7.0 M rows of 8 128-beam
+// frames' deep depths, 128 -> 64 channels: 1.13 ms; 1.52 ms with the gathered
+// rows as the row operand, the accumulators staged through LDS, the 64-bit
+// requantisation and selects that zeroed absent rows and weights (2640 vector
+// instructions per wave of 64 rows).  With the weights in LDS instead (one
+// block of 16 waves per CU) the CU cycles fall by a quarter, but the launches
+// end unevenly and the calls gain nothing.
 // ---------------------------------------------------------------------------
 template <int MODE>
 struct Taps;
@@ -469,7 +473,10 @@ __global__ __launch_bounds__(256) void k_conv_split(const GemmSeg* __restrict__ 
 //
 // 14 M parents (8 128-beam frames, 18 levels, C = 64): 0.85 ms, against 1.70
 // ms when a tile's gathers were issued together after the products (latency:
-// 32 % of the vector issue slots and 20 % of the matrix cycles used).
+// 32 % of the vector issue slots and 20 % of the matrix cycles used).  Bound
+// now: the texture units, busy 97 % of the time with the gathers.  Two tiles of
+// gathers in flight, the children through LDS, and the weights in LDS with
+// four waves per SIMD were each no faster end to end.
 // ---------------------------------------------------------------------------
 template <int C, int FL, bool TABLE>
 __global__ __launch_bounds__(256, 2) void k_down(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
