@@ -1115,20 +1115,50 @@ __device__ __forceinline__ uint32_t recip_k(uint32_t S) {  // floor(65281 * 2^16
 // by its two users (sub-dword source selects), which the compiler does only
 // for a single user, and it forms the multiply-add with the quarter-rate
 // 64-bit one.  No matrix instruction is in flight here (the maximum over all
-// logits comes first), so the asm needs no wait states it cannot see.
-__device__ __forceinline__ uint32_t freq_add(uint32_t run, uint32_t E, uint32_t S, uint32_t K) {
-  uint32_t m, t, o;
-  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(m) : "v"(E), "v"(K), "s"(0x10000));
+// logits comes first).  The compare's VCC may be read as a carry only two wait
+// states later, and the compiler does not look inside the asm: the first two
+// instructions of the next entry lie in between.
+struct FreqStep {
+  uint32_t m, t;  // E K + 2^16 (q1 in its high half), q1 S
+};
+__device__ __forceinline__ FreqStep freq_begin(uint32_t E, uint32_t S, uint32_t K) {
+  FreqStep f;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(f.m) : "v"(E), "v"(K), "s"(0x10000));
   asm("v_mul_u32_u24_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD"
-      : "=v"(t)
-      : "v"(m), "v"(S));
+      : "=v"(f.t)
+      : "v"(f.m), "v"(S));
+  return f;
+}
+// run + f of entry E, begun in s; begins the entry En in s
+__device__ __forceinline__ uint32_t freq_next(uint32_t run, FreqStep& s, uint32_t E, uint32_t En, uint32_t S,
+                                              uint32_t K) {
+  FreqStep n;
+  uint32_t o;
+  const uint32_t p = __umul24(E & 0xFFFFu, 65281u);
+  asm("v_cmp_le_u32_e32 vcc, %3, %4\n\t"
+      "v_mad_u32_u24 %1, %5, %6, %7\n\t"
+      "v_mul_u32_u24_sdwa %2, %1, %8 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_addc_co_u32_sdwa %0, vcc, %9, %10, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+      : "=v"(o), "=&v"(n.m), "=&v"(n.t)
+      : "v"(s.t), "v"(p), "v"(En), "v"(K), "s"(0x10000), "v"(S), "v"(run), "v"(s.m)
+      : "vcc");
+  s = n;
+  return o;
+}
+// run + f of the last entry E, begun in s
+__device__ __forceinline__ uint32_t freq_last(uint32_t run, const FreqStep& s, uint32_t E) {
+  uint32_t o;
   const uint32_t p = __umul24(E & 0xFFFFu, 65281u);
   asm("v_cmp_le_u32_e32 vcc, %1, %2\n\t"
+      "s_nop 1\n\t"
       "v_addc_co_u32_sdwa %0, vcc, %3, %4, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
       : "=v"(o)
-      : "v"(t), "v"(p), "v"(run), "v"(m)
+      : "v"(s.t), "v"(p), "v"(run), "v"(s.m)
       : "vcc");
   return o;
+}
+__device__ __forceinline__ uint32_t freq_of(uint32_t E, uint32_t S, uint32_t K) {
+  return freq_last(0u, freq_begin(E, S, K), E);
 }
 
 // Reductions over the lanes of a node.  Both forms join the four lane groups
@@ -1275,9 +1305,11 @@ __device__ __forceinline__ void row_prefix(int (&e)[SMALL ? 16 : 64], const Node
                                            uint32_t& p1, uint32_t& R) {
   constexpr int NS = SMALL ? 16 : 64;
   uint32_t run = 0;
+  FreqStep fs = freq_begin((uint32_t)e[0], n.S, n.K);
 #pragma unroll
   for (int j = 0; j < NS; j++) {
-    const uint32_t next = freq_add(run, (uint32_t)e[j], n.S, n.K);
+    const uint32_t next = j + 1 < NS ? freq_next(run, fs, (uint32_t)e[j], (uint32_t)e[(j + 1) % NS], n.S, n.K)
+                                     : freq_last(run, fs, (uint32_t)e[j]);
     e[j] = (int)run;
     run = next;
   }
@@ -1311,7 +1343,7 @@ __device__ __forceinline__ v4i row_chunk(const int (&e)[NS], int c, int ablk, ui
 // smaller table entry gives a smaller frequency: the table falls by at least
 // 1984 of 32768 from entry 0 to 1, and S < 2^23).
 __device__ __forceinline__ void row_remainder(uint32_t* p, const NodeSum& n, uint32_t R) {
-  const uint32_t fmax = freq_add(0u, 32768u, n.S, n.K) & 0xFFFFu;
+  const uint32_t fmax = freq_of(32768u, n.S, n.K) & 0xFFFFu;
   const uint32_t lo = p[0], hi = p[1];
   const uint32_t v0 = lo & 0xFFFFu, v1 = lo >> 16, v2 = hi & 0xFFFFu, v3 = hi >> 16;
   const bool a0 = ((v1 - v0) & 0xFFFFu) == fmax;
@@ -1402,6 +1434,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
       // the lanes before it add their totals.
       const int sord = sym / NS, sblk = n.ord == sord ? (sym % NS) / 4 : -1;
       uint32_t run = 0, runb = 0, rlast = 0;
+      FreqStep fs = freq_begin((uint32_t)e[0], n.S, n.K);
 #pragma unroll
       for (int b = 0; b < NBL; b++) {
         if (b == sblk) {
@@ -1410,8 +1443,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
         }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          if (4 * b + i == NS - 1) rlast = run;
-          run = freq_add(run, (uint32_t)e[4 * b + i], n.S, n.K);
+          const int j = 4 * b + i;
+          if (j == NS - 1) rlast = run;
+          run = j + 1 < NS ? freq_next(run, fs, (uint32_t)e[j], (uint32_t)e[(j + 1) % NS], n.S, n.K)
+                           : freq_last(run, fs, (uint32_t)e[j]);
         }
       }
       const uint32_t tot = n.tail ? rlast : run;
@@ -1425,7 +1460,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
         bool lower = false, here = false;  // the maximum lies at a lower entry of the block / at the symbol
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          const uint32_t f = freq_add(0u, (uint32_t)es[i], n.S, n.K);
+          const uint32_t f = freq_of((uint32_t)es[i], n.S, n.K);
           st += i < si ? f : 0u;
           fr = i == si ? f : fr;
           lower = lower || (i < si && es[i] == 32768);
