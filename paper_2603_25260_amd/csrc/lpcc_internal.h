@@ -64,10 +64,11 @@ __device__ __forceinline__ int requant_l(int acc, const LayerDev& L) {
 // term, f_rnd = rnd + z_out 2^r (floor((x + z 2^r) / 2^r) = floor(x / 2^r) +
 // z); and where the outputs at f_lo and f_hi are inside int8 already, so are
 // all between them and the final clamp falls away.  The host checks all of it
-// (requant_fast).
+// (requant_fast).  The sum stays inside int32; with a negative zero point the
+// product alone may not, so both are taken modulo 2^32.
 __device__ __forceinline__ int requant_f(int acc, const LayerDev& L) {
   const int a = min(max(acc, L.f_lo), L.f_hi);
-  return (__mul24(a, L.f_m) + L.f_rnd) >> L.r;
+  return (int)((uint32_t)__mul24(a, L.f_m) + (uint32_t)L.f_rnd) >> L.r;
 }
 
 // The same function scaled by 2^24 (rqt): multiplier(s) and rounding term are
