@@ -393,7 +393,7 @@ int lpcc_ctx_set_kmap_mode(lpcc_ctx* c, int mode);
 int lpcc_softmax_table(int32_t* out);
 
 /*
- * The form in which the kernels evaluate one layer's requantisation (Eq. 14):
+ * The general form in which the kernels evaluate one layer's requantisation (Eq. 14):
  * q(a) = ((a m + 2^(r-1)) >> r) + z_out, m = m_pos for a >= 0 else m_neg,
  * clamped to [-128, 127].  The kernels clamp the int32 accumulator to
  * [a_lo, a_hi] first: a_hi is the smallest a >= 0 with q(a) >= 127 (INT32_MAX
@@ -402,11 +402,24 @@ int lpcc_softmax_table(int32_t* out);
  * multiplier above 256 is replaced by 256 (the same function).
  * out[0..4] = {m_pos, m_neg, a_lo, a_hi, rq24} as used, where rq24 = 1 when
  * a m + 2^(r-1) over the clamped range is an exact 24-bit signed
- * multiply-add inside int32 (the kernels then skip the 64-bit product); host
- * memory (5 int32), needs no device.  LPCC_E_INVAL for parameters a weight blob may not hold (negative
- * multipliers, r outside [0, 62], z_out outside int8).
+ * multiply-add inside int32 (a property of the parameters; lpcc_requant_fast
+ * says where the kernels skip the 64-bit product); host memory (5 int32),
+ * needs no device.  LPCC_E_INVAL for parameters a weight blob may not hold
+ * (negative multipliers, r outside [0, 62], z_out outside int8).
  */
 int lpcc_requant_bounds(int32_t m_pos, int32_t m_neg, int r, int z_out, int32_t* out);
+
+/*
+ * The forms of the same function that take one 24-bit multiply-add, and
+ * whether the kernels use them for these parameters.  out[0..8] = {rqf, rqt,
+ * f_lo, f_hi, f_m, f_rnd, t_m, t_mn, t_rnd}; with a' the accumulator clamped
+ * to [f_lo, f_hi] and sums modulo 2^32:
+ *   rqf = 1:  q(a) = (a' f_m + f_rnd) >> r           (predictor layers);
+ *   rqt != 0: q(a) = (a' t + t_rnd) >> 24, t = t_m, with rqt = 2 t_mn for a'
+ *             below 0                                (sparse and dense layers).
+ * Host memory (9 int32), needs no device; the errors of lpcc_requant_bounds.
+ */
+int lpcc_requant_fast(int32_t m_pos, int32_t m_neg, int r, int z_out, int32_t* out);
 
 #ifdef __cplusplus
 }

@@ -187,8 +187,9 @@ int64_t requant_q(int64_t a, int64_t m, int r, int z) {
   return ((a * m + rnd) >> r) + z;
 }
 
-// Whether a m + rnd is an exact 24-bit signed multiply-add inside int32 over
-// the clamped range: on each side of 0 either the multiplier is 0 (any
+// lpcc_requant_bounds' rq24 (the kernels' own condition is requant_fast's):
+// whether a m + rnd is an exact 24-bit signed multiply-add inside int32 over
+// the clamped range, on each side of 0 either the multiplier is 0 (any
 // truncation of a times 0 is 0) or |a| and m are below 2^23 and a m + rnd
 // stays in [-2^31, 2^31) (rnd >= 0 moves negative products towards 0).
 bool requant_fits24(int32_t m_pos, int32_t m_neg, int32_t a_lo, int32_t a_hi, int64_t rnd) {
@@ -260,6 +261,19 @@ void requant_fast(LayerDev& F) {
   F.t_mn = (int32_t)(F.m_neg * up);
   F.t_rnd = (int32_t)(rnd * up);
   F.rqt = single ? 1 : 2;
+}
+
+// a layer's requantisation as the kernels read it
+void set_requant(LayerDev& F, int32_t m_pos, int32_t m_neg, int r, int z_out) {
+  const RqBounds B = requant_bounds(m_pos, m_neg, r, z_out);
+  F.m_pos = B.m_pos;
+  F.m_neg = B.m_neg;
+  F.a_lo = B.a_lo;
+  F.a_hi = B.a_hi;
+  F.r = r;
+  F.z_out = z_out;
+  F.rnd = r > 0 ? (1ll << (r - 1)) : 0;
+  requant_fast(F);
 }
 
 // Frequencies of a base depth from the counts n_s of its 255 codes (the
@@ -2764,20 +2778,12 @@ int lpcc_model_load(const void* blob, size_t len, int device, lpcc_model** out) 
     D.zc = im[i].zc.empty() ? nullptr : (const int32_t*)put(im[i].zc.data(), im[i].zc.size() * 4);
     D.biasz = im[i].biasz.empty() ? D.bias : (const int32_t*)put(im[i].biasz.data(), im[i].biasz.size() * 4);
     D.z_in = L.z_in;
-    const RqBounds rq = requant_bounds(L.m_pos, L.m_neg, L.r, L.z_out);
-    D.m_pos = rq.m_pos;
-    D.m_neg = rq.m_neg;
-    D.a_lo = rq.a_lo;
-    D.a_hi = rq.a_hi;
-    D.r = L.r;
-    D.z_out = L.z_out;
+    set_requant(D, L.m_pos, L.m_neg, L.r, L.z_out);
     D.taps = L.taps;
     D.cin = L.cin;
     D.cout = L.cout;
     D.ksteps = im[i].ksteps;
     D.npad = im[i].npad;
-    D.rnd = L.r > 0 ? (1ll << (L.r - 1)) : 0;
-    requant_fast(D);
   }
   int32_t lut[256];
   softmax_table(lut);
@@ -3084,6 +3090,16 @@ int lpcc_requant_bounds(int32_t m_pos, int32_t m_neg, int r, int z_out, int32_t*
   out[2] = B.a_lo;
   out[3] = B.a_hi;
   out[4] = requant_fits24(B.m_pos, B.m_neg, B.a_lo, B.a_hi, r > 0 ? (1ll << (r - 1)) : 0) ? 1 : 0;
+  return LPCC_OK;
+}
+
+int lpcc_requant_fast(int32_t m_pos, int32_t m_neg, int r, int z_out, int32_t* out) {
+  if (!out || m_pos < 0 || m_neg < 0 || r < 0 || r > 62 || z_out < -128 || z_out > 127) return LPCC_E_INVAL;
+  LayerDev F;
+  memset(&F, 0, sizeof(F));
+  set_requant(F, m_pos, m_neg, r, z_out);
+  const int32_t v[9] = {F.rqf, F.rqt, F.f_lo, F.f_hi, F.f_m, F.f_rnd, F.t_m, F.t_mn, F.t_rnd};
+  memcpy(out, v, sizeof(v));
   return LPCC_OK;
 }
 

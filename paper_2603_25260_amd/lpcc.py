@@ -82,6 +82,7 @@ def lib():
                                        ctypes.POINTER(i64)]
         L.lpcc_softmax_table.argtypes = [vp]
         L.lpcc_requant_bounds.argtypes = [i32, i32, i32, i32, vp]
+        L.lpcc_requant_fast.argtypes = [i32, i32, i32, i32, vp]
         L.lpcc_ctx_set_tiling.argtypes = [vp, i32]
         L.lpcc_ctx_set_base_depth.argtypes = [vp, i32]
         L.lpcc_ctx_set_kmap_mode.argtypes = [vp, i32]
@@ -129,11 +130,19 @@ def softmax_table() -> np.ndarray:
 
 
 def requant_bounds(m_pos: int, m_neg: int, r: int, z_out: int):
-    """(m_pos, m_neg, a_lo, a_hi, rq24) of a requantisation as the kernels
-    use it (host computation)."""
+    """(m_pos, m_neg, a_lo, a_hi, rq24) of a requantisation in the kernels'
+    general form (host computation)."""
     out = np.zeros(5, np.int32)
     _check(lib().lpcc_requant_bounds(m_pos, m_neg, r, z_out, out.ctypes.data))
     return tuple(int(v) for v in out)
+
+
+def requant_fast(m_pos: int, m_neg: int, r: int, z_out: int):
+    """The kernels' single-multiply-add forms of a requantisation: a dict of
+    rqf, rqt, f_lo, f_hi, f_m, f_rnd, t_m, t_mn, t_rnd (host computation)."""
+    out = np.zeros(9, np.int32)
+    _check(lib().lpcc_requant_fast(m_pos, m_neg, r, z_out, out.ctypes.data))
+    return dict(zip(("rqf", "rqt", "f_lo", "f_hi", "f_m", "f_rnd", "t_m", "t_mn", "t_rnd"), map(int, out)))
 
 
 W_NO_XFP, W_ZERO_POINTS, W_SHARED = 1, 2, 4
