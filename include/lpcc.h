@@ -199,10 +199,12 @@ int lpcc_level_probs(lpcc_ctx* c, const lpcc_model* m, const int32_t* xyz, int64
 /*
  * Depth and point count from the first 16 bytes of a stream (host memory
  * only; the stream layout above).  max_workspace (may be NULL): device
- * workspace bytes a fresh context needs to decode this stream with any model
- * it may have been made with (C <= 64), computed from the depth counts, so it
- * needs len >= 16 + 4 D (base-geometry streams: their tables too); with fewer
- * bytes it is 0.  Errors: LPCC_E_INVAL (null), LPCC_E_CORRUPT (bad header).
+ * workspace bytes in which a fresh context can decode this stream with any
+ * model it may have been made with (C <= 64); an upper bound, with 512 bytes
+ * per node of the largest depth that the decode does not hold.  It is computed
+ * from the depth counts, so it needs len >= 16 + 4 D (base-geometry streams:
+ * their tables too); with fewer bytes it is 0.  Errors: LPCC_E_INVAL (null),
+ * LPCC_E_CORRUPT (bad header).
  */
 int lpcc_peek_header(const uint8_t* bs, size_t len, int* D, int64_t* n_points, size_t* max_workspace);
 

@@ -414,8 +414,10 @@ hipError_t launch_keys_to_xyz(XyzFrames& X, hipStream_t s);
 // calls use, and the serving engine's hooks into a context.
 // ---------------------------------------------------------------------------
 void encode_workspace_bound(const lpcc_model* m, int nf, const int64_t* n, int cl, bool host_in, size_t out[3]);
-// N[f]: the D + 1 node counts of stream f (its header), cl[f] its chunk size
-void decode_workspace_bound(const lpcc_model* m, int nf, const int64_t* const* N, const int* cl, size_t out[3]);
+// N[f]: the D + 1 node counts of stream f (its header), cl[f] its chunk size,
+// base[f] its base depth
+void decode_workspace_bound(const lpcc_model* m, int nf, const int64_t* const* N, const int* cl, const int* base,
+                            size_t out[3]);
 void ctx_caps(const lpcc_ctx* c, size_t caps[3]);
 void ctx_set_budget(lpcc_ctx* c, size_t budget);
 void ctx_trim(lpcc_ctx* c);  // frees the arenas (the context stays usable)

@@ -2297,9 +2297,11 @@ void carve_decode(Arena& A, const lpcc_model* m, const Frames& fr, size_t paybyt
   carve_model(A, m, fr, D - 1, wanted, B, nb);
 }
 
-// Arenas a decode of one stream needs, from its depth counts (`N`, D + 1
-// entries), base depth and chunk size.  A chunk's payload is at most two
-// bytes per symbol (every renormalisation emits at most two) and the flush.
+// Arenas that hold a decode of one stream, from its depth counts (`N`, D + 1
+// entries), base depth and chunk size, with room for the CDF rows of its
+// largest depth whatever the base depth (what lpcc_peek_header reports).  A
+// chunk's payload is at most two bytes per symbol (every renormalisation emits
+// at most two) and the flush.
 void decode_workspace(const lpcc_model* m, const int64_t* N, int nb, int cl, size_t out[3]) {
   const int D = m->D;
   Frames fr;
@@ -2327,37 +2329,42 @@ void decode_workspace(const lpcc_model* m, const int64_t* N, int nb, int cl, siz
 }  // namespace
 
 void lpcc::decode_workspace_bound(const lpcc_model* m, int nf, const int64_t* const* N, const int* cl,
-                                  size_t out[3]) {
-  const int D = m->D;
-  Frames fr;
-  fr.nf = nf;
-  fr.tot.assign(D + 1, 0);
-  fr.N.assign(nf, std::vector<int64_t>(D + 1, 0));
-  fr.off.assign(nf, std::vector<int64_t>(D + 1, 0));
-  std::vector<size_t> dch(D, 0);
-  size_t nch = 0, pay = 0;
-  for (int f = 0; f < nf; f++)
-    for (int d = 0; d <= D; d++) {
-      fr.N[f][d] = N[f][d];
-      fr.off[f][d] = fr.tot[d];
-      fr.tot[d] += N[f][d];
-      if (d < D) {
-        const size_t k = (size_t)nchunks_of(N[f][d], cl[f]);
-        dch[d] += k;
-        nch += k;
-        pay += 2 * (size_t)N[f][d] + 8 * k + 16;
+                                  const int* base, size_t out[3]) {
+  for (int i = 0; i < 3; i++) out[i] = 0;
+  // a call whose streams differ in base depth decodes them one at a time
+  const bool alike = std::all_of(base, base + nf, [&](int b) { return b == base[0]; });
+  for (int f0 = 0; f0 < nf; f0 += alike ? nf : 1) {
+    const int k = alike ? nf : 1;
+    const int D = m->D, nb = std::min(base[f0], m->k0);  // deeper ones are refused
+    Frames fr;
+    fr.nf = k;
+    fr.tot.assign(D + 1, 0);
+    fr.N.assign(k, std::vector<int64_t>(D + 1, 0));
+    fr.off.assign(k, std::vector<int64_t>(D + 1, 0));
+    std::vector<size_t> dch(D, 0);
+    size_t nch = 0, pay = 0;
+    for (int f = 0; f < k; f++)
+      for (int d = 0; d <= D; d++) {
+        fr.N[f][d] = N[f0 + f][d];
+        fr.off[f][d] = fr.tot[d];
+        fr.tot[d] += fr.N[f][d];
+        if (d < D) {
+          const size_t c = (size_t)nchunks_of(fr.N[f][d], cl[f0 + f]);
+          dch[d] += c;
+          nch += c;
+          pay += 2 * (size_t)fr.N[f][d] + 8 * c + 16;
+        }
       }
-    }
-  size_t maxch = 0;
-  for (int d = 0; d < D; d++) maxch = std::max(maxch, dch[d]);
-  Levels lv;
-  ModelBufs B;
-  DecBufs db;
-  Arena a;
-  carve_decode(a, m, fr, align_up(pay, 16), maxch, true, 0, lv, B, db, D + 1);
-  out[0] = 0;
-  out[1] = a.off + 4096;
-  out[2] = desc_bound(fr, nch);
+    size_t maxch = 0;
+    for (int d = 0; d < D; d++) maxch = std::max(maxch, dch[d]);
+    Levels lv;
+    ModelBufs B;
+    DecBufs db;
+    Arena a;
+    carve_decode(a, m, fr, align_up(pay, 16), maxch, true, nb, lv, B, db, nb);
+    out[1] = std::max(out[1], a.off + 4096);
+    out[2] = std::max(out[2], desc_bound(fr, nch));
+  }
 }
 
 void lpcc::ctx_caps(const lpcc_ctx* c, size_t caps[3]) {

@@ -42,6 +42,7 @@ struct Pending {
   int64_t points;            // encode: input points; decode: points in the stream header
   std::vector<int64_t> N;    // decode: node counts of every depth (header)
   int cl = 8;                // decode: chunk size of the stream
+  int base = 0;              // decode: base depth of the stream
   bool host_in = false;      // encode: coordinates in host memory (staged)
   size_t need[3] = {0, 0, 0};  // workspace bound of the job alone (per arena)
 };
@@ -88,12 +89,13 @@ void bound_of(lpcc_server* S, const std::vector<const Pending*>& b, size_t need[
     lpcc::encode_workspace_bound(m, (int)b.size(), n.data(), b[0]->job.chunk_log2, host, need);
   } else {
     std::vector<const int64_t*> N;
-    std::vector<int> cl;
+    std::vector<int> cl, base;
     for (auto* p : b) {
       N.push_back(p->N.data());
       cl.push_back(p->cl);
+      base.push_back(p->base);
     }
-    lpcc::decode_workspace_bound(m, (int)b.size(), N.data(), cl.data(), need);
+    lpcc::decode_workspace_bound(m, (int)b.size(), N.data(), cl.data(), base.data(), need);
   }
 }
 
@@ -328,9 +330,9 @@ int lpcc_server_submit(lpcc_server* S, const lpcc_job* job, uint64_t* ticket) {
     p.points = job->n_points;
     p.host_in = !dev;
   } else {
-    // depth counts from the stream header (host streams directly, device
-    // ones by copy): they bound the decode's workspace
-    uint8_t h[16 + 4 * lpcc::kMaxD];
+    // depth counts and base depth from the stream header (host streams
+    // directly, device ones by copy): they bound the decode's workspace
+    uint8_t h[16 + 4 * lpcc::kMaxD + 1];
     if (job->in_len < 16) return LPCC_E_CORRUPT;
     const size_t nh = std::min(job->in_len, sizeof(h));
     if (dev) {
@@ -348,6 +350,7 @@ int lpcc_server_submit(lpcc_server* S, const lpcc_job* job, uint64_t* ticket) {
     if (D != mD || nh < 16 + 4 * (size_t)D) return LPCC_E_CORRUPT;
     p.points = np;
     p.cl = h[7];
+    p.base = h[4] == 2 && nh > 16 + 4 * (size_t)D ? h[16 + 4 * (size_t)D] : 0;
     if (p.cl < 4 || p.cl > 14) return LPCC_E_CORRUPT;
     p.N.assign(D + 1, 0);
     auto rd = [&](size_t o) {
