@@ -1602,8 +1602,10 @@ __device__ __forceinline__ void put_lane(uint32_t& v, uint32_t s, int k) {
   asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(s), "n"(k));
 }
 
+// Three waves per SIMD: LDS holds four blocks of NP = 2 (36 KB and the payload
+// each) per compute unit, and the predictor takes 129 to 138 registers here.
 template <int C, int NP, int RQ>
-__global__ __launch_bounds__(64 * (NP + 1)) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4 : 3))) void k_decode_chunks(
+__global__ __launch_bounds__(64 * (NP + 1)) __attribute__((amdgpu_waves_per_eu(3))) void k_decode_chunks(
     const Chunk* __restrict__ chunks, const uint8_t* __restrict__ payload, const int32_t* __restrict__ lut_g,
     const DecArg A, uint8_t* __restrict__ codes, uint32_t* __restrict__ csum, uint32_t* __restrict__ err,
     int pay_words) {

@@ -7,7 +7,8 @@ but does not look inside inline assembly, so its listing is checked as a whole:
 * a vector register written by a vector instruction and read across lanes by
   DPP: 2; by a lane read: 1.
 
-Every instruction in between counts one, ``s_nop n`` n + 1."""
+Every instruction in between counts one, ``s_nop n`` n + 1.  And the occupancy
+that a kernel's attributes state is one its registers allow."""
 import concurrent.futures
 import os
 import re
@@ -87,7 +88,7 @@ def _asm(src, out):
     cmd = [B.HIPCC, *flags, "--cuda-device-only", "-S", "-o", out, os.path.join(B.CSRC, src)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    return open(out).read()
+    return open(out).read(), r.stderr
 
 
 @pytest.fixture(scope="module")
@@ -102,10 +103,16 @@ def asm():
 
 @pytest.mark.parametrize("src", KERNEL_SOURCES)
 def test_dependent_vector_instructions_keep_their_distance(asm, src):
-    kernels = re.findall(r"^(_Z\w+):(.*?)^\.Lfunc_end\d+:", asm[src], re.S | re.M)
+    kernels = re.findall(r"^(_Z\w+):(.*?)^\.Lfunc_end\d+:", asm[src][0], re.S | re.M)
     assert kernels
     bad = [(name, *v) for name, body in kernels for v in violations(body)]
     assert not bad, (len(bad), bad[:5])
+
+
+@pytest.mark.parametrize("src", KERNEL_SOURCES)
+def test_stated_occupancy_is_reached(asm, src):
+    missed = [line for line in asm[src][1].split("\n") if "failed to meet occupancy target" in line]
+    assert not missed, missed[:3]
 
 
 @pytest.mark.parametrize("body,n", [
