@@ -302,7 +302,8 @@ int lpcc_timing_read(lpcc_ctx* c, int64_t* launches, double* total_ms, int64_t* 
  * on the present taps of a wave's rows or the occupied children of a block's
  * parents, and a dense one over every tap or child slot (absent ones
  * contribute zeros); the child convolution works on every slot, with a choice
- * of parents per block.  A wave computes rb blocks of 16 rows.  rb = 0 (the
+ * of parents per block (a fixed tiling takes it from the rows of the launch).
+ * A wave computes rb blocks of 16 rows.  rb = 0 (the
  * default) autotunes: the first launch of every (kernel, widths, log2 rows)
  * class on this context runs each candidate, timed with HIP events on the
  * context's stream, and later launches of the class use the fastest.  rb =

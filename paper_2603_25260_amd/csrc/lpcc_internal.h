@@ -337,8 +337,8 @@ hipError_t launch_up(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int 
 // the same over the occupied children only; tiles of 64 one.tpw parents
 hipError_t launch_up_slots(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
                            hipStream_t s);
-// the largest tiles of the child-slot kernels serve a launch that has this many
-// of them, the smallest any other (more blocks in flight)
+// the upsampling's large tiles serve a launch that has this many of them, the
+// small ones any other (more blocks in flight)
 constexpr int kSlotTileBlocks = 512;
 // rows of the codes through a table in LDS (every segment with codes); tiles of kEmbRows
 constexpr int kEmbRows = 2048;

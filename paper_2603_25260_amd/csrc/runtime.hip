@@ -723,6 +723,7 @@ int64_t count_tiles(const std::vector<int64_t>& rows, int rows_per_tile = 64) {
 // Upsampling: 201 / 202 (occupied children, 256 / 1024 parents per block) or
 // 210 + rb (all child slots of every parent).
 constexpr int kUpSmall = 256, kUpLarge = 1024;
+constexpr int kCUs = 256;  // compute units of the device
 struct Variant {
   int code, tile_rows;
 };
@@ -742,8 +743,16 @@ Variant fixed_variant(bool up, int mode, int tiling, int64_t rows) {
     return count_tiles({rows}, kUpLarge) >= kSlotTileBlocks ? Variant{202, kUpLarge} : Variant{201, kUpSmall};
   }
   if (mode == G_DOWN) {
-    if (dense) return {tiling + 100, 128 * rb};
-    return count_tiles({rows}, 1024) >= kSlotTileBlocks ? Variant{102, 1024} : Variant{101, 64};
+    // The most parents per block that leave every compute unit a block: a wave
+    // loads the whole layer (32 KB at C = 64) before its first parent, so the
+    // more parents follow the better.  The child convolutions of one 128-beam
+    // frame (18 levels, C = 64): encode 0.115 ms, decode 0.163 ms; with 64
+    // parents below 524288 rows 0.148 and 0.284 ms, and from 512 blocks on
+    // 0.117 and 0.175 ms.  8 such frames: 0.81 and 0.79 ms, with 128 parents
+    // throughout 1.36 and 1.26 ms.
+    for (const Variant& v : {Variant{102, 1024}, Variant{114, 512}, Variant{112, 256}, Variant{111, 128}})
+      if (count_tiles({rows}, v.tile_rows) >= kCUs) return v;
+    return {101, 64};
   }
   if (mode == G_CONV) return {tiling, dense ? 16 * rb : 64 * rb};
   return {rb, 64 * rb};
