@@ -196,6 +196,7 @@ struct GemmArg {
   int32_t fl;     // flavour of the sparse and dense layers' kernels (model.hip)
   int32_t tpw;    // down and up: parents per block / 64
   int32_t table;  // down: every segment reads its children through ccode
+  int32_t all;    // conv: every tap, present or not
 };
 struct PredArg {
   PredSeg seg;

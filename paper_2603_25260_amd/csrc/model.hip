@@ -214,6 +214,7 @@ __global__ __launch_bounds__(256) void k_conv(const GemmSeg* __restrict__ segs, 
   int tapof = 0;
   if (MODE == G_CONV) {
     if (lane < WR && myrow < S.rows) U = (uint32_t)gp(S.kmap)[27 * S.kstride + myrow];
+    if (A.all) U = (1u << 27) - 1u;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) U |= (uint32_t)__shfl_xor((int)U, o);
     U = (uint32_t)__builtin_amdgcn_readfirstlane((int)U);

@@ -724,6 +724,7 @@ int64_t count_tiles(const std::vector<int64_t>& rows, int rows_per_tile = 64) {
 // 210 + rb (all child slots of every parent).
 constexpr int kUpSmall = 256, kUpLarge = 1024;
 constexpr int kCUs = 256;  // compute units of the device
+constexpr int kDenseTiles = 2 * kCUs;
 struct Variant {
   int code, tile_rows;
 };
@@ -754,7 +755,12 @@ Variant fixed_variant(bool up, int mode, int tiling, int64_t rows) {
       if (count_tiles({rows}, v.tile_rows) >= kCUs) return v;
     return {101, 64};
   }
-  if (mode == G_CONV) return {tiling, dense ? 16 * rb : 64 * rb};
+  // Every tap: a block's waves share the taps of 16 rb rows, until blocks of 64
+  // rb rows with all taps in each wave fill the chip twice (their weights are
+  // then read once for 64 rb rows).  The convolutions of 8 128-beam frames (18
+  // levels, C = 64), rb = 1 / 2 / 4: 8.5 / 5.3 / 3.9 ms, shared 9.0 / 6.4 / 8.0
+  // ms; a frame's decode, rb = 4: 0.89 ms, 1.18 ms from four times the chip on.
+  if (mode == G_CONV) return {tiling, dense && count_tiles({rows}, 64 * rb) < kDenseTiles ? 16 * rb : 64 * rb};
   return {rb, 64 * rb};
 }
 hipError_t launch_variant(const Variant& v, bool up, int mode, int cin, int cout, const GemmSeg* S, const Tile* T,
@@ -768,8 +774,10 @@ hipError_t launch_variant(const Variant& v, bool up, int mode, int cin, int cout
   }
   if (mode == G_DOWN) return launch_down(cout, S, T, nt, one, st);
   if (mode == G_DENSE) return launch_dense(cin, cout, S, T, nt, one, code, st);
-  if (code > 10) return launch_conv_split(cin, cout, S, T, nt, one, code - 10, st);
-  return launch_conv(cin, cout, S, T, nt, one, code, st);
+  const int rb = code % 10;
+  if (code > 10 && v.tile_rows == 16 * rb) return launch_conv_split(cin, cout, S, T, nt, one, rb, st);
+  one.all = code > 10;
+  return launch_conv(cin, cout, S, T, nt, one, rb, st);
 }
 
 hipError_t tune_event(lpcc_ctx* c, hipEvent_t* e) {

@@ -33,7 +33,7 @@ def test_fixed_tiling_at_block_size_edges(L, n, C, zp):
     want = torch.zeros((len(xyz), 256), dtype=torch.int32, device="cuda")
     got = torch.zeros_like(want)
     k = L.level_probs(L.Context(0), m, dx, D - 1, out=want)
-    for tiling in (2, 11):
+    for tiling in (2, 11, 12, 14):
         ctx = L.Context(0)
         ctx.set_tiling(tiling)
         got.zero_()
