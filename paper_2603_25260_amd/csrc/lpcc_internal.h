@@ -245,8 +245,8 @@ enum : uint32_t { ERR_COORD = 1u, ERR_CORRUPT = 2u, ERR_COUNT = 4u, ERR_ACC = 8u
 // ---------------------------------------------------------------------------
 // Morton keys and their LSD radix sort (Sec. S3.2: coordinates sorted in
 // Morton order), on bits [0, end_bit).  Small sorts (tile > 0): passes of at
-// most kSortBits bits, hist is [2^kSortBits][64] counts of the current pass
-// (bin, tile) and [2^kSortBits] counts of all keys.  Large ones: passes of at
+// most kSortBits bits, hist is [2^bits][sort_stride] counts of the current pass
+// (bin, tile) and [2^bits] counts of all keys.  Large ones: passes of at
 // most 8 bits, tiles of kSortTile keys, hist is [passes][tiles][256] per-tile
 // digit counts and totals [passes][256] digit counts of all keys (both zeroed
 // first).
@@ -262,6 +262,7 @@ struct SortPasses {
   int32_t bits[8];
 };
 SortPasses sort_passes(int64_t n, int end_bit);
+int sort_stride(int64_t n, int tile);
 struct MortonFrames {
   const int32_t* xyz[kMortonGroup];  // device coordinates of each frame
   int64_t start[kMortonGroup + 1];   // key range of each frame (start[nf] = end)

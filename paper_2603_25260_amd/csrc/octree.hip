@@ -64,6 +64,15 @@ SortPasses sort_passes(int64_t n, int end_bit) {
   return sp;
 }
 
+// words between the counts of two digits of a small sort: a power of two, so
+// that a digit's counts share as few cache lines with others' as they can (a
+// 64-beam frame's encode: 488 and 491 us with 64 words, 499 and 500 us with 58)
+int sort_stride(int64_t n, int tile) {
+  int s = 1;
+  while ((int64_t)s * tile < n) s *= 2;
+  return s;
+}
+
 __device__ __forceinline__ uint32_t digit_of(uint64_t key, int shift, int bits) {
   return (uint32_t)(key >> shift) & ((1u << bits) - 1u);
 }
@@ -142,11 +151,11 @@ hipError_t launch_morton_sort0(const MortonFrames& mf, int D, uint64_t* keys, ui
   return hipGetLastError();
 }
 
-// Small sorts, digit counts of one pass: hist[bin][64 tiles] over tiles of 256
-// x ITEMS keys.
+// Small sorts, digit counts of one pass: hist[bin][stride] over tiles of 256 x
+// ITEMS keys.
 template <int ITEMS>
 __global__ __launch_bounds__(256) void k_sort_count_few(const uint64_t* __restrict__ kin, int64_t n, int shift,
-                                                        int bits, uint32_t* __restrict__ hist) {
+                                                        int bits, uint32_t* __restrict__ hist, int stride) {
   __shared__ uint32_t h[1 << kSortBits];
   const int nb = 1 << bits;
   uint64_t key[ITEMS];
@@ -163,18 +172,18 @@ __global__ __launch_bounds__(256) void k_sort_count_few(const uint64_t* __restri
     if (i < n) atomicAdd(&h[digit_of(key[k], shift, bits)], 1u);
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < nb; b += 256) gp(hist)[64 * b + blockIdx.x] = h[b];
+  for (int b = threadIdx.x; b < nb; b += 256) gp(hist)[stride * b + blockIdx.x] = h[b];
 }
 
 // Small sorts: every bin's counts become the number of its keys in earlier
 // tiles, and totals[bin] the number in all.  A wave per bin, a lane per tile.
-__global__ __launch_bounds__(256) void k_sort_scan_few(uint32_t* __restrict__ hist, int ntiles, int nb,
+__global__ __launch_bounds__(256) void k_sort_scan_few(uint32_t* __restrict__ hist, int ntiles, int stride, int nb,
                                                        uint32_t* __restrict__ totals) {
   const int bin = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (bin >= nb) return;  // wave-uniform
-  const uint32_t c = lane < ntiles ? gp(hist)[64 * bin + lane] : 0u;
+  const uint32_t c = lane < ntiles ? gp(hist)[stride * bin + lane] : 0u;
   const uint32_t inc = wave_scan_incl(c);
-  gp(hist)[64 * bin + lane] = inc - c;
+  if (lane < ntiles) gp(hist)[stride * bin + lane] = inc - c;
   if (lane == 63) gp(totals)[bin] = inc;
 }
 
@@ -187,7 +196,7 @@ __global__ __launch_bounds__(256) void k_sort_scan_few(uint32_t* __restrict__ hi
 template <int ITEMS>
 __global__ __launch_bounds__(256) void k_sort_scatter_few(const uint64_t* __restrict__ kin,
                                                           uint64_t* __restrict__ kout, int64_t n, int shift, int bits,
-                                                          const uint32_t* __restrict__ hist,
+                                                          const uint32_t* __restrict__ hist, int stride,
                                                           const uint32_t* __restrict__ totals,
                                                           uint32_t* __restrict__ err) {
   constexpr int kBins = 1 << kSortBits;
@@ -207,7 +216,7 @@ __global__ __launch_bounds__(256) void k_sort_scatter_few(const uint64_t* __rest
   for (int j = 0; j < PT; j++) {
     const bool has = j < pt && tid * pt + j < nb;
     all[j] = has ? gp(totals)[tid * pt + j] : 0u;
-    before[j] = has ? gp(hist)[64 * (tid * pt + j) + blockIdx.x] : 0u;
+    before[j] = has ? gp(hist)[stride * (tid * pt + j) + blockIdx.x] : 0u;
   }
   for (int b = tid; b < 4 * kBins; b += 256) (&cnt[0][0])[b] = 0u;
   __syncthreads();
@@ -380,12 +389,12 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint64_t* __restrict
 template <int ITEMS>
 static hipError_t launch_few(const uint64_t* kin, uint64_t* kout, int64_t n, int shift, int bits, uint32_t* hist,
                              uint32_t* err, hipStream_t s) {
-  uint32_t* totals = hist + (64 << kSortBits);
-  const int nt = (int)((n + 256 * ITEMS - 1) / (256 * ITEMS));
-  hipLaunchKernelGGL((k_sort_count_few<ITEMS>), dim3(nt), dim3(256), 0, s, kin, n, shift, bits, hist);
-  hipLaunchKernelGGL(k_sort_scan_few, dim3(((1 << bits) + 3) / 4), dim3(256), 0, s, hist, nt, 1 << bits, totals);
+  const int nt = (int)((n + 256 * ITEMS - 1) / (256 * ITEMS)), stride = sort_stride(n, 256 * ITEMS);
+  uint32_t* totals = hist + ((size_t)stride << bits);
+  hipLaunchKernelGGL((k_sort_count_few<ITEMS>), dim3(nt), dim3(256), 0, s, kin, n, shift, bits, hist, stride);
+  hipLaunchKernelGGL(k_sort_scan_few, dim3(((1 << bits) + 3) / 4), dim3(256), 0, s, hist, nt, stride, 1 << bits, totals);
   hipLaunchKernelGGL((k_sort_scatter_few<ITEMS>), dim3(nt), dim3(256), 0, s, kin, kout, n, shift, bits,
-                     (const uint32_t*)hist, (const uint32_t*)totals, err);
+                     (const uint32_t*)hist, stride, (const uint32_t*)totals, err);
   return hipGetLastError();
 }
 

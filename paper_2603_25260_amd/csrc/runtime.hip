@@ -1414,9 +1414,15 @@ void carve_octree(Arena& A, const OctreeShape& S, Levels& lv, OctreeBufs& o) {
   o.totals = A.take<uint32_t>(D + 1);
   o.bhist = nbh ? A.take<uint32_t>(nbh) : nullptr;
   for (int d = 0; d <= D; d++) lv.code[d] = A.take<uint8_t>(align_up(S.ub[d], 4) + 4);
-  if (o.sp.tile) {  // a small sort counts without clearing
+  size_t counts_end = 0;
+  if (o.sp.tile) {
+    // a small sort counts without clearing, in the memory of the arrays that
+    // are written after it
     o.zero_hi = (char*)(lv.code[D] + align_up(S.ub[D], 4) + 4);
-    o.shist = A.take<uint32_t>((size_t)65 << kSortBits);
+    const size_t at = A.off;
+    o.shist = A.take<uint32_t>((size_t)(sort_stride(S.ntot, o.sp.tile) + 1) << o.sp.bits[0]);
+    counts_end = A.off;
+    A.off = at;
   } else {
     o.stot = A.take<uint32_t>((size_t)o.sp.n * 256);
     o.shist = A.take<uint32_t>((size_t)o.sp.n * std::max<int64_t>(o.sntiles, 1) * 256);
@@ -1426,6 +1432,7 @@ void carve_octree(Arena& A, const OctreeShape& S, Levels& lv, OctreeBufs& o) {
     lv.key[d] = A.take<uint64_t>(S.ub[d]);
     lv.cstart[d] = A.take<int32_t>(S.ub[d] + 1);
   }
+  A.off = std::max(A.off, counts_end);
 }
 
 OctreeShape octree_shape(int nf, const int64_t* n, int D, int base, bool need_stage) {
