@@ -725,6 +725,10 @@ int64_t count_tiles(const std::vector<int64_t>& rows, int rows_per_tile = 64) {
 constexpr int kUpSmall = 256, kUpLarge = kUpTile;
 constexpr int kCUs = 256;  // compute units of the device
 constexpr int kDenseTiles = 2 * kCUs;
+// Larger convolutions are not timed with the taps shared by a block: of some
+// twenty workloads (a 16-beam frame to 8 128-beam frames, C = 16 to 64) none
+// chose that from 131072 rows on, and tiles of 16 rows are many descriptors.
+constexpr int64_t kSharedTapRows = 131072;
 struct Variant {
   int code, tile_rows;
 };
@@ -1091,7 +1095,8 @@ void plan_gemm(Batch& b, const lpcc_model* m, const char* fam, int mode, int cin
     if (rec->best) {
       cands = {of_code(rec->best)};
     } else {
-      cands = all;
+      for (const Variant& v : all)
+        if (v.code < 10 || v.code > 100 || units < kSharedTapRows) cands.push_back(v);
       rec->ncand = (int)cands.size();
       for (size_t k = 0; k < cands.size(); k++) rec->cand[k] = cands[k].code;
     }
