@@ -336,8 +336,7 @@ hipError_t launch_down(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, in
 // upsampling, every slot of 16-parent blocks; tiles of 64 rb parents
 hipError_t launch_up(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
                      int rb, hipStream_t s);
-// the same over the occupied children only; tiles of 64 one.tpw parents, at most kUpTile
-constexpr int kUpTile = 1024;
+// the same over the occupied children only; tiles of 64 one.tpw parents
 hipError_t launch_up_slots(int C, const GemmSeg* segs_dev, const Tile* tiles_dev, int ntiles, const GemmArg& one,
                            hipStream_t s);
 // the upsampling's large tiles serve a launch that has this many of them, the

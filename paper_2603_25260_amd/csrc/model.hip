@@ -802,21 +802,21 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {  // set bits of m 
 // of one child.  No barrier: the waves share nothing but the caches (the same
 // parents' rows, and the two halves of an output line).  A list entry holds
 // all a group needs: the parent (10 bits), its code (8) and the child's row
-// relative to the block's first child (14; padding and children out of range
+// relative to the batch's first child (14; padding and children out of range
 // have the largest value, which is past the end of every output descriptor).
-// The inputs of three groups are in flight behind the products.
+// The inputs of three groups are in flight behind the products, and the codes
+// of the next batch (1024 parents) behind a batch's groups.
 //
 // Bound: memory and vector issue together (64-byte rows read and written: 1.1 ms
 // of the figure below without the arithmetic, 0.9 ms without the reads or
 // without the writes).  The 28 M children of 8 128-beam frames (18 levels, C =
 // 64) take 1.38 ms; a block's waves sharing one list of all slots, built
 // between barriers, with the weights reloaded at each change of slot, took 1.69
-// ms.  Tiles of 512 / 1024 / 2048 parents (the last in two lists): 1.39 / 1.38 /
-// 1.38 ms, and 1.44 / 1.46 / 1.57 ms in the smaller launches of a decode of the
-// same frames; tiles of 256 are for launches that would leave compute units
-// idle.
+// ms.  Tiles of 512 / 1024 / 2048 parents: 1.39 / 1.38 / 1.38 ms, and 1.44 /
+// 1.46 / 1.57 ms in the smaller launches of a decode of the same frames; tiles
+// of 256 are for launches that would leave compute units idle.
 constexpr uint32_t kNoChild = 0x3FFFu << 18;
-static_assert(kUpTile <= 1024, "a list entry has 10 bits for the parent, 14 for the child");
+constexpr int kUpBatch = 1024;
 
 template <int C, int FL>
 __global__ __launch_bounds__(512, 4) void k_up_slots(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
@@ -824,16 +824,16 @@ __global__ __launch_bounds__(512, 4) void k_up_slots(const GemmSeg* __restrict__
   constexpr int KS = (C + 8 + 63) / 64;
   constexpr int NBS = C / 16;          // column blocks per child slot
   constexpr int NBT = 8 * NBS;         // column blocks of the layer
-  constexpr int Q = kUpTile / 256;     // lane l holds parents 256 q + 4 l .. + 3
+  constexpr int Q = kUpBatch / 256;    // lane l holds parents 256 q + 4 l .. + 3
   static_assert(C == 16 || C == 32 || C == 64, "C");
-  __shared__ uint32_t lists[8][kUpTile + 16];
+  __shared__ uint32_t lists[8][kUpBatch + 16];
 
   GemmSeg S;
   LayerDev L;
-  const int p0 = pick_seg(segs, tiles, A, S, L, 64 * A.tpw);
+  int p0 = pick_seg(segs, tiles, A, S, L, 64 * A.tpw);
   const int o = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
-  const int np = min(S.rows - p0, 64 * A.tpw);
+  const int pend = min(S.rows, p0 + 64 * A.tpw);
   uint32_t* list = lists[o];
 
   v4i wb[KS][NBS], bb[NBS];
@@ -845,107 +845,113 @@ __global__ __launch_bounds__(512, 4) void k_up_slots(const GemmSeg* __restrict__
       for (int nb = 0; nb < NBS; nb++) wb[s][nb] = w[(s * NBT + nb) * 64];
     acc_bias<C>(bb, L.bias + o * C, g);
   }
-  // codes and first children of the lane's parents (the arrays are readable to
-  // a multiple of 16 bytes past a depth's last row)
+  // codes and first children of the lane's parents of the batch at p (the
+  // arrays are readable to a multiple of 16 bytes past a depth's last row)
   uint32_t code[Q];
   v4i first[Q];
-  {
-    const __amdgpu_buffer_rsrc_t bcode = rsrc_of(S.code + p0, (np + 3) & ~3);
-    const __amdgpu_buffer_rsrc_t bcst = rsrc_of(S.cstart + p0, 4ll * ((np + 3) & ~3));
+  auto parents = [&](int p) {
+    const int np = min(pend - p, kUpBatch);
+    const __amdgpu_buffer_rsrc_t bcode = rsrc_of(S.code + p, (np + 3) & ~3);
+    const __amdgpu_buffer_rsrc_t bcst = rsrc_of(S.cstart + p, 4ll * ((np + 3) & ~3));
 #pragma unroll
     for (int q = 0; q < Q; q++) {
       const uint32_t t = 256u * q + 4u * lane;
       code[q] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(bcode, t, 0, 0);
       first[q] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(bcst, 4 * t, 0, 0);
     }
-  }
+  };
   // lanes of the input row's channels, and the lane with the occupancy bits
   const uint32_t c0 = 16 * g < C ? 16u * g : kNoRow;
   const uint32_t om = g == (C & 63) / 16 ? 0xFFu : 0u;
   const uint32_t st0 = (uint32_t)(C / 4 * g);
   const uint32_t below = (1u << o) - 1u;
 
-  const int cfirst = __builtin_amdgcn_readfirstlane(first[0][0]);
-  const int cbase = min(max(cfirst, 0), S.child_rows);
-  const __amdgpu_buffer_rsrc_t bin = rsrc_of(S.in + (int64_t)p0 * C, (int64_t)np * C);
-  const __amdgpu_buffer_rsrc_t bout =
-      rsrc_of(S.out + (int64_t)cbase * C, (int64_t)min(S.child_rows - cbase, 8 * kUpTile) * C);
-  int n = 0;
+  parents(p0);
+  for (; p0 < pend; p0 += kUpBatch) {
+    const int np = min(pend - p0, kUpBatch);
+    const int cfirst = __builtin_amdgcn_readfirstlane(first[0][0]);
+    const int cbase = min(max(cfirst, 0), S.child_rows);
+    const __amdgpu_buffer_rsrc_t bin = rsrc_of(S.in + (int64_t)p0 * C, (int64_t)np * C);
+    const __amdgpu_buffer_rsrc_t bout =
+        rsrc_of(S.out + (int64_t)cbase * C, (int64_t)min(S.child_rows - cbase, 8 * kUpBatch) * C);
+    int n = 0;
 #pragma unroll
-  for (int q = 0; q < Q; q++) {
-    if (256 * q >= np) break;
-    const int left = np - (256 * q + 4 * lane);  // parents of this lane inside the tile
-    const uint32_t cw = left >= 4 ? code[q] : (left <= 0 ? 0u : code[q] & ((1u << (8 * left)) - 1u));
+    for (int q = 0; q < Q; q++) {
+      if (256 * q >= np) break;
+      const int left = np - (256 * q + 4 * lane);  // parents of this lane inside the batch
+      const uint32_t cw = left >= 4 ? code[q] : (left <= 0 ? 0u : code[q] & ((1u << (8 * left)) - 1u));
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const uint32_t cd = (cw >> (8 * i)) & 0xFFu;
-      const bool has = (cd >> o) & 1u;
-      const uint64_t m = __ballot(has);
-      const uint32_t at = (uint32_t)(first[q][i] - cbase) + (uint32_t)__popc(cd & below);
-      if (has) list[n + (int)lanes_below(m)] = (256u * q + 4u * lane + i) | (cd << 10) | (min(at, 0x3FFFu) << 18);
-      n += __popcll(m);
-    }
-  }
-  if (lane < 16) list[n + lane] = kNoChild;
-  wave_lds_sync();
-  const int G = (n + 15) >> 4;
-  if (G == 0) return;
-
-  auto entry = [&](int gi) { return list[16 * min(gi, G - 1) + r]; };
-  auto row = [&](uint32_t e) {
-    return (v4i)__builtin_amdgcn_raw_buffer_load_b128(bin, (e & 0x3FFu) * (uint32_t)C + c0, 0, 0);
-  };
-  auto group = [&](uint32_t e, const v4i& x) {
-    // occupancy bits as int8 {0, 127}
-    const uint32_t cd = (e >> 10) & om;
-    const uint32_t lo = __builtin_amdgcn_perm(0u, 0x7F00u, __umul24(cd & 15u, 0x204081u) & 0x01010101u);
-    const uint32_t hi = __builtin_amdgcn_perm(0u, 0x7F00u, __umul24(cd >> 4, 0x204081u) & 0x01010101u);
-    v4i acc[NBS];
-#pragma unroll
-    for (int nb = 0; nb < NBS; nb++) {
-      if (KS == 1) {
-        acc[nb] = mfma16(wb[0][nb], v4i{x[0] | (int)lo, x[1] | (int)hi, x[2], x[3]}, bb[nb]);
-      } else {
-        acc[nb] = mfma16(wb[KS - 1][nb], v4i{(int)lo, (int)hi, 0, 0}, bb[nb]);
-        acc[nb] = mfma16(wb[0][nb], x, acc[nb]);
+      for (int i = 0; i < 4; i++) {
+        const uint32_t cd = (cw >> (8 * i)) & 0xFFu;
+        const bool has = (cd >> o) & 1u;
+        const uint64_t m = __ballot(has);
+        const uint32_t at = (uint32_t)(first[q][i] - cbase) + (uint32_t)__popc(cd & below);
+        if (has) list[n + (int)lanes_below(m)] = (256u * q + 4u * lane + i) | (cd << 10) | (min(at, 0x3FFFu) << 18);
+        n += __popcll(m);
       }
     }
-    typedef typename RowPart<C>::T T;
-    T none;
-    const T y = row_out<C, FL, true>(acc, L, false, none);
-    const uint32_t at = (e >> 18) * (uint32_t)C + st0;
-    if constexpr (C == 64) __builtin_amdgcn_raw_buffer_store_b128(y, bout, at, 0, 0);
-    else if constexpr (C == 32) __builtin_amdgcn_raw_buffer_store_b64(y, bout, at, 0, 0);
-    else __builtin_amdgcn_raw_buffer_store_b32(y[0], bout, at, 0, 0);
-  };
-  uint32_t e[3], en;
-  v4i x[3];
+    if (lane < 16) list[n + lane] = kNoChild;
+    wave_lds_sync();
+    if (p0 + kUpBatch < pend) parents(p0 + kUpBatch);
+    const int G = (n + 15) >> 4;
+    if (G == 0) continue;
+
+    auto entry = [&](int gi) { return list[16 * min(gi, G - 1) + r]; };
+    auto row = [&](uint32_t e) {
+      return (v4i)__builtin_amdgcn_raw_buffer_load_b128(bin, (e & 0x3FFu) * (uint32_t)C + c0, 0, 0);
+    };
+    auto group = [&](uint32_t e, const v4i& x) {
+      // occupancy bits as int8 {0, 127}
+      const uint32_t cd = (e >> 10) & om;
+      const uint32_t lo = __builtin_amdgcn_perm(0u, 0x7F00u, __umul24(cd & 15u, 0x204081u) & 0x01010101u);
+      const uint32_t hi = __builtin_amdgcn_perm(0u, 0x7F00u, __umul24(cd >> 4, 0x204081u) & 0x01010101u);
+      v4i acc[NBS];
 #pragma unroll
-  for (int k = 0; k < 3; k++) e[k] = entry(k);
+      for (int nb = 0; nb < NBS; nb++) {
+        if (KS == 1) {
+          acc[nb] = mfma16(wb[0][nb], v4i{x[0] | (int)lo, x[1] | (int)hi, x[2], x[3]}, bb[nb]);
+        } else {
+          acc[nb] = mfma16(wb[KS - 1][nb], v4i{(int)lo, (int)hi, 0, 0}, bb[nb]);
+          acc[nb] = mfma16(wb[0][nb], x, acc[nb]);
+        }
+      }
+      typedef typename RowPart<C>::T T;
+      T none;
+      const T y = row_out<C, FL, true>(acc, L, false, none);
+      const uint32_t at = (e >> 18) * (uint32_t)C + st0;
+      if constexpr (C == 64) __builtin_amdgcn_raw_buffer_store_b128(y, bout, at, 0, 0);
+      else if constexpr (C == 32) __builtin_amdgcn_raw_buffer_store_b64(y, bout, at, 0, 0);
+      else __builtin_amdgcn_raw_buffer_store_b32(y[0], bout, at, 0, 0);
+    };
+    uint32_t e[3], en;
+    v4i x[3];
 #pragma unroll
-  for (int k = 0; k < 3; k++) {
-    x[k] = row(e[k]);
-    __builtin_amdgcn_sched_barrier(0);  // in the order of use
-  }
-  int gi = 0;
-  for (; gi + 3 <= G; gi += 3) {
+    for (int k = 0; k < 3; k++) e[k] = entry(k);
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-      en = entry(gi + k + 3);
-      group(e[k], x[k]);
-      e[k] = en;
-      x[k] = row(en);
-      __builtin_amdgcn_sched_barrier(0);  // else the loads sink below the next group
+      x[k] = row(e[k]);
+      __builtin_amdgcn_sched_barrier(0);  // in the order of use
     }
+    int gi = 0;
+    for (; gi + 3 <= G; gi += 3) {
+#pragma unroll
+      for (int k = 0; k < 3; k++) {
+        en = entry(gi + k + 3);
+        group(e[k], x[k]);
+        e[k] = en;
+        x[k] = row(en);
+        __builtin_amdgcn_sched_barrier(0);  // else the loads sink below the next group
+      }
+    }
+    if (gi < G) group(e[0], x[0]);
+    if (gi + 1 < G) group(e[1], x[1]);
+    wave_lds_sync();  // the list is written again
   }
-  if (gi < G) group(e[0], x[0]);
-  if (gi + 1 < G) group(e[1], x[1]);
 }
 
 hipError_t launch_up_slots(int C, const GemmSeg* segs, const Tile* tiles, int ntiles, const GemmArg& A,
                            hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (64 * A.tpw > kUpTile) return hipErrorInvalidValue;
 #define LPCC_U(CC)                                                                                            \
   if (C == CC) {                                                                                              \
     if (A.fl == F_FAST)                                                                                       \

@@ -722,7 +722,7 @@ int64_t count_tiles(const std::vector<int64_t>& rows, int rows_per_tile = 64) {
 // (parents per block): 101 (64), 111 (128), 112 (256), 114 (512), 102 (1024).
 // Upsampling: 201 / 202 (occupied children, 256 / 1024 parents per block) or
 // 210 + rb (all child slots of every parent).
-constexpr int kUpSmall = 256, kUpLarge = kUpTile;
+constexpr int kUpSmall = 256, kUpLarge = 1024;
 constexpr int kCUs = 256;  // compute units of the device
 constexpr int kDenseTiles = 2 * kCUs;
 // Larger convolutions are not timed with the taps shared by a block: of some
