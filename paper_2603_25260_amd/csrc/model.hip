@@ -1117,49 +1117,62 @@ __device__ __forceinline__ uint32_t recip_k(uint32_t S) {  // floor(65281 * 2^16
 // for a single user, and it forms the multiply-add with the quarter-rate
 // 64-bit one.  No matrix instruction is in flight here (the maximum over all
 // logits comes first).  The compare's VCC may be read as a carry only two wait
-// states later, and the compiler does not look inside the asm: the first two
-// instructions of the next entry lie in between.
-struct FreqStep {
-  uint32_t m, t;  // E K + 2^16 (q1 in its high half), q1 S
-};
-__device__ __forceinline__ FreqStep freq_begin(uint32_t E, uint32_t S, uint32_t K) {
-  FreqStep f;
-  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(f.m) : "v"(E), "v"(K), "s"(0x10000));
+// states later, and the compiler does not look inside the asm.  An s_nop costs
+// the least where four waves per SIMD fill the issue slots: the encoder's
+// predictor takes 1.40 ms for 8 128-beam frames, 1.43 ms with the next entry's
+// instructions in between (freq_next).
+__device__ __forceinline__ uint32_t freq_mad(uint32_t E, uint32_t K) {
+  uint32_t m;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(m) : "v"(E), "v"(K), "s"(0x10000));
+  return m;
+}
+__device__ __forceinline__ uint32_t freq_mul(uint32_t m, uint32_t S) {
+  uint32_t t;
   asm("v_mul_u32_u24_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD"
-      : "=v"(f.t)
-      : "v"(f.m), "v"(S));
-  return f;
+      : "=v"(t)
+      : "v"(m), "v"(S));
+  return t;
 }
-// run + f of entry E, begun in s; begins the entry En in s
-__device__ __forceinline__ uint32_t freq_next(uint32_t run, FreqStep& s, uint32_t E, uint32_t En, uint32_t S,
-                                              uint32_t K) {
-  FreqStep n;
+__device__ __forceinline__ uint32_t freq_end(uint32_t run, uint32_t m, uint32_t t, uint32_t p) {
   uint32_t o;
-  const uint32_t p = __umul24(E & 0xFFFFu, 65281u);
-  asm("v_cmp_le_u32_e32 vcc, %3, %4\n\t"
-      "v_mad_u32_u24 %1, %5, %6, %7\n\t"
-      "v_mul_u32_u24_sdwa %2, %1, %8 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n\t"
-      "v_addc_co_u32_sdwa %0, vcc, %9, %10, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
-      : "=v"(o), "=&v"(n.m), "=&v"(n.t)
-      : "v"(s.t), "v"(p), "v"(En), "v"(K), "s"(0x10000), "v"(S), "v"(run), "v"(s.m)
-      : "vcc");
-  s = n;
-  return o;
-}
-// run + f of the last entry E, begun in s
-__device__ __forceinline__ uint32_t freq_last(uint32_t run, const FreqStep& s, uint32_t E) {
-  uint32_t o;
-  const uint32_t p = __umul24(E & 0xFFFFu, 65281u);
   asm("v_cmp_le_u32_e32 vcc, %1, %2\n\t"
       "s_nop 1\n\t"
       "v_addc_co_u32_sdwa %0, vcc, %3, %4, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
       : "=v"(o)
-      : "v"(s.t), "v"(p), "v"(run), "v"(s.m)
+      : "v"(t), "v"(p), "v"(run), "v"(m)
       : "vcc");
   return o;
 }
-__device__ __forceinline__ uint32_t freq_of(uint32_t E, uint32_t S, uint32_t K) {
-  return freq_last(0u, freq_begin(E, S, K), E);
+__device__ __forceinline__ uint32_t freq_prod(uint32_t E) { return __umul24(E & 0xFFFFu, 65281u); }
+__device__ __forceinline__ uint32_t freq_add(uint32_t run, uint32_t E, uint32_t S, uint32_t K) {
+  const uint32_t m = freq_mad(E, K);
+  return freq_end(run, m, freq_mul(m, S), freq_prod(E));
+}
+
+// The same over consecutive entries, with the next entry's products in between:
+// 2.86 ms for the decoder of 8 128-beam frames, three waves per SIMD, 2.91 ms
+// with the s_nop.
+struct FreqStep {
+  uint32_t m, t, p;  // of the next entry: E K + 2^16 (q1 in its high half), q1 S, E 65281
+};
+__device__ __forceinline__ FreqStep freq_begin(uint32_t E, uint32_t S, uint32_t K) {
+  const uint32_t m = freq_mad(E, K);
+  return FreqStep{m, freq_mul(m, S), freq_prod(E)};
+}
+// run + f of the entry begun in s; begins the entry E1 in s
+__device__ __forceinline__ uint32_t freq_next(uint32_t run, FreqStep& s, uint32_t E1, uint32_t S, uint32_t K) {
+  FreqStep n;
+  uint32_t o;
+  asm("v_cmp_le_u32_e32 vcc, %4, %5\n\t"
+      "v_mad_u32_u24 %1, %6, %7, %8\n\t"
+      "v_mul_u32_u24_e32 %3, %9, %6\n\t"
+      "v_mul_u32_u24_sdwa %2, %1, %10 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_addc_co_u32_sdwa %0, vcc, %11, %12, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+      : "=v"(o), "=&v"(n.m), "=&v"(n.t), "=&v"(n.p)
+      : "v"(s.t), "v"(s.p), "v"(E1), "v"(K), "s"(0x10000), "s"(65281), "v"(S), "v"(run), "v"(s.m)
+      : "vcc");
+  s = n;
+  return o;
 }
 
 // Reductions over the lanes of a node.  Both forms join the four lane groups
@@ -1309,8 +1322,8 @@ __device__ __forceinline__ void row_prefix(int (&e)[SMALL ? 16 : 64], const Node
   FreqStep fs = freq_begin((uint32_t)e[0], n.S, n.K);
 #pragma unroll
   for (int j = 0; j < NS; j++) {
-    const uint32_t next = j + 1 < NS ? freq_next(run, fs, (uint32_t)e[j], (uint32_t)e[(j + 1) % NS], n.S, n.K)
-                                     : freq_last(run, fs, (uint32_t)e[j]);
+    const uint32_t next =
+        j + 1 < NS ? freq_next(run, fs, (uint32_t)e[(j + 1) % NS], n.S, n.K) : freq_end(run, fs.m, fs.t, fs.p);
     e[j] = (int)run;
     run = next;
   }
@@ -1344,7 +1357,7 @@ __device__ __forceinline__ v4i row_chunk(const int (&e)[NS], int c, int ablk, ui
 // smaller table entry gives a smaller frequency: the table falls by at least
 // 1984 of 32768 from entry 0 to 1, and S < 2^23).
 __device__ __forceinline__ void row_remainder(uint32_t* p, const NodeSum& n, uint32_t R) {
-  const uint32_t fmax = freq_of(32768u, n.S, n.K) & 0xFFFFu;
+  const uint32_t fmax = freq_add(0u, 32768u, n.S, n.K) & 0xFFFFu;
   const uint32_t lo = p[0], hi = p[1];
   const uint32_t v0 = lo & 0xFFFFu, v1 = lo >> 16, v2 = hi & 0xFFFFu, v3 = hi >> 16;
   const bool a0 = ((v1 - v0) & 0xFFFFu) == fmax;
@@ -1435,7 +1448,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
       // the lanes before it add their totals.
       const int sord = sym / NS, sblk = n.ord == sord ? (sym % NS) / 4 : -1;
       uint32_t run = 0, runb = 0, rlast = 0;
-      FreqStep fs = freq_begin((uint32_t)e[0], n.S, n.K);
 #pragma unroll
       for (int b = 0; b < NBL; b++) {
         if (b == sblk) {
@@ -1444,10 +1456,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
         }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          const int j = 4 * b + i;
-          if (j == NS - 1) rlast = run;
-          run = j + 1 < NS ? freq_next(run, fs, (uint32_t)e[j], (uint32_t)e[(j + 1) % NS], n.S, n.K)
-                           : freq_last(run, fs, (uint32_t)e[j]);
+          if (4 * b + i == NS - 1) rlast = run;
+          run = freq_add(run, (uint32_t)e[4 * b + i], n.S, n.K);
         }
       }
       const uint32_t tot = n.tail ? rlast : run;
@@ -1461,7 +1471,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
         bool lower = false, here = false;  // the maximum lies at a lower entry of the block / at the symbol
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          const uint32_t f = freq_of((uint32_t)es[i], n.S, n.K);
+          const uint32_t f = freq_add(0u, (uint32_t)es[i], n.S, n.K);
           st += i < si ? f : 0u;
           fr = i == si ? f : fr;
           lower = lower || (i < si && es[i] == 32768);
@@ -1604,7 +1614,7 @@ __device__ __forceinline__ void put_lane(uint32_t& v, uint32_t s, int k) {
 }
 
 // Three waves per SIMD: LDS holds four blocks of NP = 2 (36 KB and the payload
-// each) per compute unit, and the predictor takes 129 to 138 registers here.
+// each) per compute unit, and the predictor takes up to 130 registers here.
 template <int C, int NP, int RQ>
 __global__ __launch_bounds__(64 * (NP + 1)) __attribute__((amdgpu_waves_per_eu(3))) void k_decode_chunks(
     const Chunk* __restrict__ chunks, const uint8_t* __restrict__ payload, const int32_t* __restrict__ lut_g,

@@ -5,7 +5,7 @@ but does not look inside inline assembly, so its listing is checked as a whole:
 * a scalar register or VCC written by a vector instruction (compare, carry,
   lane read) and read by one: 2 wait states (4 as a lane select);
 * a vector register written by a vector instruction and read across lanes by
-  DPP: 2; by a lane read: 1.
+  DPP or a lane swap: 2; by a lane read: 1.
 
 Every instruction in between counts one, ``s_nop n`` n + 1.  And the occupancy
 that a kernel's attributes state is one its registers allow."""
@@ -24,6 +24,7 @@ KERNEL_SOURCES = ["octree.hip", "model.hip", "rc.hip"]
 REG = re.compile(r"\b([sv])(\d+)\b|\b([sv])\[(\d+):(\d+)\]|\b(vcc)(_lo|_hi)?\b")
 CARRY_OUT = re.compile(r"v_(add|addc|sub|subb|subrev|subbrev)_co_|v_mad_[ui]64_")
 LANE = re.compile(r"v_(readlane|writelane)_b32")
+SWAP = re.compile(r"v_permlane(16|32)_swap")
 READ_LANE = re.compile(r"v_read(first)?lane")
 
 
@@ -55,6 +56,8 @@ def violations(body):
             vector = op.startswith("v_") and not op.startswith("v_mfma")
             ndef = 2 if CARRY_OUT.match(op) else 1
             defs, uses = regs(",".join(args[:ndef])), args[ndef:]
+            if SWAP.match(op):  # both operands are read and written
+                defs, uses = regs(rest), args
             close = set()
             if vector:
                 for k, a in enumerate(uses):
@@ -67,6 +70,8 @@ def violations(body):
                         elif READ_LANE.match(op):
                             need = 1
                         elif re.search(r"\b(quad_perm|row_|wave_)", rest) and k == 0:
+                            need = 2
+                        elif SWAP.match(op):
                             need = 2
                         if age[r][0] < need:
                             close.add((age[r][0], need, age[r][1], line))
@@ -124,6 +129,8 @@ def test_stated_occupancy_is_reached(asm, src):
     ("v_max_u32_e32 v1, v2, v3\nv_readlane_b32 s4, v1, s5", 1),
     ("v_max_u32_e32 v1, v2, v3\ns_ff1_i32_b64 s5, s[6:7]\nv_readlane_b32 s4, v1, s5", 0),
     ("v_max_u32_e32 v1, v2, v3\nv_nop\nv_min_u32_dpp v4, v1, v5 wave_shr:1 row_mask:0xf bank_mask:0xf", 1),
+    ("v_add_u32_e32 v1, v2, v3\nv_mov_b32_e32 v4, v5\nv_permlane16_swap_b32_e32 v1, v6", 1),
+    ("v_add_u32_e32 v1, v2, v3\ns_nop 1\nv_permlane16_swap_b32_e32 v1, v6", 0),
     ("v_cmp_le_u32_e64 s[0:1], v1, v2\ns_and_b64 vcc, s[0:1], s[2:3]", 0),
 ])
 def test_detector(body, n):
