@@ -196,19 +196,19 @@ FAMILY_BOUND = {"conv": "hbm", "down": "hbm", "skip": "hbm", "emb": "hbm", "up":
 # what the same counters read for a 256 MiB device copy (fetch x2, write x1).
 # They hold for the library sources whose digest is TRAFFIC_SOURCES; any other
 # source tree reports traffic null.
-TRAFFIC_SOURCES = "668293a82610b1ee"
+TRAFFIC_SOURCES = "7c468989866da520"
 FAMILY_TRAFFIC = {
-    "conv": (6008226684, 2248017151),
-    "down": (1607387348, 2081497215),
-    "skip": (1707822211, 853240960),
-    "emb": (3185717, 170779340),
-    "up": (3977180695, 4444667148),
-    "predict": (837734373, 52342387),
-    "decode": (854779605, 15637462),
-    "rc_encode": (58726162, 19075567),
-    "hash": (516034354, 808287584),
-    "expand": (136322436, 170685344),
-    "pack": (32340150, 15933325),
+    "conv": (6004233798, 2248017151),
+    "down": (1607320682, 2081497215),
+    "skip": (1707835364, 853240960),
+    "emb": (3185735, 170779335),
+    "up": (4004494503, 4479041319),
+    "predict": (837762419, 52342377),
+    "decode": (854874578, 15637302),
+    "rc_encode": (58725992, 19127518),
+    "hash": (515908199, 808269491),
+    "expand": (136323411, 170685344),
+    "pack": (32340278, 15933377),
 }
 
 

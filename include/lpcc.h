@@ -288,7 +288,9 @@ void lpcc_server_free(lpcc_server* s);
 /*
  * Kernel timing (measurement, no part of the method): when enabled, the context records HIP events around every
  * launch of the kernel family named `name` ("predict", "conv", "up", ...) on
- * its stream and accumulates their durations.  lpcc_timing_read returns the
+ * its stream and accumulates their durations.  A decode's predictor and range
+ * decoder of a modelled depth are one launch, family "decode"; "rc_decode" has
+ * the base depths.  lpcc_timing_read returns the
  * number of launches and the summed milliseconds since the last reset.
  */
 int lpcc_timing_enable(lpcc_ctx* c, const char* name);

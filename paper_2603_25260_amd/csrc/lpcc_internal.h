@@ -19,10 +19,13 @@ constexpr int kTaps3 = 27;
 
 enum LayerKind { K_EMB = 1, K_DOWN, K_CONV1, K_CONV2, K_SKIP, K_UP, K_FC1, K_FC2 };
 
-// One layer as the kernels see it.  Weights are packed for the B operand of
-// v_mfma_i32_16x16x64_i8: for k-step s (64 input rows k) and column block nb
-// (16 outputs) lane l holds 16 bytes W[64 s + 16 (l/16) + i][16 nb + l%16],
-// i = 0..15, zero-padded beyond K = taps*cin and cout.
+// One layer as the kernels see it.  Weights are packed for the row operand of
+// v_mfma_i32_16x16x64_i8: for k-step s (64 input rows k) and block nb of 16
+// outputs lane l holds 16 bytes W[64 s + 16 (l/16) + i][o(nb, l%16)], i =
+// 0..15, zero-padded beyond K = taps*cin and cout.  The output o is 16 nb +
+// l%16 for the predictor's first layer, out_channel (per child slot for the
+// upsampling) for the sparse and dense layers, logit_symbol for the logits,
+// whose K order is logit_channel's.
 struct LayerDev {
   const int8_t* Wp;     // packed weights, Kpad x Npad bytes
   const int8_t* Wr;     // row-major W[taps][cin][cout] (VALU paths)
@@ -187,8 +190,9 @@ struct PredSeg {
 
 // A launch with a single segment passes it, with its layers, by value in the
 // kernel arguments (no dependent descriptor loads before the first data
-// load); tile t then covers rows [64 t, 64 t + 64).  Otherwise `one` is 0 and
-// blocks read their tile and segment from the descriptor arrays.
+// load); tile t then covers rows [n t, n t + n), n the launch's rows per tile
+// (16 to 2048).  Otherwise `one` is 0 and blocks read their tile and segment
+// from the descriptor arrays.
 struct GemmArg {
   GemmSeg seg;
   LayerDev L;

@@ -814,7 +814,12 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {  // set bits of m 
 // between barriers, with the weights reloaded at each change of slot, took 1.69
 // ms.  Tiles of 512 / 1024 / 2048 parents: 1.39 / 1.38 / 1.38 ms, and 1.44 /
 // 1.46 / 1.57 ms in the smaller launches of a decode of the same frames; tiles
-// of 256 are for launches that would leave compute units idle.
+// of 256 are for launches that would leave compute units idle.  With the tiles
+// in use, 256 and 1024, the loop over batches runs once.  It stays because the
+// kernel without it is slower: half the registers at C = 32, so four blocks
+// instead of two share a compute unit's caches, 0.86 -> 0.89 ms for the
+// encode of 8 such frames and 0.297 -> 0.317 ms for 32 uneven ones (0.303 ms
+// with the waves held at four per SIMD).
 constexpr uint32_t kNoChild = 0x3FFFu << 18;
 constexpr int kUpBatch = 1024;
 
@@ -1022,8 +1027,8 @@ __global__ __launch_bounds__(256) void k_emb(const GemmSeg* __restrict__ segs, c
 // The same for launches of many rows: a block computes the 256 possible rows
 // once, into LDS, and copies one per code, 16 bytes per thread.  It pays from
 // about a thousand rows per block (computed, a row costs 14 instructions per
-// channel).  The largest launch of 8 128-beam frames (C = 64): 28 us, 98 us
-// computed row by row.
+// channel).  The launches of 8 128-beam frames (C = 64): 28 us in the decode and
+// 39 us in the encode, 98 and 100 us computed row by row.
 template <int C>
 __global__ __launch_bounds__(256) void k_emb_rows(const GemmSeg* __restrict__ segs, const Tile* __restrict__ tiles,
                                                   const GemmArg A) {
@@ -1077,9 +1082,9 @@ hipError_t launch_emb(const GemmSeg* segs, const Tile* tiles, int ntiles, int C,
 //
 // Both products are formed transposed (weights as the MFMA row operand, nodes
 // as columns), and the row order of the logit weights is permuted on the host
-// (pack_logits), so that lane (r, g) ends with the 64 consecutive symbols
-// 64g .. 64g + 63 of ONE node, r.  Everything per node (M, S, the reciprocal,
-// the coded symbol) is then a per-lane value: the reductions run over the 4
+// (logit_symbol, logit_channel), so that lane (r, g) ends with the 64
+// consecutive symbols 64g .. 64g + 63 of ONE node, r.  Everything per node (M,
+// S, the reciprocal, the coded symbol) is then a per-lane value: the reductions run over the 4
 // lanes of a node, the prefix sums are serial inside a lane, and the biases
 // ride in the accumulators.  fc1's accumulators are already fc2's column
 // operand (the permutation of K is in the packed weights), so no activations
@@ -1088,7 +1093,7 @@ hipError_t launch_emb(const GemmSeg* segs, const Tile* tiles, int ntiles, int C,
 // The kernel is bound by vector instruction issue: this form needs 17.2
 // vector instructions per 64 logits in encode mode where the one with 16 lanes
 // per node needed 30.4, and for the 12.75 M nodes of 8 128-beam frames (18
-// levels, C = 64) it takes 1.58 ms where that took 2.39 ms.
+// levels, C = 64) it takes 1.40 ms where that took 2.39 ms.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t recip_k(uint32_t S) {  // floor(65281 * 2^16 / S), 2^15 <= S < 2^23
   uint32_t rem = 65281u << 16;  // < 2^32
@@ -1375,7 +1380,8 @@ enum { P_ENCODE = 0, P_CDF32 = 2 };
 // else 16 nodes per wave and `groups` such groups one after the other, so the
 // block's copy of the weights in LDS serves 64 x groups nodes.
 template <int C, int MODE, bool SMALL, int RQ>
-// at most 128 VGPRs (four waves per SIMD); the general requantisation needs more
+// at most 128 VGPRs (four waves per SIMD); the general requantisation may take
+// more
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4 : 3))) void k_predict(
     const PredSeg* __restrict__ segs, const Tile* __restrict__ tiles, const int32_t* __restrict__ lut_g, int groups,
     const PredArg A) {
@@ -1532,7 +1538,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RQ == 1 ? 4
 // one barrier per step.  The rows (512 bytes per node) so never leave the
 // compute unit, and the decoder's serial chain (latency) runs beside the
 // predictor's arithmetic (issue), which as two launches took turns: over the
-// 18 depths of 8 128-beam frames (12.75 M nodes) 2.28 + 1.92 ms became 2.99
+// 18 depths of 8 128-beam frames (12.75 M nodes) 2.28 + 1.92 ms became 2.86
 // ms, over the 12 depths of a 16-beam frame 390 us became 245 us.
 //
 // Range decoder (G. N. N. Martin 1979, as in rc.hip): state code and range,
@@ -1771,9 +1777,10 @@ __global__ __launch_bounds__(64 * (NP + 1)) __attribute__((amdgpu_waves_per_eu(3
 // 27.5 us with 3 (the chain, 175 cycles per symbol, sets the pace), 31.5 us
 // with 2 (it waits for rows; 66 us with 1) and 29 us with 5.  With thousands
 // of chunks both arithmetic and chains are in flight anyway, and 2 leave a
-// compute unit more chunks at once: the 8-frame 128-beam batch decodes in
-// 10.17 ms with 2 and 10.42 ms with 3, one such frame (at most 920 chunks) in
-// 2.58 and 2.54 ms.
+// compute unit more chunks at once: 8 128-beam frames decode in 8.04 ms with 2
+// and 8.28 ms with 3, one such frame (at most 920 chunks) in 2.12 and 2.09 ms,
+// a 64-beam frame in 0.87 and 0.82 ms.  With the 64-bit requantisation the line
+// lies at the same place: 8.70 and 8.92, 2.36 and 2.29, 0.92 and 0.86 ms.
 constexpr int kDecodeWide = 1024;
 
 hipError_t launch_decode_chunks(int C, const Chunk* chunks, int nchunks, const uint8_t* payload, const int32_t* lut,
